@@ -25,7 +25,7 @@ constexpr int kMaxPairRows = (2 * kMaxLAO + 1) * (2 * kMaxLAO + 1);   // functio
 // power-of-two scale 2^e (stored as a double) with |x| <= 127/128 2^e, and
 // x ~ 2^e sum_{s<kI8Slices} a_s 2^{-7(s+1)}, a_0 in [-127, 127], a_s in
 // [-64, 64].  Storage per row: chunks of kI8Chunk elements, each chunk the
-// kI8Slices slices one after another ([chunk][slice][64] bytes).  The
+// slices one after another ([chunk][slice][64] bytes; i8_slices of them).  The
 // contraction index of a slab runs over column passes of the half transform
 // (ht_pass_frags below), then aux rows, then the
 // pass's columns (its width rounded up to even, so every pass region is a
@@ -60,6 +60,7 @@ inline int64_t ht_ldc(int64_t ncol) { return ht_passes(ncol) * ht_pass_frags(nco
 // Contraction length of one aux slab of plen rows with ncol columns as the
 // precision stores it, and the bytes of its X buffers (main and second plane).
 inline bool is_int8(int precision) { return precision == DFJK_MIXED_INT8 || precision == DFJK_MIXED_INT8_FAST; }
+inline int i8_slices(int precision) { return precision == DFJK_MIXED_INT8_FAST ? kI8Slices - 1 : kI8Slices; }   // stored
 inline int64_t x_kdim(int precision, int64_t plen, int64_t ncol)
 {
     return plen * (is_int8(precision) ? ncol + (ncol & 1) : ncol);
@@ -71,7 +72,7 @@ inline size_t x_bytes(int precision, int64_t rows, int64_t kdim)
     case DFJK_FP64: return n * 8;
     case DFJK_MIXED_FP32: return n * 4;
     case DFJK_MIXED_BF16X3: return n * 2;
-    default: return n * kI8Slices;
+    default: return n * i8_slices(precision);
     }
 }
 inline size_t x_lo_bytes(int precision, int64_t rows, int64_t kdim)
@@ -194,7 +195,7 @@ struct Plan {
     hipStream_t j_stream = nullptr;     // side stream: J of a build, the integrals of a setup
     hipEvent_t ev_jfork = nullptr, ev_jdone = nullptr;
     // split counts chosen by dfjk_autotune for the closed-shell C-route build,
-    // keyed by nocc * 4 + precision
+    // keyed by nocc * 8 + precision
     std::map<int64_t, int> tuned_nsplit;
     std::map<int64_t, int> tuned_ktile;   // the FP64 K GEMM tile kept with that split count
     int device = 0;

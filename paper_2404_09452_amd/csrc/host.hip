@@ -1757,6 +1757,7 @@ static std::vector<int> autotune_candidates(const Plan &p, int32_t nocc, int32_t
     std::vector<int> c;
     std::vector<int> tiles = {kTileK};
     if (precision == DFJK_FP64) { tiles.push_back(64); tiles.push_back(96); }
+    if (precision == DFJK_MIXED_INT8_FAST) tiles.push_back(64);
     for (int kt : tiles) {
         const BuildLayout L = build_layout(p, nocc, precision, false, false, -1, true, 0, kt);   // built-in split
         const int64_t maxs = L.kdim / 256 > 0 ? L.kdim / 256 : 1;
@@ -1851,8 +1852,8 @@ int dfjk_autotune(dfjk_plan *plan, const double *d_C, int32_t nocc, int32_t prec
     HIP_OR_FAIL(err);
     HIP_OR_FAIL(hipGetLastError());
     const size_t best = (size_t)(std::min_element(t.begin(), t.end()) - t.begin());
-    p.tuned_nsplit[(int64_t)nocc * 4 + precision] = cands[best] % 1000;
-    p.tuned_ktile[(int64_t)nocc * 4 + precision] = cands[best] / 1000;
+    p.tuned_nsplit[(int64_t)nocc * 8 + precision] = cands[best] % 1000;
+    p.tuned_ktile[(int64_t)nocc * 8 + precision] = cands[best] / 1000;
     if (chosen) *chosen = cands[best];
     if (ncand) {
         const int nmax = *ncand;

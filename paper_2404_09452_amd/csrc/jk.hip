@@ -320,11 +320,11 @@ struct HTArgs {
     int32_t ldc;
     const int32_t *hk_off, *hk_row, *hk_nu;   // partner lists, each padded to a multiple of kHtChunk
     void *X;                  // [nao][plen][ncol]: aux rows p_begin .. p_begin + plen - 1
-                              // (int8 slices: [nao][kdim/64][5][64], see kI8Slices)
+                              // (int8 slices: [nao][kdim/64][nslice][64])
     void *Xlo;                // second plane for the BF16 split; block scales for int8
     int64_t p_begin, plen;    // aux slab (multiples of 128)
     const int32_t *order;     // blockIdx.y -> AO function (longest list first)
-    int32_t nslice;           // int8 slices written (the rest of each chunk is left as it was)
+    int32_t nslice;           // int8 slices stored
 };
 
 
@@ -352,7 +352,7 @@ template <int NCOL> struct HtLds {
 // rounded up to even wide).  Contraction index inside the slab:
 //   k = plen * ic0 + (P - p_begin) * w_e + (col - ic0),
 // so the workgroup owns 128 w_e / 256 whole scale blocks and one contiguous
-// byte range of the row (chunks of 64 k, five slices each).  Per block: the
+// byte range of the row (chunks of 64 k, nslice slices each).  Per block: the
 // largest |x| (LDS atomics on the bit pattern, which orders like the value
 // for non-negative doubles), e = the least exponent with 2^e > |x|max
 // 128/127, the scale 2^e to g.Xlo; then x 2^-e = sum_s a_s 2^{-7(s+1)} by
@@ -416,8 +416,8 @@ __device__ __forceinline__ void store_i8(const HTArgs &g, const f64x4 (&acc)[NIB
         bexp[tid] = e;
         static_cast<double *>(g.Xlo)[(int64_t)mu * nblk + kbase / kI8Block + tid] = ldexp(1.0, e);
     }
-    unsigned char *dst = static_cast<unsigned char *>(g.X) + (int64_t)mu * kdim * kI8Slices +
-                         (kbase / kI8Chunk) * (kI8Chunk * kI8Slices);
+    unsigned char *dst = static_cast<unsigned char *>(g.X) + (int64_t)mu * kdim * g.nslice +
+                         (kbase / kI8Chunk) * (kI8Chunk * g.nslice);
     const int qk = 32 * we;                                            // k of 32 aux rows
     for (int q = 0; q < 4; ++q) {
         __syncthreads();   // exponents written; the previous quarter's values read
@@ -438,7 +438,7 @@ __device__ __forceinline__ void store_i8(const HTArgs &g, const f64x4 (&acc)[NIB
             double t[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) t[u] = ldexp(st[kq + u], -e);
-            unsigned char *d = dst + (k / kI8Chunk) * (kI8Chunk * kI8Slices) + (k % kI8Chunk);
+            unsigned char *d = dst + (k / kI8Chunk) * (kI8Chunk * g.nslice) + (k % kI8Chunk);
 #pragma unroll
             for (int sl = 0; sl < kI8Slices; ++sl) {
                 if (sl >= g.nslice) break;
@@ -892,11 +892,13 @@ __global__ __launch_bounds__(256) void k_energies_grouped(EnergyGroup grp, doubl
 // (two per CU for these kernels) fit in one round, so no nearly empty last
 // round idles the chip; at least 256 k values per split.
 int mixed_nsplit(int64_t nao, int64_t kdim, bool lower, int num_cus);
-int i8_nsplit(int64_t nao, int64_t kdim, bool lower, int num_cus);
+int i8_fast_tile(int64_t nao);
+int i8_nsplit(int64_t nao, int64_t kdim, bool lower, int tile, int num_cus);
 void launch_gemm_i8(bool lower, const void *A, const double *sA, const void *B, const double *sB, int64_t nao,
-                    int64_t kdim, int nsplit, bool fast, double *part, hipStream_t s);
-void launch_gemm_i8_group(bool fast, int n, const void *const *X, const double *const *sX, const int64_t *nao,
-                          const int64_t *kdim, const int *nsplit, double *const *part, hipStream_t s);
+                    int64_t kdim, int nsplit, bool fast, int tile, double *part, hipStream_t s);
+void launch_gemm_i8_group(bool fast, int tile, int n, const void *const *X, const double *const *sX,
+                          const int64_t *nao, const int64_t *kdim, const int *nsplit, double *const *part,
+                          hipStream_t s);
 
 static int choose_ksplit(int ntiles, int64_t kdim, int num_cus, int per_cu = 2)
 {
@@ -932,7 +934,7 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     if (precision == DFJK_FP64 && !delta) {
         int kt = ktile != 0 ? ktile : p.k_tile;
         if (kt == 0 && nsplit == 0 && !with_D) {
-            const auto it = p.tuned_ktile.find((int64_t)nocc * 4 + precision);
+            const auto it = p.tuned_ktile.find((int64_t)nocc * 8 + precision);
             if (it != p.tuned_ktile.end()) kt = it->second;
         }
         if (kt == 0) {
@@ -941,13 +943,21 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
         }
         if (kt == 64 || kt == 96) L.ktile = kt;
     }
+    if (precision == DFJK_MIXED_INT8_FAST && !delta) {
+        int kt = ktile;
+        if (kt == 0 && nsplit == 0) {
+            const auto it = p.tuned_ktile.find((int64_t)nocc * 8 + precision);
+            if (it != p.tuned_ktile.end()) kt = it->second;
+        }
+        L.ktile = kt == 64 || kt == kTileK ? kt : i8_fast_tile(p.nao);
+    }
     L.ntile = (int)((p.nao + L.ktile - 1) / L.ktile);
     L.delta = delta;
     // aux slab of the K build: X = nao x slab x ncol elements per operand
     // bytes of X per element (both BF16 planes; int8 slices plus block scales)
     const double esz = precision == DFJK_FP64 ? 8.0
                      : precision == DFJK_MIXED_FP32 ? 4.0
-                     : precision == DFJK_MIXED_BF16X3 ? 4.0 : kI8Slices + 8.0 / kI8Block;
+                     : precision == DFJK_MIXED_BF16X3 ? 4.0 : i8_slices(precision) + 8.0 / kI8Block;
     // automatic: the largest multiple of 128 whose slab-sized buffers (X, its low part,
     // the expanded B of the density route, the second operand of the increment) stay
     // within kAutoSlabBytes
@@ -996,10 +1006,10 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     // 8 or more is rounded down to a multiple of the XCD count, so that the
     // syrk runs whole splits per XCD.
     L.nsplit_k = precision == DFJK_FP64 ? xcd_round(choose_ksplit(ntiles, L.kdim, p.num_cus, L.ktile == 64 ? 64 : L.ktile == 96 ? 32 : 16))
-               : is_int8(precision) ? i8_nsplit(p.nao, L.kdim, !delta, p.num_cus)
+               : is_int8(precision) ? i8_nsplit(p.nao, L.kdim, !delta, L.ktile, p.num_cus)
                                               : mixed_nsplit(p.nao, L.kdim, !delta, p.num_cus);
     if (nsplit == 0 && !with_D && !delta) {   // a split count the autotuner measured for this shape
-        const auto it = p.tuned_nsplit.find((int64_t)nocc * 4 + precision);
+        const auto it = p.tuned_nsplit.find((int64_t)nocc * 8 + precision);
         if (it != p.tuned_nsplit.end()) nsplit = it->second;
     }
     if (nsplit > 0) {   // a batch (or the autotuner) chooses the split count
@@ -1085,7 +1095,7 @@ static HTArgs ht_args(const Plan &p, int precision, const double *B, int64_t ld,
                       int64_t p_begin, int64_t plen, void *X, void *Xlo)
 {
     return HTArgs{B, ld, Cp, ncol, (int32_t)ht_ldc(ncol), p.d.hk_off, p.d.hk_row, p.d.hk_nu, X, Xlo, p_begin, plen,
-                  p.d.hk_order, precision == DFJK_MIXED_INT8_FAST ? kI8Slices - 1 : kI8Slices};
+                  p.d.hk_order, i8_slices(precision)};
 }
 
 static void launch_ht(const Plan &p, int precision, const double *B, int64_t ld, const double *Cp, int32_t ncol,
@@ -1108,7 +1118,7 @@ static void slab_gemm(const BuildLayout &L, bool lower, const void *X, const voi
                         L.nsplit_k, L.ktile, part, s);
     } else if (is_int8(L.precision)) {
         launch_gemm_i8(lower, X, static_cast<const double *>(Xlo), Bop, static_cast<const double *>(Bop_lo), nao,
-                       kdim, L.nsplit_k, L.precision == DFJK_MIXED_INT8_FAST, part, s);
+                       kdim, L.nsplit_k, L.precision == DFJK_MIXED_INT8_FAST, L.ktile, part, s);
     } else {
         launch_gemm_mixed(L.precision, lower, X, Xlo, Bop, Bop_lo, nao, kdim, L.nsplit_k, part, s);
     }
@@ -1402,7 +1412,7 @@ void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const 
     std::vector<const void *> i8x;                        // grouped int8 K: slices, scales, sizes, splits, partials
     std::vector<const double *> i8s;
     std::vector<int64_t> i8m, i8k;
-    std::vector<int> i8n;
+    std::vector<int> i8n, i8t;
     std::vector<double *> i8p;
     bool i8fast = false;
     std::vector<const double *> kx;
@@ -1438,6 +1448,7 @@ void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const 
                 i8m.push_back(nao);
                 i8k.push_back(x_kdim(L.precision, p.naux_pad, L.ncol));
                 i8n.push_back(L.nsplit_k);
+                i8t.push_back(L.ktile);
                 i8p.push_back(reinterpret_cast<double *>(sc + L.o_Kpart));
                 i8fast = L.precision == DFJK_MIXED_INT8_FAST;
                 continue;
@@ -1480,9 +1491,21 @@ void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const 
     // the half transforms of the one-slab molecules, grouped by output and fragment count
     launch_halftrans_groups<OUT_F64>(hts, s);
     launch_halftrans_groups<OUT_I8>(hts8, s);
-    if (!i8x.empty())
-        launch_gemm_i8_group(i8fast, (int)i8x.size(), i8x.data(), i8s.data(), i8m.data(), i8k.data(), i8n.data(),
-                             i8p.data(), s);
+    for (int T : {64, 128}) {   // one grouped int8 K per tile width
+        std::vector<const void *> gx;
+        std::vector<const double *> gs;
+        std::vector<int64_t> gm, gk;
+        std::vector<int> gn;
+        std::vector<double *> gp;
+        for (size_t i = 0; i < i8x.size(); ++i)
+            if (i8t[i] == T) {
+                gx.push_back(i8x[i]); gs.push_back(i8s[i]); gm.push_back(i8m[i]); gk.push_back(i8k[i]);
+                gn.push_back(i8n[i]); gp.push_back(i8p[i]);
+            }
+        if (!gx.empty())
+            launch_gemm_i8_group(i8fast, T, (int)gx.size(), gx.data(), gs.data(), gm.data(), gk.data(), gn.data(),
+                                 gp.data(), s);
+    }
     for (int T : {64, 96, 128}) {   // one grouped syrk per tile width
         std::vector<const double *> gx;
         std::vector<double *> gp;

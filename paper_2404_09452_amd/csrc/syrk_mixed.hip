@@ -230,23 +230,37 @@ __global__ __launch_bounds__(256) void k_gemm_mixed(MixedArgs g)
 // accumulators.  The only rounding is the truncation of the slices.
 //
 // DFJK_MIXED_INT8_FAST (FAST below) keeps the orders i + j <= 3 and the one
-// order-4 product a_2 b_2 (11 products; slice a_4 is neither loaded nor
+// order-4 product a_2 b_2 (11 products; slice a_4 is neither stored, loaded nor
 // used).  a_2 b_2 stays because on the diagonal it is a square: dropped, it
 // would shift every K_mu mu the same way and bias E_K (by 1e-6 Eh already on
 // three waters), whereas the other dropped order-4 products carry no sign.
 //
-// Workgroup: 128 rows x 64 columns of the output (half of a 128 x 128
-// partial tile, blockIdx.x = 2 tile + half), four waves of 64 x 32, each
-// 4 x 2 fragments of 16 x 16 with five int32 order accumulators (160
-// registers) and FP64 accumulators (64).  One wave per SIMD.  Operands move
-// straight from global memory into LDS (global_load_lds_dwordx4, no
-// registers): one wave instruction brings one MFMA operand fragment, 16 rows
-// x 64 k bytes of one slice, to 1 KB of LDS in lane order, so each later
-// fragment read is one contiguous 16-byte read per lane.  A chunk of 64 k is
-// 8 NS fragments of the 128 rows and 4 NS of the 64 columns for the NS slices
-// used (60 KB at NS = 5); two chunk
-// buffers, the next chunk in flight while the current one feeds the MFMAs,
-// one barrier per chunk.
+// What bounds it: the operand traffic from L2 into LDS.  Without the loads
+// the 128 x 64 FAST kernel below runs in 57% of its time; without its LDS reads
+// in 88%, without the folds in 91%.  So the loads are shaped first:
+//  - a DMA instruction (global_load_lds_dwordx4, 64 lanes x 16 bytes, LDS in
+//    lane order) takes consecutive 16-byte pieces of a row's chunk (64 k x NS
+//    slices, contiguous in X): 256 bytes of each of 4 rows for FAST.  One
+//    slice of 16 rows per instruction (64-byte segments) moved 6.6 TB/s and
+//    no more; this shape took 960 AO x 450,560 k from 3.58 to 2.67 ms (128 x 64
+//    tiles) and 3,840 x 655,360 from 67.0 to 54.2 ms (int8: 4.47 to 4.06 and
+//    84.0 to 76.0 ms).
+//  - inside a row the pieces are stored at a permuted slot, so that the 16
+//    rows of a fragment read fall on 16 different 16-byte bank groups: slot =
+//    piece xor (row mod 16) for the 16 pieces of FAST, (piece + (row / 4) mod 4)
+//    mod 20 for the 20 of five slices.
+//  - FAST keeps the fragments of the next chunk in a second register set, read
+//    while the MFMAs use the current one, with one barrier a chunk; its 128-wide
+//    form has three chunk buffers (two chunks in flight).  3,840 AO: 54.2 to
+//    49.7 (registers) to 48.4 ms (third buffer).  Five slices leave neither the
+//    registers nor the LDS for it: there a chunk is read, the barrier tells
+//    that its buffer is free, and the DMA of the chunk two ahead goes into it.
+//
+// Workgroup: 128 rows x 64 columns of the output (half of a 128 x 128 partial
+// tile, blk = 2 tile + half) on eight waves, or (FAST, narrow molecules) a
+// 64 x 64 tile on four waves with two workgroups per CU, each wave 2 x 2
+// fragments of 16 x 16: five int32 order accumulators (80 registers), FP64
+// accumulators (32).
 // 16x16x64 i8 layout: lane l supplies row l%16 and 16 consecutive k bytes of
 // k group l/16 for both operands; accumulator r of lane l is D[4(l/16)+r][l%16].
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -254,49 +268,48 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 // s_waitcnt immediates (gfx9 encoding: vmcnt bits 3:0 and 15:14, expcnt
 // 6:4, lgkmcnt 11:8; a field at its maximum does not wait).  Issued through
 // the builtin so the compiler's own wait insertion knows what has retired.
-constexpr int kWaitVm15 = 15 | (7 << 4) | (15 << 8);             // vmcnt(15)
-constexpr int kWaitVm0 = 0 | (7 << 4) | (15 << 8);               // vmcnt(0)
+constexpr int i8_wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+constexpr int i8_wait_vm_lgkm0(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
 constexpr int kWaitLgkm0 = 15 | (7 << 4) | (0 << 8) | (3 << 14);  // lgkmcnt(0)
-constexpr int kI8WavesM = 4;   // waves along the 128 rows: 2 (one wave per SIMD) or 4 (two)
 
 struct I8Args {
-    const unsigned char *A, *B;   // [M][kdim / 64][5][64] slices
+    const unsigned char *A, *B;   // [M][kdim / 64][NS][64] slices
     const double *sA, *sB;        // [M][kdim / 256] block scales
     int64_t kdim, M, ksplit;      // ksplit: a multiple of kI8Block
     int ntm;
     int lower;
     int nsplit;
-    double *partial;              // [split][tile][128][128]
+    double *partial;              // [split][tile][TM][TM]
 };
 
-// WGM x WGN waves, each RB x CB fragments of 16 x 16 (the workgroup tile
-// is always 128 x 64).  Fragments of a chunk are spread over the waves,
-// NFW per wave, padded with loads into a spare LDS slot so that every wave
-// issues the same count (the vmcnt immediate below).
-template <int WGM, int WGN, int RB, int CB, bool FAST>
+// TM x 64 outputs (TM = 128: half of a 128-wide tile; 64: a whole tile) on
+// waves of 32 x 32.
+template <int TM, bool FAST>
 __device__ __forceinline__ void gemm_i8_tile(I8Args g, unsigned blk)
 {
-    constexpr int NW = WGM * WGN, NT = 64 * NW;
-    constexpr int AR = WGM * RB * 16, BR = WGN * CB * 16;                 // rows of the two operands
-    static_assert(AR == T && BR == T / 2, "the workgroup tile is half of a 128 x 128 partial tile");
-    constexpr int RBA = AR / 16, RBB = BR / 16;
-    constexpr int NS = FAST ? kI8Slices - 1 : kI8Slices;                 // slices loaded
-    constexpr int FA = RBA * NS, FB = RBB * NS, NF = FA + FB;           // fragments per chunk
+    constexpr int WGN = 2, WGM = TM / 32, NW = WGM * WGN, RB = 2, CB = 2;
+    constexpr bool HALF = TM == 128;
+    static_assert(TM == 128 || (TM == 64 && FAST), "64-wide tiles are FAST only");
+    constexpr int AR = TM, BR = 64;                                      // rows of the two operands
+    constexpr int NS = FAST ? kI8Slices - 1 : kI8Slices;                 // slices stored and loaded
+    constexpr int NP = NS * kI8Chunk / 16, PITCH = NP * 16;              // 16-byte pieces and bytes of a row's chunk
+    constexpr int NF = (AR + BR) * NP / 64, NFA = AR * NP / 64;          // DMA instructions per chunk, those of A
     constexpr int NFW = (NF + NW - 1) / NW, NFS = NFW * NW;              // per wave; slots incl. spares
-    constexpr int CH = kI8Slices * kI8Chunk;                             // bytes of one row per chunk
-    static_assert(NFW <= 15, "vmcnt immediate holds 4 bits here");
-    constexpr int kWaitVmNFW = NFW | (7 << 4) | (15 << 8);              // vmcnt(NFW)
-    // two chunk buffers as separate arrays: the compiler can then tell a
-    // read of one from a DMA into the other (which buffer is known at
-    // compile time below) and does not wait for unrelated loads
+    constexpr int NBUF = FAST && HALF ? 3 : 2;
+    static_assert(AR * NP % 64 == 0 && (AR + BR) * NP % 64 == 0, "whole DMA instructions per operand");
+    // chunk buffers as separate arrays: the compiler can then tell a read of
+    // one from a DMA into another (which buffer is known at compile time
+    // below) and does not wait for unrelated loads
     __shared__ __attribute__((aligned(1024))) unsigned char sm0[NFS * 1024];
     __shared__ __attribute__((aligned(1024))) unsigned char sm1[NFS * 1024];
+    __shared__ __attribute__((aligned(1024))) unsigned char sm2[NBUF == 3 ? NFS * 1024 : 16];
 
     // workgroup -> (split, tile, half).  With a split count that is a multiple
     // of the XCD count, XCD x (workgroups are dispatched round-robin over the
     // XCDs) runs whole splits x, x + 8, ..., so each XCD's L2 holds one k
     // range of X for every tile of a split.
-    const int nth = 2 * (g.lower ? g.ntm * (g.ntm + 1) / 2 : g.ntm * g.ntm);   // tile halves per split
+    const int nt = g.lower ? g.ntm * (g.ntm + 1) / 2 : g.ntm * g.ntm;   // tiles per split
+    const int nth = HALF ? 2 * nt : nt;                                  // workgroups per split
     int split, th;
     if (g.nsplit % kXcds == 0) {
         const int xcd = blk % kXcds, local = blk / kXcds;
@@ -306,43 +319,54 @@ __device__ __forceinline__ void gemm_i8_tile(I8Args g, unsigned blk)
         split = blk / nth;
         th = blk % nth;
     }
-    const int half = th & 1, tile = th >> 1;
+    const int half = HALF ? th & 1 : 0, tile = HALF ? th >> 1 : th;
     int tm, tn;
     mixed_tile(tile, g.lower, g.ntm, tm, tn);
-    const int64_t m0 = (int64_t)tm * T, n0 = (int64_t)tn * T + 64 * half;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave / WGN, wn = wave % WGN;
+    const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TM + 64 * half;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WGN, wn = wave % WGN;
     const int64_t kb = (int64_t)split * g.ksplit;
     const int64_t ke = min(kb + g.ksplit, g.kdim);
-    const int64_t rowb = g.kdim * kI8Slices;          // bytes per row
+    const int64_t rowb = g.kdim * NS;                 // bytes per row
     const int64_t nblk = g.kdim / kI8Block;
 
-    // this lane's byte offset for each fragment its wave loads, relative to
-    // the first row of the operand's 128-row tile (which is < M); rows past
+    // this lane's byte offset for each DMA instruction of its wave, relative to
+    // the first row of the operand's TM-row tile (which is < M); rows past
     // M read row M-1, whose products only reach outputs that are dropped.
-    // Spare slots re-read the first A fragment.  The host keeps 128 rows
-    // below 4 GiB.
-    const int64_t a0 = m0, b0 = (int64_t)tn * T;
+    // Spare slots repeat the last instruction's loads.  The host keeps 128
+    // rows below 4 GiB.
+    const int64_t a0 = m0, b0 = (int64_t)tn * TM;
     uint32_t loff[NFW];
 #pragma unroll
     for (int q = 0; q < NFW; ++q) {
-        const int f = wave + NW * q;
-        const bool isA = f < FA || f >= NF;
-        const int rb = f >= NF ? 0 : isA ? f % RBA : (f - FA) % RBB;
-        const int64_t base = isA ? a0 : b0;
-        const int64_t r = min((isA ? m0 : n0) + rb * 16 + (lane & 15), g.M - 1);
-        loff[q] = (uint32_t)((r - base) * rowb + 16 * (lane >> 4));
+        const int piece = min(wave + NW * q, NF - 1) * 64 + lane, row = piece / NP, slot = piece % NP;
+        const int p = FAST ? slot ^ (row & 15) : (slot - ((row >> 2) & 3) + NP) % NP;
+        const bool isA = row < AR;
+        const int64_t r = min(isA ? m0 + row : n0 + row - AR, g.M - 1);
+        loff[q] = (uint32_t)((r - (isA ? a0 : b0)) * rowb + 16 * p);
     }
     auto load = [&](int64_t k0, unsigned char *dstbuf) {
-        const int64_t cb = (k0 / kI8Chunk) * CH;
+        const int64_t cb = (k0 / kI8Chunk) * PITCH;
 #pragma unroll
         for (int q = 0; q < NFW; ++q) {
             const int f = wave + NW * q;
-            const bool isA = f < FA || f >= NF;
-            const int sl = f >= NF ? 0 : isA ? f / RBA : (f - FA) / RBB;
-            const unsigned char *base = (isA ? g.A + a0 * rowb : g.B + b0 * rowb) + cb + sl * kI8Chunk;
+            const unsigned char *base = (min(f, NF - 1) < NFA ? g.A + a0 * rowb : g.B + b0 * rowb) + cb;
             __builtin_amdgcn_global_load_lds((const void *)(base + loff[q]),
                                              (__attribute__((address_space(3))) void *)(dstbuf + f * 1024), 16,
                                              0, 0);
+        }
+    };
+    // fragments of one chunk: lane l of slice s reads piece 4 s + l/16 of row l%16
+    const int fr = lane & 15, kg = lane >> 4;
+    auto frags = [&](const unsigned char *cur, i32x4 (&af)[NS][RB], i32x4 (&bf)[NS][CB]) {
+        const unsigned char *Ra = cur + wm * RB * 16 * PITCH, *Rb = cur + (AR + wn * CB * 16) * PITCH;
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) {
+            const int p = 4 * sl + kg, slot = FAST ? p ^ fr : (p + (fr >> 2)) % NP, off = fr * PITCH + slot * 16;
+#pragma unroll
+            for (int j = 0; j < CB; ++j) bf[sl][j] = *reinterpret_cast<const i32x4 *>(Rb + j * 16 * PITCH + off);
+#pragma unroll
+            for (int i = 0; i < RB; ++i) af[sl][i] = *reinterpret_cast<const i32x4 *>(Ra + i * 16 * PITCH + off);
         }
     };
 
@@ -353,127 +377,168 @@ __device__ __forceinline__ void gemm_i8_tile(I8Args g, unsigned blk)
         for (int j = 0; j < CB; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0;
+    i32x4 lev[kI8Slices][RB][CB];   // order sums t = 0..4 of the current block
+    auto products = [&](const i32x4 (&af)[NS][RB], const i32x4 (&bf)[NS][CB], bool start) {
+#pragma unroll
+        for (int si = 0; si < NS; ++si)
+#pragma unroll
+            for (int sj = 0; sj < NS; ++sj)
+#pragma unroll
+                for (int i = 0; i < RB; ++i)
+#pragma unroll
+                    for (int j = 0; j < CB; ++j) {
+                        const bool kept = FAST ? si + sj <= 3 || (si == 2 && sj == 2) : si + sj <= 4;
+                        if (!kept) continue;
+                        // the first product of each order sum in a block starts it from zero
+                        const bool first = start && si == (FAST && si + sj == 4 ? 2 : 0);
+                        const i32x4 cin = first ? i32x4{0, 0, 0, 0} : lev[si + sj][i][j];
+                        lev[si + sj][i][j] =
+                            __builtin_amdgcn_mfma_i32_16x16x64_i8(af[si][i], bf[sj][j], cin, 0, 0, 0);
+                    }
+    };
 
-    // Block scales of the 128 rows and 64 columns, staged through LDS one
-    // block ahead: thread t < 192 loads its row's (column's) scale of the
-    // next block into a register at the start of a block and writes it to
-    // ssc[next % 2] at the start of the next block, at least three barriers
-    // before the fold of that block reads it.
+    // Block scales of the operand rows, staged through LDS one block ahead:
+    // thread t < AR + BR loads its row's scale of the next block into a
+    // register during a block and writes it to ssc[next % 2] at the start of
+    // the next block, at least three barriers before the fold of that block
+    // reads it.
     __shared__ double ssc[2][AR + BR];
     const int64_t srow_t = tid < AR ? m0 + tid : n0 + (tid - AR);
     const double *sbase_t = tid < AR ? g.sA : g.sB;
     const bool sown = tid < AR + BR && srow_t < g.M;
     double snext = 0.0;
-    auto scale_fetch = [&](int64_t blk) {
-        snext = (sown && blk < nblk) ? sbase_t[srow_t * nblk + blk] : 0.0;
+    auto scale_fetch = [&](int64_t b) { snext = (sown && b < nblk) ? sbase_t[srow_t * nblk + b] : 0.0; };
+    // FP64 fold of a block: sum_t 2^{-7t} (order t sum) times the block scales.
+    // The sums of orders 1 and 2, and of 3 and 4, are joined in int32 first
+    // (|128 S_1 + S_2| < 2^30, |128 S_3 + S_4| < 2^30: five conversions and
+    // FMAs become three, same value).
+    auto fold = [&](const double *sc) {
+        double sb[CB];
+#pragma unroll
+        for (int j = 0; j < CB; ++j) sb[j] = sc[AR + (wn * CB + j) * 16 + fr] * 0x1p-14;
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            double sa[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sa[r] = sc[(wm * RB + i) * 16 + 4 * kg + r];
+#pragma unroll
+            for (int j = 0; j < CB; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int s12 = lev[1][i][j][r] * 128 + lev[2][i][j][r];
+                    const int s34 = lev[3][i][j][r] * 128 + lev[4][i][j][r];
+                    const double v = fma(fma((double)s34, 0x1p-14, (double)s12), 0x1p-14, (double)lev[0][i][j][r]);
+                    acc[i][j][r] = fma(v, sa[r] * sb[j], acc[i][j][r]);
+                }
+        }
     };
 
     // One scale block per iteration: four chunks whose five order sums live
     // only inside the iteration (the first chunk starts them from zero), then
-    // their FP64 fold.  Chunks run two ahead: a chunk's fragments are read
-    // from LDS into registers first, then (after a barrier: every wave has
-    // read that buffer) the DMA of the chunk two ahead goes into the same
-    // buffer, then the MFMAs run.  The DMA of the next chunk was issued one
-    // chunk earlier; waiting for it leaves the NFW newer loads of each wave
-    // in flight (vmcnt counts a wave's loads and they retire in order).
-    // Barriers without memory fences keep those loads outstanding across them.
+    // their FP64 fold.  Every chunk step issues one DMA (past the end: the
+    // last chunk again, never read), so each wait keeps a known number of a
+    // wave's loads in flight (they retire in order; the scale loads among
+    // them only make a wait stricter).  Barriers without memory fences keep
+    // those loads outstanding across them.
     const int64_t nch = (ke - kb) / kI8Chunk;
+    auto chunk_k = [&](int64_t ci) { return kb + min(ci, nch - 1) * kI8Chunk; };
     if (kb < ke) {
         scale_fetch(kb / kI8Block);
-        // every chunk step issues one DMA (past the end: the last chunk again,
-        // never read), so each wait below keeps exactly one chunk in flight
-        auto chunk_k = [&](int64_t ci) { return kb + min(ci, nch - 1) * kI8Chunk; };
         load(chunk_k(0), sm0);
         load(chunk_k(1), sm1);
-        __builtin_amdgcn_s_waitcnt(kWaitVmNFW);
+        if constexpr (NBUF == 3) load(chunk_k(2), sm2);
+        __builtin_amdgcn_s_waitcnt(i8_wait_vm((NBUF - 1) * NFW));
         __builtin_amdgcn_s_barrier();
-        for (int64_t k0 = kb; k0 < ke; k0 += kI8Block) {
-            const int64_t blk = k0 / kI8Block;
-            if (tid < AR + BR) ssc[blk & 1][tid] = snext;
-            scale_fetch(blk + 1);
-            i32x4 lev[kI8Slices][RB][CB];   // order sums t = 0..4
-#pragma unroll
-            for (int c = 0; c < kI8Block / kI8Chunk; ++c) {
-                const int64_t ci = (k0 - kb) / kI8Chunk + c;     // chunk index in this split (ci % 2 == c % 2)
-                unsigned char *cur = (c & 1) ? sm1 : sm0;
-                const unsigned char *Fa = cur + (wm * RB) * 1024 + lane * 16;
-                const unsigned char *Fb = cur + (FA + wn * CB) * 1024 + lane * 16;
-                i32x4 bf[NS][CB], af[NS][RB];
-#pragma unroll
-                for (int sl = 0; sl < NS; ++sl) {
-#pragma unroll
-                    for (int j = 0; j < CB; ++j)
-                        bf[sl][j] = *reinterpret_cast<const i32x4 *>(Fb + (sl * RBB + j) * 1024);
-#pragma unroll
-                    for (int i = 0; i < RB; ++i)
-                        af[sl][i] = *reinterpret_cast<const i32x4 *>(Fa + (sl * RBA + i) * 1024);
+        if constexpr (FAST) {
+            // step c: this wave's fragments of chunk c are (or are arriving) in
+            // registers and chunk c + 1 has landed once only NBUF - 2 newer
+            // chunks are outstanding; the barrier makes both true for every
+            // wave, so chunk c's buffer takes the DMA of chunk c + NBUF, the
+            // fragments of c + 1 are read and the MFMAs run on chunk c
+            i32x4 af0[NS][RB], bf0[NS][CB], af1[NS][RB], bf1[NS][CB];
+            frags(sm0, af0, bf0);
+            auto step = [&](int64_t ci, int c, unsigned char *cur, const unsigned char *nxt, i32x4 (&af)[NS][RB],
+                            i32x4 (&bf)[NS][CB], i32x4 (&afn)[NS][RB], i32x4 (&bfn)[NS][CB], int64_t blkn) {
+                __builtin_amdgcn_s_waitcnt(i8_wait_vm_lgkm0((NBUF - 2) * NFW));
+                __builtin_amdgcn_s_barrier();
+                load(chunk_k(ci + NBUF), cur);
+                if (c == 0) scale_fetch(blkn);
+                __builtin_amdgcn_sched_barrier(0);
+                frags(nxt, afn, bfn);
+                products(af, bf, c == 0);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            // a block whose first chunk lies in p0 and its next ones in p1, p2 (NBUF = 2: p0 again)
+            auto block = [&](int64_t k0, unsigned char *p0, unsigned char *p1, unsigned char *p2) {
+                const int64_t b = k0 / kI8Block, ci = (k0 - kb) / kI8Chunk;
+                if (tid < AR + BR) ssc[b & 1][tid] = snext;
+                unsigned char *p3 = NBUF == 3 ? p0 : p1;
+                step(ci, 0, p0, p1, af0, bf0, af1, bf1, b + 1);
+                step(ci + 1, 1, p1, p2, af1, bf1, af0, bf0, b + 1);
+                step(ci + 2, 2, p2, p3, af0, bf0, af1, bf1, b + 1);
+                step(ci + 3, 3, p3, NBUF == 3 ? p1 : p0, af1, bf1, af0, bf0, b + 1);
+                fold(ssc[b & 1]);
+            };
+            if constexpr (NBUF == 3) {
+                for (int64_t k0 = kb;;) {
+                    block(k0, sm0, sm1, sm2);
+                    if ((k0 += kI8Block) >= ke) break;
+                    block(k0, sm1, sm2, sm0);
+                    if ((k0 += kI8Block) >= ke) break;
+                    block(k0, sm2, sm0, sm1);
+                    if ((k0 += kI8Block) >= ke) break;
                 }
-                __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-                __builtin_amdgcn_s_barrier();
-                load(chunk_k(ci + 2), cur);
-                __builtin_amdgcn_sched_barrier(0);   // the DMA goes out before the MFMAs
-#pragma unroll
-                for (int si = 0; si < NS; ++si)
-#pragma unroll
-                    for (int sj = 0; sj < NS; ++sj)
-#pragma unroll
-                        for (int i = 0; i < RB; ++i)
-#pragma unroll
-                            for (int j = 0; j < CB; ++j) {
-                                const bool kept = FAST ? si + sj <= 3 || (si == 2 && sj == 2) : si + sj <= 4;
-                                if (!kept) continue;
-                                // the first product of each order sum in a block starts it from zero
-                                const bool first = c == 0 && si == (FAST && si + sj == 4 ? 2 : 0);
-                                const i32x4 cin = first ? i32x4{0, 0, 0, 0} : lev[si + sj][i][j];
-                                lev[si + sj][i][j] =
-                                    __builtin_amdgcn_mfma_i32_16x16x64_i8(af[si][i], bf[sj][j], cin, 0, 0, 0);
-                            }
-                __builtin_amdgcn_sched_barrier(0);   // and the wait stays after them
-                __builtin_amdgcn_s_waitcnt(kWaitVmNFW);
-                __builtin_amdgcn_s_barrier();
+            } else {
+                for (int64_t k0 = kb; k0 < ke; k0 += kI8Block) block(k0, sm0, sm1, sm0);
             }
-            // FP64 fold: sum_t 2^{-7t} (order t sum) times the block scales
-            const double *sc = ssc[blk & 1];
-            double sb[CB];
+        } else {
+            // a chunk's fragments are read from LDS into registers first, then
+            // (after a barrier: every wave has read that buffer) the DMA of the
+            // chunk two ahead goes into the same buffer, then the MFMAs run
+            for (int64_t k0 = kb; k0 < ke; k0 += kI8Block) {
+                const int64_t b = k0 / kI8Block;
+                if (tid < AR + BR) ssc[b & 1][tid] = snext;
+                scale_fetch(b + 1);
 #pragma unroll
-            for (int j = 0; j < CB; ++j) sb[j] = sc[AR + (wn * CB + j) * 16 + (lane & 15)] * 0x1p-14;
-#pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                double sa[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sa[r] = sc[(wm * RB + i) * 16 + 4 * (lane >> 4) + r];
-#pragma unroll
-                for (int j = 0; j < CB; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        double v = (double)lev[4][i][j][r];
-#pragma unroll
-                        for (int t = 3; t >= 0; --t) v = fma(v, 0x1p-7, (double)lev[t][i][j][r]);
-                        acc[i][j][r] = fma(v, sa[r] * sb[j], acc[i][j][r]);
-                    }
+                for (int c = 0; c < kI8Block / kI8Chunk; ++c) {
+                    const int64_t ci = (k0 - kb) / kI8Chunk + c;     // chunk index in this split (ci % 2 == c % 2)
+                    unsigned char *cur = (c & 1) ? sm1 : sm0;
+                    i32x4 af[NS][RB], bf[NS][CB];
+                    frags(cur, af, bf);
+                    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+                    __builtin_amdgcn_s_barrier();
+                    load(chunk_k(ci + 2), cur);
+                    __builtin_amdgcn_sched_barrier(0);   // the DMA goes out before the MFMAs
+                    products(af, bf, c == 0);
+                    __builtin_amdgcn_sched_barrier(0);   // and the wait stays after them
+                    __builtin_amdgcn_s_waitcnt(i8_wait_vm(NFW));
+                    __builtin_amdgcn_s_barrier();
+                }
+                fold(ssc[b & 1]);
             }
         }
-        __builtin_amdgcn_s_waitcnt(kWaitVm0);   // no DMA into LDS outlives the workgroup
+        __builtin_amdgcn_s_waitcnt(i8_wait_vm(0));   // no DMA into LDS outlives the workgroup
     }
-    double *dst = g.partial + ((int64_t)split * (nth / 2) + tile) * (int64_t)(T * T) + 64 * half;
+    double *dst = g.partial + ((int64_t)split * nt + tile) * (int64_t)(TM * TM) + 64 * half;
 #pragma unroll
     for (int i = 0; i < RB; ++i)
 #pragma unroll
         for (int j = 0; j < CB; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int row = (wm * RB + i) * 16 + 4 * (lane >> 4) + r;
-                const int col = (wn * CB + j) * 16 + (lane & 15);
-                dst[row * T + col] = acc[i][j][r];
+                const int row = (wm * RB + i) * 16 + 4 * kg + r;
+                const int col = (wn * CB + j) * 16 + fr;
+                dst[row * TM + col] = acc[i][j][r];
             }
 }
 
-template <int WGM, int WGN, int RB, int CB, bool FAST>
-__global__ __launch_bounds__(64 * WGM * WGN)
-__attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4)))
+constexpr int i8_threads(int TM) { return 4 * TM; }   // one wave per 32 x 32 outputs
+
+template <int TM, bool FAST>
+__global__ __launch_bounds__(i8_threads(TM)) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_i8(I8Args g)
 {
-    gemm_i8_tile<WGM, WGN, RB, CB, FAST>(g, blockIdx.x);
+    gemm_i8_tile<TM, FAST>(g, blockIdx.x);
 }
 
 // The int8 K of several molecules in one launch (batches): workgroup b runs
@@ -486,29 +551,40 @@ struct I8Group {
 };
 static_assert(sizeof(I8Group) <= 4096, "kernel arguments are limited to 4 KB");
 
-template <int WGM, int WGN, int RB, int CB, bool FAST>
-__global__ __launch_bounds__(64 * WGM * WGN)
-__attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4)))
+template <int TM, bool FAST>
+__global__ __launch_bounds__(i8_threads(TM)) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_i8_group(I8Group grp)
 {
     int m = 0;
     while (m + 1 < grp.n && blockIdx.x >= grp.blk_start[m + 1]) ++m;
-    gemm_i8_tile<WGM, WGN, RB, CB, FAST>(grp.g[m], blockIdx.x - grp.blk_start[m]);
+    gemm_i8_tile<TM, FAST>(grp.g[m], blockIdx.x - grp.blk_start[m]);
 }
 
-// Split count of the int8 K: workgroups run one per CU, all with the same
-// k length, so the time is (rounds of workgroups) x (k per split).  Counts
-// that are multiples of the XCD count run whole splits per XCD (rounds
-// counted per XCD); smaller k lengths fall back to any count.  The smallest
-// count within 2% of the best wins; at least 4 scale blocks per split.
-int i8_nsplit(int64_t nao, int64_t kdim, bool lower, int num_cus)
+// Tile of the int8_fast K: 64-wide (two workgroups per CU, less above the
+// diagonal or past nao, a third more operand traffic) up to 1,440 AO, where
+// both reach 170 TFLOP/s FP64-equivalent; 480 AO 158.8 against 141.5, 960 AO 195
+// against 164, 1,200 AO 180 against 167, but 1,920 AO 151 against 193 and 3,840
+// AO 139 against 200 (the best split count of each).
+int i8_fast_tile(int64_t nao) { return nao <= 1440 ? 64 : T; }
+
+// Split count of the int8 K.  64-wide tiles: the largest multiple of the XCD
+// count up to 64 (128 above 960 AO: short k ranges keep a split's panels in L2) of
+// at least four scale blocks each, within 5% of the fewest rounds of the chip
+// (960 AO, 16 / 24 / 32 / 64 splits: 2.42 / 2.34 / 2.19 / 2.13 ms; 1,440 AO, 32 /
+// 64 / 128: 15.3 / 13.5 / 12.2 ms).  128-wide tiles (half a tile per workgroup,
+// one per CU), all with the same k length: the time is (rounds of workgroups) x
+// (k per split); counts that are multiples of the XCD count run whole splits per
+// XCD (rounds counted per XCD), smaller k lengths fall back to any count.
+int i8_nsplit(int64_t nao, int64_t kdim, bool lower, int tile, int num_cus)
 {
-    const int ntm = (int)((nao + T - 1) / T);
-    const int64_t wg = 2 * (int64_t)(lower ? ntm * (ntm + 1) / 2 : ntm * ntm);
-    const int slots = num_cus > 0 ? num_cus : 256;
+    const int ntm = (int)((nao + tile - 1) / tile);
+    const int64_t nt = lower ? ntm * (ntm + 1) / 2 : ntm * ntm;
+    const int64_t wg = tile == T ? 2 * nt : nt;
+    const int slots = (num_cus > 0 ? num_cus : 256) * (tile == T ? 1 : 2);
     const int xslots = std::max(1, slots / kXcds);
     const int64_t nblk = kdim / kI8Block;
-    const int maxs = (int)std::max<int64_t>(1, std::min<int64_t>(64, nblk / 4));
+    const int most = tile == T || nao <= 960 ? 64 : 128;
+    const int maxs = (int)std::max<int64_t>(1, std::min<int64_t>(most, nblk / 4));
     std::vector<double> cost(maxs + 1, 1e300);
     double best = 1e300;
     for (int ns = 1; ns <= maxs; ++ns) {
@@ -517,6 +593,13 @@ int i8_nsplit(int64_t nao, int64_t kdim, bool lower, int num_cus)
                                                : (wg * ns + slots - 1) / slots;
         cost[ns] = (double)rounds * (double)per;
         best = std::min(best, cost[ns]);
+    }
+    if (tile != T) {
+        for (int ns = maxs / kXcds * kXcds; ns > 0; ns -= kXcds)
+            if (cost[ns] <= 1.05 * best) return ns;
+        for (int ns = maxs; ns > 1; --ns)
+            if (cost[ns] <= 1.05 * best) return ns;
+        return 1;
     }
     // a split count that is a multiple of the XCD count runs whole splits per
     // XCD, so the tiles of one k range share their panels in one L2 while
@@ -531,65 +614,67 @@ int i8_nsplit(int64_t nao, int64_t kdim, bool lower, int num_cus)
         for (int ns = kXcds; ns <= maxs; ns += kXcds)
             if (bx == 0 || cost[ns] < cost[bx]) bx = ns;
     if (bx > 0 && cost[bx] <= 1.15 * best) return bx;
+    // else the fewest splits within 7% of the best (int8_fast, 1,920 AO: 1 / 2 /
+    // 16 splits 34.5 / 35.6 / 38.2 ms; 3,840 AO: 3 / 5 / 8 splits 67.7 / 69.6 / 74.3 ms)
     for (int ns = 1; ns <= maxs; ++ns)
-        if (cost[ns] <= 1.02 * best) return ns;
+        if (cost[ns] <= 1.07 * best) return ns;
     return 1;
 }
 
-void launch_gemm_i8(bool lower, const void *A, const double *sA, const void *B, const double *sB, int64_t nao,
-                    int64_t kdim, int nsplit, bool fast, double *part, hipStream_t s)
+static I8Args i8_args(const void *A, const double *sA, const void *B, const double *sB, int64_t nao, int64_t kdim,
+                      bool lower, int nsplit, int tile, double *part)
 {
     I8Args g{};
     g.A = static_cast<const unsigned char *>(A);
     g.B = static_cast<const unsigned char *>(B);
     g.sA = sA; g.sB = sB;
     g.kdim = kdim; g.M = nao;
-    g.ntm = (int)((nao + T - 1) / T);
+    g.ntm = (int)((nao + tile - 1) / tile);
     g.lower = lower ? 1 : 0;
-    g.ksplit = (int64_t)align_up((size_t)(((kdim / kI8Block) + nsplit - 1) / nsplit), 1) * kI8Block;
+    g.ksplit = ((kdim / kI8Block) + nsplit - 1) / nsplit * kI8Block;
     g.partial = part;
     g.nsplit = nsplit;
-    const int ntiles = lower ? g.ntm * (g.ntm + 1) / 2 : g.ntm * g.ntm;
-    const dim3 grid(2 * ntiles * nsplit), block(64 * 2 * kI8WavesM);
-    if (fast)
-        hipLaunchKernelGGL((k_gemm_i8<kI8WavesM, 2, 8 / kI8WavesM, 2, true>), grid, block, 0, s, g);
-    else
-        hipLaunchKernelGGL((k_gemm_i8<kI8WavesM, 2, 8 / kI8WavesM, 2, false>), grid, block, 0, s, g);
+    return g;
+}
+static int64_t i8_workgroups(const I8Args &g, int tile)
+{
+    return (tile == T ? 2 : 1) * (int64_t)(g.lower ? g.ntm * (g.ntm + 1) / 2 : g.ntm * g.ntm) * g.nsplit;
+}
+
+// Split-K partial tiles (tile wide: 128, or 64 for fast) of A B^T.
+void launch_gemm_i8(bool lower, const void *A, const double *sA, const void *B, const double *sB, int64_t nao,
+                    int64_t kdim, int nsplit, bool fast, int tile, double *part, hipStream_t s)
+{
+    const I8Args g = i8_args(A, sA, B, sB, nao, kdim, lower, nsplit, tile, part);
+    const dim3 grid((unsigned)i8_workgroups(g, tile)), block(i8_threads(tile));
+    if (!fast) hipLaunchKernelGGL((k_gemm_i8<T, false>), grid, block, 0, s, g);
+    else if (tile == T) hipLaunchKernelGGL((k_gemm_i8<T, true>), grid, block, 0, s, g);
+    else hipLaunchKernelGGL((k_gemm_i8<64, true>), grid, block, 0, s, g);
 }
 
 // Lower-tile int8 K partials of several molecules (one X and its block
-// scales each, kdim[i] long, nsplit[i] splits), as launch_gemm_i8 lays them
-// out, in launches of up to kI8GroupMax molecules.
-void launch_gemm_i8_group(bool fast, int n, const void *const *X, const double *const *sX, const int64_t *nao,
-                          const int64_t *kdim, const int *nsplit, double *const *part, hipStream_t s)
+// scales each, kdim[i] long, nsplit[i] splits), all on tiles of one width, as
+// launch_gemm_i8 lays them out, in launches of up to kI8GroupMax molecules.
+void launch_gemm_i8_group(bool fast, int tile, int n, const void *const *X, const double *const *sX,
+                          const int64_t *nao, const int64_t *kdim, const int *nsplit, double *const *part,
+                          hipStream_t s)
 {
     I8Group grp{};
     int64_t total = 0;
-    const dim3 block(64 * 2 * kI8WavesM);
+    const dim3 block(i8_threads(tile));
     auto flush = [&]() {
         if (grp.n == 0) return;
         grp.blk_start[grp.n] = (uint32_t)total;
-        if (fast)
-            hipLaunchKernelGGL((k_gemm_i8_group<kI8WavesM, 2, 8 / kI8WavesM, 2, true>), dim3((unsigned)total), block,
-                               0, s, grp);
-        else
-            hipLaunchKernelGGL((k_gemm_i8_group<kI8WavesM, 2, 8 / kI8WavesM, 2, false>), dim3((unsigned)total), block,
-                               0, s, grp);
+        const dim3 grid((unsigned)total);
+        if (!fast) hipLaunchKernelGGL((k_gemm_i8_group<T, false>), grid, block, 0, s, grp);
+        else if (tile == T) hipLaunchKernelGGL((k_gemm_i8_group<T, true>), grid, block, 0, s, grp);
+        else hipLaunchKernelGGL((k_gemm_i8_group<64, true>), grid, block, 0, s, grp);
         grp = I8Group{};
         total = 0;
     };
     for (int i = 0; i < n; ++i) {
-        I8Args g{};
-        g.A = static_cast<const unsigned char *>(X[i]);
-        g.B = g.A;
-        g.sA = sX[i]; g.sB = sX[i];
-        g.kdim = kdim[i]; g.M = nao[i];
-        g.ntm = (int)((nao[i] + T - 1) / T);
-        g.lower = 1;
-        g.ksplit = (int64_t)align_up((size_t)(((kdim[i] / kI8Block) + nsplit[i] - 1) / nsplit[i]), 1) * kI8Block;
-        g.partial = part[i];
-        g.nsplit = nsplit[i];
-        const int64_t nwg = 2 * (int64_t)(g.ntm * (g.ntm + 1) / 2) * nsplit[i];
+        const I8Args g = i8_args(X[i], sX[i], X[i], sX[i], nao[i], kdim[i], true, nsplit[i], tile, part[i]);
+        const int64_t nwg = i8_workgroups(g, tile);
         if (nwg <= 0) continue;
         if (grp.n == kI8GroupMax || total + nwg > (int64_t)UINT32_MAX / 2) flush();
         grp.blk_start[grp.n] = (uint32_t)total;

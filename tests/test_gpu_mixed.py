@@ -234,3 +234,33 @@ def test_int8_open_shell(water3):
         assert (np.abs(Ks - Kf) / (2.0 ** -39 * S + 1e-13 * Kmax)).max() <= 1.0
         assert (np.abs(Ks - Kr) / (2.0 ** -33 * S + 1e-12 * Kmax)).max() <= 1.0
     assert abs(E[1] - ref["EK"]) <= 1e-6
+
+
+@pytest.mark.parametrize("n,nocc,slab", [(1, 2, 128), (3, 15, 0), (5, 25, 384), (9, 45, 0)])
+def test_int8_fast_tile_widths(n, nocc, slab):
+    """int8_fast on its 64-wide tiles (builds; nao 30 to 270: inside one tile and
+    ragged last tiles) and on its 128-wide ones (increments), from one scale
+    block per split (kdim 256) to many and a ragged last slab: the format's
+    exact evaluation and total bound, as above."""
+    mol, S, C = case(n, nocc=nocc)
+    plan = G.Plan.from_molecule(mol, schwarz_thresh=TAU, aux_slab=slab).screen().setup()
+    assert plan.build_shape(nocc, "int8_fast")["k_tile"] == 64
+    U, V = oracle.int3c(mol), oracle.int2c(mol)
+    B, _ = oracle.whitened_3c(mol, U)
+    ref = oracle.jk_from_B(B, C=C)
+    J, K, E = (t.cpu().numpy() for t in plan.build(C=C, precision="int8_fast"))
+    Xp = internal_x(mol, plan, C, U, V)
+    slab = slab or Xp.shape[0]
+    check_format("int8_fast", K, ref["K"], int8_rows(Xp, slab))
+    C1 = W.perturbed_orbitals(C, S, 1, eps=1e-2, seed=1000)
+    K0 = torch.as_tensor(ref["K"], device="cuda")
+    J, K, E = (t.cpu().numpy() for t in plan.build_delta(C1, C, K0, precision="int8_fast"))
+    r1 = oracle.jk_from_B(B, C=C1)
+    u, _, vt = np.linalg.svd(C1.T @ C)
+    Cr = C1 @ (u @ vt)               # the build rotates C1 onto C first (orthogonal polar factor)
+    Xu, Xw = (int8_rows(internal_x(mol, plan, X, U, V), slab) for X in (Cr + C, Cr - C))
+    G8 = sum(M.int8_product(a, b, keep=M.int8_fast_keep) for a, b in zip(Xu, Xw))
+    Sc = 2 * sum(M.int8_scale_envelope(a, b) for a, b in zip(Xu, Xw))
+    Kmax = np.abs(r1["K"]).max()
+    assert (np.abs(K - (ref["K"] + G8 + G8.T)) / (2.0 ** -35 * Sc + 1e-13 * Kmax)).max() <= 1.0
+    assert (np.abs(K - r1["K"]) / (2.0 ** -27 * Sc + 1e-12 * Kmax)).max() <= 1.0
