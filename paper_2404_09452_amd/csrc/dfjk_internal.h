@@ -81,6 +81,10 @@ inline size_t x_lo_bytes(int precision, int64_t rows, int64_t kdim)
     if (is_int8(precision)) return (size_t)rows * (size_t)(kdim / kI8Block) * 8;   // block scales
     return 0;
 }
+// Where the FP32 X keeps contraction element k of a row: each 16 elements
+// transposed as 4 x 4, so that a lane's 16-byte read holds the k of four
+// consecutive MFMA steps.
+constexpr int64_t f32_k_slot(int64_t k) { return (k & ~(int64_t)15) | ((k & 3) << 2) | ((k >> 2) & 3); }
 inline bool valid_precision(int precision) { return precision >= DFJK_FP64 && precision <= DFJK_MIXED_INT8_FAST; }
 
 // Boys table: F_m(T_k) at T_k = k * h, 0 <= k < kBoysNT, 0 <= m < kBoysNM.
@@ -326,9 +330,10 @@ struct BuildLayout {
     int32_t nocc_a, nocc_b;
     const double *C0, *K0;              // reference orbitals and K for the increment
     int nsplit_c;
-    int ntile;                          // syrk output tiles per side (128 wide)
+    int ntile;                          // K output tiles per side (ktile wide)
     int nsplit_k;                       // k splits per slab
-    int ktile;                          // FP64 K GEMM tile (128, or 64 written into the 128-wide partials)
+    int nsub;                           // FP32: parts of each of the nsplit_k / nsub ranges that fold on their own
+    int ktile;                          // K output tile: 64, 96 or 128
     int64_t slab, nslab;                // aux functions per slab (multiple of 128), slab count
     int64_t kdim;                       // slab * ncol: contraction length of one slab
     size_t bytes;
@@ -350,7 +355,7 @@ struct BuildLayout {
 // else 128; 64 or 128 = that tile
 BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool with_D, bool delta = false,
                          int nsplit = 0, bool allow_overlap = true, int64_t force_slab = 0, int ktile = 0);
-int batch_nsplit(const Plan *const *plans, int n);
+void batch_nsplits(const Plan *const *plans, int n, const BuildLayout *Ls, int *ns);
 void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const double *const *C, double *const *J,
                         double *const *K, double *const *E, char *const *scratch, hipStream_t s);
 BuildLayout build_layout_uks(const Plan &p, int32_t nocc_a, int32_t nocc_b, int32_t precision);
@@ -376,10 +381,13 @@ void launch_direct_build(const Plan &p, const DirectLayout &L, const double *C, 
 void launch_density(const double *C, int64_t nao, int32_t nocc, double scale, double *D, hipStream_t s);
 
 // align.hip: Cr = C Q, Q the orthogonal polar factor of C^T C0 (Procrustes)
-// FP64 K contraction by LDS DMA (syrk_f64.hip): split-K partial tiles of
-// A B^T, lower tiles or every tile, T = 64 or 128
+// FP64 and FP32 K contraction by LDS DMA (syrk_f64.hip): split-K partial tiles
+// of A B^T, lower tiles or every tile, T = 64, 96 or 128
 void launch_syrk_f64(bool lower, const double *A, const double *B, int64_t M, int64_t kdim, int64_t ksplit,
                      int nsplit, int T, double *partial, hipStream_t s);
+void launch_syrk_f32(bool lower, const float *A, const float *B, int64_t M, int64_t kdim, int64_t ksplit, int nsplit,
+                     int nsub, int T, double *partial, hipStream_t s);
+int syrk_tile_width(int64_t nao, bool f64);
 void launch_syrk_f64_group(int T, int n, const double *const *A, const int64_t *M, const int64_t *kdim,
                            const int64_t *ksplit, const int *nsplit, double *const *partial, hipStream_t s);
 void launch_gemm_nt_tri(const double *A, const double *B, double *C, int64_t M, int64_t N, int64_t ld,

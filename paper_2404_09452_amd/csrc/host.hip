@@ -1614,12 +1614,16 @@ static int batch_layouts(int32_t n, dfjk_plan *const *plans, const int32_t *nocc
         if (nocc[i] < 1 || nocc[i] > ps[i]->nao)
             return fail(DFJK_E_INVALID, "nocc[" + std::to_string(i) + "] must be in [1, nao]");
     }
-    const int ns = precision == DFJK_FP64 ? batch_nsplit(ps.data(), n) : 0;
     Ls.resize(n);
+    std::vector<int> ns(n, 0);
+    if (precision == DFJK_FP64) {
+        for (int i = 0; i < n; ++i) Ls[i] = build_layout(*ps[i], nocc[i], precision, false, false, -1, false, 0, 0);
+        batch_nsplits(ps.data(), n, Ls.data(), ns.data());
+    }
     off.resize(n);
     total = 0;
     for (int i = 0; i < n; ++i) {
-        Ls[i] = build_layout(*ps[i], nocc[i], precision, false, false, ns, false, 0, 0);   // each molecule's own tile
+        Ls[i] = build_layout(*ps[i], nocc[i], precision, false, false, ns[i], false, 0, 0);   // each molecule's own tile
         off[i] = align_up(total, 256);
         total = off[i] + Ls[i].bytes;
     }
@@ -1756,7 +1760,7 @@ static std::vector<int> autotune_candidates(const Plan &p, int32_t nocc, int32_t
 {
     std::vector<int> c;
     std::vector<int> tiles = {kTileK};
-    if (precision == DFJK_FP64) { tiles.push_back(64); tiles.push_back(96); }
+    if (precision == DFJK_FP64 || precision == DFJK_MIXED_FP32) { tiles.push_back(64); tiles.push_back(96); }
     if (precision == DFJK_MIXED_INT8_FAST) tiles.push_back(64);
     for (int kt : tiles) {
         const BuildLayout L = build_layout(p, nocc, precision, false, false, -1, true, 0, kt);   // built-in split

@@ -568,7 +568,8 @@ __device__ __forceinline__ void halftrans_tile(HTArgs g, unsigned bx, unsigned b
             if (OUT == OUT_F64) {
                 __builtin_nontemporal_store(v64, static_cast<double *>(g.X) + o);
             } else if (OUT == OUT_F32) {
-                __builtin_nontemporal_store((float)v64, static_cast<float *>(g.X) + o);
+                const int64_t k = (P - g.p_begin) * g.ncol + col;
+                static_cast<float *>(g.X)[(int64_t)mu * g.plen * g.ncol + f32_k_slot(k)] = (float)v64;
             } else {
                 const float v = (float)v64;
                 const unsigned short hi = f32_to_bf16_rne(v);
@@ -889,8 +890,10 @@ __global__ __launch_bounds__(256) void k_energies_grouped(EnergyGroup grp, doubl
 // ---------------------------------------------------------------------------
 
 // Split-K count for the K contraction: the largest count whose workgroups
-// (two per CU for these kernels) fit in one round, so no nearly empty last
-// round idles the chip; at least 256 k values per split.
+// (per_cu per CU) fit in one round, so no nearly empty last round idles the
+// chip; at least 256 k values per split, or 128 where that leaves fewer than four
+// workgroups per CU (30 AO x 640 k: 2 splits 15.8 us; a chunk of 16 k takes a lone
+// workgroup 0.6 us).
 int mixed_nsplit(int64_t nao, int64_t kdim, bool lower, int num_cus);
 int i8_fast_tile(int64_t nao);
 int i8_nsplit(int64_t nao, int64_t kdim, bool lower, int tile, int num_cus);
@@ -904,7 +907,8 @@ static int choose_ksplit(int ntiles, int64_t kdim, int num_cus, int per_cu = 2)
 {
     const int slots = per_cu * (num_cus > 0 ? num_cus : 256);
     int ns = ntiles >= slots ? 1 : slots / ntiles;
-    const int64_t maxs = kdim / 256;
+    const int64_t few = 4 * (int64_t)(num_cus > 0 ? num_cus : 256) / ntiles;
+    const int64_t maxs = std::max<int64_t>(kdim / 256, std::min<int64_t>(kdim / 128, few));
     if (ns > maxs) ns = (int)(maxs > 0 ? maxs : 1);
     if (ns < 1) ns = 1;
     return ns;
@@ -923,25 +927,19 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     L.precision = precision;
     L.with_D = with_D;
     L.nsplit_c = (int)((p.nf_pad + kCSplitRows - 1) / kCSplitRows);
-    // The FP64 syrk (C and density routes) may run on 64-wide tiles, whose
-    // partials and reduction then use that width: less of its work above the
-    // diagonal or past nao.  The autotuner's choice for the shape, or the
-    // caller's, wins; otherwise 64 when the 128-wide tiles would execute over
-    // 14% more products (the 64-wide kernel sustains about 70% of the FP64
-    // MFMA peak, the 128-wide one 80%).  Mixed precision, the increment and
-    // batches keep 128.
+    // Tile width of the K contraction: for FP64 (C and density routes) and FP32
+    // the rule of syrk_tile_width, for int8_fast that of i8_fast_tile; for FP64
+    // the autotuner's choice for the shape, or the caller's, wins.  int8, BF16x3
+    // and every increment keep 128.
     L.ktile = kTileK;
-    if (precision == DFJK_FP64 && !delta) {
-        int kt = ktile != 0 ? ktile : p.k_tile;
+    if ((precision == DFJK_FP64 || precision == DFJK_MIXED_FP32) && !delta) {
+        int kt = ktile;
+        if (kt == 0 && precision == DFJK_FP64) kt = p.k_tile;
         if (kt == 0 && nsplit == 0 && !with_D) {
             const auto it = p.tuned_ktile.find((int64_t)nocc * 8 + precision);
             if (it != p.tuned_ktile.end()) kt = it->second;
         }
-        if (kt == 0) {
-            auto executed = [&](int64_t t) { const int64_t n = (p.nao + t - 1) / t; return n * (n + 1) / 2 * t * t; };
-            if ((double)executed(kTileK) > 1.14 * (double)executed(64)) kt = 64;
-        }
-        if (kt == 64 || kt == 96) L.ktile = kt;
+        L.ktile = kt == 64 || kt == 96 || kt == kTileK ? kt : syrk_tile_width(p.nao, precision == DFJK_FP64);
     }
     if (precision == DFJK_MIXED_INT8_FAST && !delta) {
         int kt = ktile;
@@ -998,16 +996,27 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     L.j_side = allow_overlap && !p.host_B;
     L.kdim = x_kdim(precision, slab, L.ncol);
     const int ntiles = delta ? L.ntile * L.ntile : L.ntile * (L.ntile + 1) / 2;
-    // FP64 syrk: enough splits for 64 workgroups per CU with 64-wide tiles
-    // and 16 with 128-wide ones (one workgroup fills a CU's LDS; short k
-    // ranges keep a split's panels in L2).  On the 32-water cluster, 64-wide
-    // tiles x 16 / 32 / 64 / 128 splits: 10.56 / 10.06 / 9.81 / 9.61 ms per
-    // build; 128-wide x 8 / 16 / 32: 17.9 / 14.3 / 12.4 ms.  A split count of
-    // 8 or more is rounded down to a multiple of the XCD count, so that the
-    // syrk runs whole splits per XCD.
-    L.nsplit_k = precision == DFJK_FP64 ? xcd_round(choose_ksplit(ntiles, L.kdim, p.num_cus, L.ktile == 64 ? 64 : L.ktile == 96 ? 32 : 16))
-               : is_int8(precision) ? i8_nsplit(p.nao, L.kdim, !delta, L.ktile, p.num_cus)
-                                              : mixed_nsplit(p.nao, L.kdim, !delta, p.num_cus);
+    // FP64 and FP32 syrk: enough splits for 32 workgroups per CU with 64- and
+    // 96-wide tiles and 16 with 128-wide ones (FP64, 960 AO on 64-wide tiles, 64 /
+    // 136 / 272 splits: 6.14 / 6.19 / 6.23 ms; 1,920 AO on 96-wide, 16 / 32 / 72: 89.9 /
+    // 85.4 / 84.1 ms; 3,840 AO on 128-wide, 4 / 8 / 16: 179 / 168 / 168 ms).  A
+    // split count of 8 or more is rounded down to a multiple of the XCD count,
+    // so that the syrk runs whole splits per XCD.  In FP32 they are parts of the
+    // mixed_nsplit ranges in which the FP32 sums fold.
+    const int many = xcd_round(choose_ksplit(ntiles, L.kdim, p.num_cus, L.ktile == kTileK ? 16 : precision == DFJK_FP64 ? 32 : 64));
+    L.nsub = 1;
+    if (precision == DFJK_FP64) {
+        L.nsplit_k = many;
+    } else if (is_int8(precision)) {
+        L.nsplit_k = i8_nsplit(p.nao, L.kdim, !delta, L.ktile, p.num_cus);
+    } else {
+        L.nsplit_k = mixed_nsplit(p.nao, L.kdim, !delta, p.num_cus);
+        if (precision == DFJK_MIXED_FP32) {
+            const int64_t folds = (L.kdim / L.nsplit_k + 511) / 512;
+            L.nsub = (int)std::max<int64_t>(1, std::min<int64_t>((many + L.nsplit_k / 2) / L.nsplit_k, folds));
+            L.nsplit_k *= L.nsub;
+        }
+    }
     if (nsplit == 0 && !with_D && !delta) {   // a split count the autotuner measured for this shape
         const auto it = p.tuned_nsplit.find((int64_t)nocc * 8 + precision);
         if (it != p.tuned_nsplit.end()) nsplit = it->second;
@@ -1015,6 +1024,7 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     if (nsplit > 0) {   // a batch (or the autotuner) chooses the split count
         const int64_t maxs = L.kdim / 256 > 0 ? L.kdim / 256 : 1;
         L.nsplit_k = nsplit < maxs ? nsplit : (int)maxs;
+        L.nsub = 1;
     }
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -1057,8 +1067,8 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     return L;
 }
 
-void launch_gemm_mixed(int precision, bool lower, const void *A, const void *Alo, const void *B, const void *Blo,
-                       int64_t nao, int64_t kdim, int nsplit, double *part, hipStream_t s);
+void launch_gemm_bf16x3(bool lower, const void *A, const void *Alo, const void *B, const void *Blo, int64_t nao,
+                        int64_t kdim, int nsplit, double *part, hipStream_t s);
 
 // J from the resident B and the density in scratch (steps 2-4).
 static void launch_j(Plan &p, const BuildLayout &L, const double *D, double *J, char *scratch, hipStream_t s)
@@ -1116,11 +1126,16 @@ static void slab_gemm(const BuildLayout &L, bool lower, const void *X, const voi
         const int64_t ksplit = (int64_t)align_up((size_t)((kdim + L.nsplit_k - 1) / L.nsplit_k), 16);
         launch_syrk_f64(lower, static_cast<const double *>(X), static_cast<const double *>(Bop), nao, kdim, ksplit,
                         L.nsplit_k, L.ktile, part, s);
+    } else if (L.precision == DFJK_MIXED_FP32) {
+        const int ranges = L.nsplit_k / L.nsub;
+        const int64_t ksplit = (int64_t)align_up((size_t)((kdim + ranges - 1) / ranges), 32);
+        launch_syrk_f32(lower, static_cast<const float *>(X), static_cast<const float *>(Bop), nao, kdim, ksplit,
+                        L.nsplit_k, L.nsub, L.ktile, part, s);
     } else if (is_int8(L.precision)) {
         launch_gemm_i8(lower, X, static_cast<const double *>(Xlo), Bop, static_cast<const double *>(Bop_lo), nao,
                        kdim, L.nsplit_k, L.precision == DFJK_MIXED_INT8_FAST, L.ktile, part, s);
     } else {
-        launch_gemm_mixed(L.precision, lower, X, Xlo, Bop, Bop_lo, nao, kdim, L.nsplit_k, part, s);
+        launch_gemm_bf16x3(lower, X, Xlo, Bop, Bop_lo, nao, kdim, L.nsplit_k, part, s);
     }
 }
 
@@ -1386,17 +1401,25 @@ void launch_build_uks(Plan &p, const BuildLayout &L, const double *Ca, const dou
     pr.mark(ST_KREDUCE, false);
 }
 
-// Split count shared by the molecules of a batch: enough workgroups over all
-// their lower K tiles to fill one round of the chip.
-int batch_nsplit(const Plan *const *plans, int n)
+// FP64 split counts of a batch's molecules, by their own build layouts: every
+// workgroup of the grouped syrk about the same k length, so that the batch has
+// about 24 of them per CU (16 molecules of 1-12 waters: one count for all, for 2
+// workgroups per CU of 128-wide tiles, left up to 432 chunks in a row to one
+// workgroup: 1.30 ms against a floor of 0.75).
+void batch_nsplits(const Plan *const *plans, int n, const BuildLayout *Ls, int *ns)
 {
-    int tiles = 0, cus = 256;
+    double work = 0.0;
+    int cus = 256;
     for (int i = 0; i < n; ++i) {
-        const int nt = (int)((plans[i]->nao + kTileK - 1) / kTileK);
-        tiles += nt * (nt + 1) / 2;
+        const double nt = Ls[i].ntile * (Ls[i].ntile + 1) / 2;
+        work += nt * Ls[i].ktile * Ls[i].ktile / 4096.0 * (double)Ls[i].kdim;
         cus = plans[i]->num_cus;
     }
-    return choose_ksplit(tiles > 0 ? tiles : 1, (int64_t)1 << 40, cus);
+    const double per = std::max(256.0, work / (24.0 * cus));   // k of a 64-wide tile's workgroup
+    for (int i = 0; i < n; ++i) {
+        const double k = std::max(256.0, per * 4096.0 / ((double)Ls[i].ktile * Ls[i].ktile));
+        ns[i] = xcd_round((int)std::max(1.0, (double)Ls[i].kdim / k + 0.5));
+    }
 }
 
 // A batch of closed-shell builds on one stream.  Per molecule: density, J and

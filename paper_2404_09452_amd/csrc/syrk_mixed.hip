@@ -1,23 +1,22 @@
-// Mixed-precision products for K on gfx950 matrix cores:
-//   syrk mode:    P = A A^T on the lower 128x128 tiles      (direct mixed K)
-//   general mode: P = A B^T on every 128x128 tile          (incremental K)
+// Mixed-precision products for K on gfx950 matrix cores (FP32 is with FP64 in
+// syrk_f64.hip):
+//   syrk mode:    P = A A^T on the lower tiles      (direct mixed K)
+//   general mode: P = A B^T on every tile           (incremental K)
 // with split-K into FP64 partial tiles summed elsewhere in a fixed order.
 //
-//  FP32:    operands stored FP32, v_mfma_f32_16x16x4f32.
 //  BF16x3:  every operand x stored as hi + lo, both BF16 (hi = rn(x),
 //           lo = rn(x - hi)); a b ~ hi_a hi_b + hi_a lo_b + lo_a hi_b on
 //           v_mfma_f32_16x16x32_bf16 (the lo lo term, ~2^-16 relative, is
-//           dropped).
-// Products accumulate in FP32 over at most kChunk k values and are then
-// added into FP64 accumulators, so FP32 rounding does not grow with the full
-// contraction length.  The k loop is pipelined like the FP64 tile GEMM: the
-// next chunk is prefetched into registers while the current one is consumed
-// from double-buffered LDS, one barrier per chunk.
+//           dropped).  Products accumulate in FP32 over at most kChunk k
+//           values and are then added into FP64 accumulators.  The k loop is
+//           pipelined like the FP64 tile GEMM: the next chunk is prefetched
+//           into registers while the current one is consumed from
+//           double-buffered LDS, one barrier per chunk.
+//  int8:    below.
 //
-// f32-accumulating MFMA layouts (checked on the device):
-//   16x16x4 f32:   lane l supplies A[l%16][l/16], B[l/16][l%16];
-//   16x16x32 bf16: lane l supplies A[l%16][8(l/16)..+7], B[8(l/16)..+7][l%16];
-//   both: accumulator r of lane l is D[4(l/16) + r][l%16].
+// 16x16x32 bf16 layout (checked on the device): lane l supplies
+// A[l%16][8(l/16)..+7], B[8(l/16)..+7][l%16]; accumulator r of lane l is
+// D[4(l/16) + r][l%16].
 #include "dfjk_internal.h"
 
 #include <algorithm>
@@ -47,7 +46,7 @@ __device__ __forceinline__ void mixed_tile(int t, bool lower, int ntm, int &tm, 
 }
 
 struct MixedArgs {
-    const void *A, *Alo, *B, *Blo;   // [M][ld] planes (lo planes for BF16x3 only)
+    const void *A, *Alo, *B, *Blo;   // [M][ld] planes
     int64_t ld;                      // = kdim
     int64_t M;                       // rows of A and of B (nao)
     int64_t kdim, ksplit;
@@ -56,28 +55,12 @@ struct MixedArgs {
     double *partial;                 // [split][tile][T][T]
 };
 
-template <int PREC>
-struct MixStage;   // operand chunk staging per precision
-
-// FP32: chunk of KC = 32 k; A and B tiles 128 x 32 floats each.
-template <>
-struct MixStage<DFJK_MIXED_FP32> {
-    static constexpr int KC = 32, LDK = KC + 4;
-    static constexpr int SMEM = 2 * 2 * T * LDK;     // floats: [buf][A/B][T*LDK]
-};
-// BF16x3: chunk of KC = 32 k; four planes (A hi/lo, B hi/lo) of 128 x 32 bf16.
-template <>
-struct MixStage<DFJK_MIXED_BF16X3> {
-    static constexpr int KC = 32, LDK = KC + 8;
-    static constexpr int SMEM = 2 * 4 * T * LDK;     // bf16: [buf][plane][T*LDK]
-};
-
-template <int PREC>
-__global__ __launch_bounds__(256) void k_gemm_mixed(MixedArgs g)
+// Chunk of 32 k; four planes (A hi/lo, B hi/lo) of 128 x 32 bf16.
+__global__ __launch_bounds__(256) void k_gemm_bf16x3(MixedArgs g)
 {
-    constexpr int KC = MixStage<PREC>::KC, LDK = MixStage<PREC>::LDK;
-    using Elem = typename std::conditional<PREC == DFJK_MIXED_FP32, float, unsigned short>::type;
-    __shared__ __attribute__((aligned(16))) Elem sm[MixStage<PREC>::SMEM];
+    constexpr int KC = 32, LDK = KC + 8, NP = 4;
+    using Elem = unsigned short;
+    __shared__ __attribute__((aligned(16))) Elem sm[2 * NP * T * LDK];   // [buf][plane][T * LDK]
 
     int tm, tn;
     mixed_tile(blockIdx.x, g.lower, g.ntm, tm, tn);
@@ -98,16 +81,13 @@ __global__ __launch_bounds__(256) void k_gemm_mixed(MixedArgs g)
 
     // Each thread moves 16-byte pieces: row = idx / (KC*esz/16), column piece idx % (...).
     constexpr int PIECES = KC * (int)sizeof(Elem) / 16;    // 16-byte pieces per row
-    constexpr int NP = PREC == DFJK_MIXED_FP32 ? 2 : 4;   // planes
     constexpr int LOADS = T * PIECES / 256;                // pieces per thread per plane
     uint4 reg[NP][LOADS];
     const Elem *src[NP];
     src[0] = static_cast<const Elem *>(g.A);
     src[1] = static_cast<const Elem *>(g.lower ? g.A : g.B);
-    if (NP == 4) {
-        src[2] = static_cast<const Elem *>(g.Alo);
-        src[3] = static_cast<const Elem *>(g.lower ? g.Alo : g.Blo);
-    }
+    src[2] = static_cast<const Elem *>(g.Alo);
+    src[3] = static_cast<const Elem *>(g.lower ? g.Alo : g.Blo);
     auto load = [&](int64_t k0) {
 #pragma unroll
         for (int pl = 0; pl < NP; ++pl) {
@@ -142,46 +122,27 @@ __global__ __launch_bounds__(256) void k_gemm_mixed(MixedArgs g)
         for (int64_t k0 = kb; k0 < ke; k0 += KC) {
             const bool more = k0 + KC < ke;
             if (more) load(k0 + KC);
-            if constexpr (PREC == DFJK_MIXED_FP32) {
-                const float *As = reinterpret_cast<const float *>(sm) + ((buf * 2 + 0) * T) * LDK;
-                const float *Bs = reinterpret_cast<const float *>(sm) + ((buf * 2 + 1) * T) * LDK;
+            const unsigned short *P0 = reinterpret_cast<const unsigned short *>(sm) + (buf * 4) * T * LDK;
+            const unsigned short *Ah = P0, *Bh = P0 + T * LDK, *Al = P0 + 2 * T * LDK, *Bl = P0 + 3 * T * LDK;
 #pragma unroll
-                for (int ks = 0; ks < KC / 4; ++ks) {
-                    float a[4], b[4];
+            for (int ks = 0; ks < KC / 32; ++ks) {
+                bf16x8 ah[4], al[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        a[i] = As[(wm * 64 + i * 16 + (lane & 15)) * LDK + ks * 4 + (lane >> 4)];
-                        b[i] = Bs[(wn * 64 + i * 16 + (lane & 15)) * LDK + ks * 4 + (lane >> 4)];
-                    }
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            a32[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], a32[i][j], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) {
+                    const int o = (wm * 64 + i * 16 + (lane & 15)) * LDK + ks * 32 + 8 * (lane >> 4);
+                    ah[i] = *reinterpret_cast<const bf16x8 *>(&Ah[o]);
+                    al[i] = *reinterpret_cast<const bf16x8 *>(&Al[o]);
                 }
-            } else {
-                const unsigned short *P0 = reinterpret_cast<const unsigned short *>(sm) + (buf * 4) * T * LDK;
-                const unsigned short *Ah = P0, *Bh = P0 + T * LDK, *Al = P0 + 2 * T * LDK, *Bl = P0 + 3 * T * LDK;
 #pragma unroll
-                for (int ks = 0; ks < KC / 32; ++ks) {
-                    bf16x8 ah[4], al[4];
+                for (int j = 0; j < 4; ++j) {
+                    const int o = (wn * 64 + j * 16 + (lane & 15)) * LDK + ks * 32 + 8 * (lane >> 4);
+                    const bf16x8 bh = *reinterpret_cast<const bf16x8 *>(&Bh[o]);
+                    const bf16x8 bl = *reinterpret_cast<const bf16x8 *>(&Bl[o]);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int o = (wm * 64 + i * 16 + (lane & 15)) * LDK + ks * 32 + 8 * (lane >> 4);
-                        ah[i] = *reinterpret_cast<const bf16x8 *>(&Ah[o]);
-                        al[i] = *reinterpret_cast<const bf16x8 *>(&Al[o]);
-                    }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int o = (wn * 64 + j * 16 + (lane & 15)) * LDK + ks * 32 + 8 * (lane >> 4);
-                        const bf16x8 bh = *reinterpret_cast<const bf16x8 *>(&Bh[o]);
-                        const bf16x8 bl = *reinterpret_cast<const bf16x8 *>(&Bl[o]);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            a32[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh, a32[i][j], 0, 0, 0);
-                            a32[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl, a32[i][j], 0, 0, 0);
-                            a32[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh, a32[i][j], 0, 0, 0);
-                        }
+                        a32[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh, a32[i][j], 0, 0, 0);
+                        a32[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl, a32[i][j], 0, 0, 0);
+                        a32[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh, a32[i][j], 0, 0, 0);
                     }
                 }
             }
@@ -701,22 +662,18 @@ int mixed_nsplit(int64_t nao, int64_t kdim, bool lower, int num_cus)
     return mixed_splits(lower ? ntm * (ntm + 1) / 2 : ntm * ntm, kdim, num_cus);
 }
 
-void launch_gemm_mixed(int precision, bool lower, const void *A, const void *Alo, const void *B, const void *Blo,
-                       int64_t nao, int64_t kdim, int nsplit, double *part, hipStream_t s)
+void launch_gemm_bf16x3(bool lower, const void *A, const void *Alo, const void *B, const void *Blo, int64_t nao,
+                        int64_t kdim, int nsplit, double *part, hipStream_t s)
 {
     MixedArgs g{};
     g.A = A; g.Alo = Alo; g.B = B; g.Blo = Blo;
     g.ld = kdim; g.M = nao; g.kdim = kdim;
     g.ntm = (int)((nao + T - 1) / T);
     g.lower = lower ? 1 : 0;
-    const int kc = precision == DFJK_MIXED_FP32 ? MixStage<DFJK_MIXED_FP32>::KC : MixStage<DFJK_MIXED_BF16X3>::KC;
-    g.ksplit = (int64_t)align_up((size_t)((kdim + nsplit - 1) / nsplit), kc);
+    g.ksplit = (int64_t)align_up((size_t)((kdim + nsplit - 1) / nsplit), 32);
     g.partial = part;
     const int ntiles = lower ? g.ntm * (g.ntm + 1) / 2 : g.ntm * g.ntm;
-    if (precision == DFJK_MIXED_FP32)
-        hipLaunchKernelGGL(k_gemm_mixed<DFJK_MIXED_FP32>, dim3(ntiles, nsplit), dim3(256), 0, s, g);
-    else
-        hipLaunchKernelGGL(k_gemm_mixed<DFJK_MIXED_BF16X3>, dim3(ntiles, nsplit), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(k_gemm_bf16x3, dim3(ntiles, nsplit), dim3(256), 0, s, g);
 }
 
 }  // namespace dfjk

@@ -264,3 +264,23 @@ def test_int8_fast_tile_widths(n, nocc, slab):
     Kmax = np.abs(r1["K"]).max()
     assert (np.abs(K - (ref["K"] + G8 + G8.T)) / (2.0 ** -35 * Sc + 1e-13 * Kmax)).max() <= 1.0
     assert (np.abs(K - r1["K"]) / (2.0 ** -27 * Sc + 1e-12 * Kmax)).max() <= 1.0
+
+
+@pytest.mark.parametrize("n,nocc,slab,tile", [(1, 1, 128, 64), (7, 35, 256, 64), (16, 80, 0, 96), (32, 40, 0, 64)])
+def test_fp32_tile_widths(n, nocc, slab, tile):
+    """FP32 K on each of its tiles (64-wide with and without skipped edge
+    fragments, 96-wide; 128-wide in the increment) against FP64, element by
+    element: (2^-15 + 2^-23) 2 sum_k |x||x|, and 2 sum_k |x_mu||x_nu| <=
+    sqrt(K_mu,mu K_nu,nu) by Cauchy-Schwarz."""
+    mol, S, C = case(n, nocc=nocc)
+    plan = G.Plan.from_molecule(mol, schwarz_thresh=TAU, aux_slab=slab).screen().setup()
+    assert plan.build_shape(nocc, "fp32")["k_tile"] == tile
+    J0, K0, _ = plan.build(C=C)
+    J, K, _ = plan.build(C=C, precision="fp32")
+    assert torch.equal(J, J0) and torch.equal(K, K.T)
+    d = torch.sqrt(torch.diagonal(K0).clamp(min=0))
+    tol = (2.0 ** -15 + 2.0 ** -23) * torch.outer(d, d) + 1e-14 * K0.abs().max()
+    assert ((K - K0).abs() / tol).max().item() <= 1.0
+    # the increment (from K0 back to itself with C0 = -C: U = 0 after the rotation, so K0 comes back)
+    _, Kd, _ = plan.build_delta(C, -C, K0, precision="fp32")
+    assert ((Kd - K0).abs() / tol).max().item() <= 1.0
