@@ -329,7 +329,7 @@ struct BuildLayout {
     bool uks;                           // open shell: K_a, K_b from C_a, C_b (ncol = max nocc)
     int32_t nocc_a, nocc_b;
     const double *C0, *K0;              // reference orbitals and K for the increment
-    int nsplit_c;
+    int nsplit_c, crows;                // partial sums of c, rows of B in each
     int ntile;                          // K output tiles per side (ktile wide)
     int nsplit_k;                       // k splits per slab
     int nsub;                           // FP32: parts of each of the nsplit_k / nsub ranges that fold on their own
@@ -338,7 +338,7 @@ struct BuildLayout {
     int64_t kdim;                       // slab * ncol: contraction length of one slab
     size_t bytes;
     // offsets into the scratch
-    size_t o_D, o_d, o_cpart, o_c, o_X, o_Xlo, o_Bfull, o_X2, o_X2lo, o_U, o_W, o_Kpart, o_Epart, o_Da, o_Db;
+    size_t o_D, o_cpart, o_c, o_X, o_Xlo, o_Bfull, o_X2, o_X2lo, o_U, o_W, o_Kpart, o_Epart, o_Da, o_Db;
     size_t o_Cr, o_align;               // increment: C rotated onto C0, and the alignment's work
     size_t o_Cp, o_Cp2;                 // zero-padded coefficients read by the half transform (two for the increment)
     bool norms;                         // int8: add each slab's digit sums into o_norms (dfjk_build_checked)

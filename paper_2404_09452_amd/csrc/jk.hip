@@ -2,24 +2,27 @@
 // (f = stored AO function pair of a significant shell pair, P = aux function,
 // row length naux_pad):
 //   1. D = 2 C C^T                           (C route only)
-//   2. d_f = w_f D[mu_f][nu_f]               (w = 2 for a != b blocks, 1 for a == a)
-//   3. c_P = sum_f d_f B[f][P]               split over f, fixed-order sum
-//   4. J[mu_f][nu_f] = sum_P B[f][P] c_P     one wave per row f
-//   5. X[mu][P][i] = sum_nu B[f(mu,nu)][P] C[nu][i]
+//   2. c_P = sum_f d_f B[f][P], d_f = w_f D[mu_f][nu_f] (w = 2 for a != b blocks, 1
+//      for a == a)                           split over f, fixed-order sum
+//   3. J[mu_f][nu_f] = sum_P B[f][P] c_P     one wave per row f
+//   4. X[mu][P][i] = sum_nu B[f(mu,nu)][P] C[nu][i]
 //                                            gathered GEMM on FP64 MFMA, one
 //                                            workgroup per (mu, 128 aux rows)
-//   6. K = 2 X X^T (C route) or X B~^T (D route) on FP64 MFMA, lower tiles,
+//   5. K = 2 X X^T (C route) or X B~^T (D route) on FP64 MFMA, lower tiles,
 //      split-K into partial tiles summed in a fixed order
-//   7. E_J = 1/2 sum_P c_P^2 (= 1/2 Tr DJ), E_K = -1/4 sum D K
+//   6. E_J = 1/2 sum_P c_P^2 (= 1/2 Tr DJ), E_K = -1/4 sum D K
 // No floating-point atomics anywhere, so results are bitwise reproducible.
 #include "dfjk_internal.h"
 #include "gemm_f64.h"
+
+#include <algorithm>
 
 namespace dfjk {
 
 
 constexpr int kCSplitRows = 512; // f rows per partial of c
 constexpr double kAutoSlabBytes = 48e9;  // automatic aux slab: slab-sized K buffers up to this
+constexpr double kJSideBytes = 64e6;     // J beside K from this size of B on (below, the fork costs more)
 
 // ---------------------------------------------------------------------------
 __global__ void k_fill(double *p, int64_t n, double v)
@@ -32,13 +35,13 @@ static void fill(double *p, int64_t n, double v, hipStream_t s)
     hipLaunchKernelGGL(k_fill, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n, v);
 }
 
-// D = scale C C^T, one thread per element of a 16x16 output block.
-__global__ __launch_bounds__(256) void k_density(const double *__restrict__ C, int64_t nao, int32_t nocc,
-                                                 double scale, double *__restrict__ D)
+// D = scale C C^T, one thread per element of a 16x16 output block (block bx, by).
+__device__ __forceinline__ void density_block(const double *__restrict__ C, int64_t nao, int32_t nocc, double scale,
+                                              double *__restrict__ D, unsigned bx, unsigned by)
 {
     __shared__ double Ca[16][65], Cb[16][65];
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int64_t m0 = (int64_t)blockIdx.y * 16, n0 = (int64_t)blockIdx.x * 16;
+    const int64_t m0 = (int64_t)by * 16, n0 = (int64_t)bx * 16;
     double s = 0.0;
     for (int i0 = 0; i0 < nocc; i0 += 64) {
         for (int e = threadIdx.x; e < 16 * 64; e += 256) {
@@ -55,12 +58,19 @@ __global__ __launch_bounds__(256) void k_density(const double *__restrict__ C, i
     if (m0 + ty < nao && n0 + tx < nao) D[(m0 + ty) * nao + n0 + tx] = scale * s;
 }
 
+__global__ __launch_bounds__(256) void k_density(const double *__restrict__ C, int64_t nao, int32_t nocc,
+                                                 double scale, double *__restrict__ D)
+{
+    density_block(C, nao, nocc, scale, D, blockIdx.x, blockIdx.y);
+}
+
 void launch_density(const double *C, int64_t nao, int32_t nocc, double scale, double *D, hipStream_t s)
 {
     hipLaunchKernelGGL(k_density, dim3((unsigned)((nao + 15) / 16), (unsigned)((nao + 15) / 16)), dim3(256), 0, s,
                        C, nao, nocc, scale, D);
 }
 
+// D = a + b (the open-shell total density).
 __global__ void k_add(const double *__restrict__ a, const double *__restrict__ b, int64_t n,
                       double *__restrict__ out)
 {
@@ -68,59 +78,121 @@ __global__ void k_add(const double *__restrict__ a, const double *__restrict__ b
     if (i < n) out[i] = a[i] + b[i];
 }
 
-__global__ void k_gather_d(const double *__restrict__ D, int64_t nao, const int32_t *__restrict__ fmu,
-                           const int32_t *__restrict__ fnu, const double *__restrict__ fw, int64_t nf,
-                           int64_t nf_pad, double *__restrict__ d)
+// Rows of B per partial sum of c: about 128 partial sums, 16 to kCSplitRows rows
+// each (one workgroup summing 512 rows took 15.6 us of the 82 us build of one
+// water), kCSplitRows with the static scratch, which is sized for no more.
+static int c_split_rows(int64_t nf_pad, bool fixed)
 {
-    const int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (f >= nf_pad) return;
-    d[f] = (f < nf) ? fw[f] * D[(int64_t)fmu[f] * nao + fnu[f]] : 0.0;
+    if (fixed) return kCSplitRows;
+    const int64_t r = (nf_pad / 128 + 15) / 16 * 16;
+    return (int)std::min<int64_t>(std::max<int64_t>(r, 16), kCSplitRows);
 }
 
-// cpart[s][P] = sum_{f in rows of split s} d_f B[f][P]
-__global__ __launch_bounds__(256) void k_c_partial(const double *__restrict__ B, int64_t ld,
-                                                   const double *__restrict__ d, int64_t nf_pad,
-                                                   double *__restrict__ cpart)
+// Partial sums of c, block (bx, split) of 512 columns and `rows` rows of B:
+// part[split][P] = sum_f d_f B[f][P], the rows' d_f = w_f D[mu_f][nu_f] gathered into
+// LDS first.  HBM-bound: B once, 16 bytes a lane.
+constexpr int kCCols = 512;
+__device__ __forceinline__ void c_partial_block(const double *__restrict__ B, int64_t ld, const double *__restrict__ D,
+                                                int64_t nao, const int32_t *__restrict__ fmu,
+                                                const int32_t *__restrict__ fnu, const double *__restrict__ fw,
+                                                int64_t nf, int64_t nf_pad, int32_t rows, double *__restrict__ part,
+                                                unsigned bx, unsigned split)
 {
-    const int64_t P = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (P >= ld) return;
-    const int64_t f0 = (int64_t)blockIdx.y * kCSplitRows;
-    int64_t f1 = f0 + kCSplitRows;
-    if (f1 > nf_pad) f1 = nf_pad;
-    double s0 = 0.0, s1 = 0.0;
-    int64_t f = f0;
-#pragma unroll 4
-    for (; f + 1 < f1; f += 2) {
-        s0 += d[f] * B[f * ld + P];
-        s1 += d[f + 1] * B[(f + 1) * ld + P];
+    __shared__ double d[kCSplitRows];
+    const int64_t f0 = (int64_t)split * rows;
+    const int nr = (int)min((int64_t)rows, nf_pad - f0);
+    for (int r = threadIdx.x; r < nr; r += 256) {
+        const int64_t f = f0 + r;
+        d[r] = f < nf ? fw[f] * D[(int64_t)fmu[f] * nao + fnu[f]] : 0.0;
     }
-    if (f < f1) s0 += d[f] * B[f * ld + P];
-    cpart[blockIdx.y * ld + P] = s0 + s1;
+    __syncthreads();
+    const int64_t P = (int64_t)bx * kCCols + 2 * threadIdx.x;
+    if (P >= ld) return;
+    const double2 *b = reinterpret_cast<const double2 *>(B + f0 * ld + P);
+    double2 s0{0.0, 0.0}, s1{0.0, 0.0};
+    int r = 0;
+#pragma unroll 4
+    for (; r + 1 < nr; r += 2) {
+        const double2 u = b[r * (ld / 2)], v = b[(r + 1) * (ld / 2)];
+        s0.x += d[r] * u.x;
+        s0.y += d[r] * u.y;
+        s1.x += d[r + 1] * v.x;
+        s1.y += d[r + 1] * v.y;
+    }
+    if (r < nr) {
+        const double2 u = b[r * (ld / 2)];
+        s0.x += d[r] * u.x;
+        s0.y += d[r] * u.y;
+    }
+    *reinterpret_cast<double2 *>(part + (int64_t)split * ld + P) = double2{s0.x + s1.x, s0.y + s1.y};
 }
 
-__global__ void k_c_reduce(const double *__restrict__ cpart, int nsplit, int64_t ld, double *__restrict__ c)
+__global__ __launch_bounds__(256) void k_c_partial(const double *__restrict__ B, int64_t ld,
+                                                   const double *__restrict__ D, int64_t nao,
+                                                   const int32_t *__restrict__ fmu, const int32_t *__restrict__ fnu,
+                                                   const double *__restrict__ fw, int64_t nf, int64_t nf_pad,
+                                                   int32_t rows, double *__restrict__ part)
 {
-    const int64_t P = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (P >= ld) return;
+    c_partial_block(B, ld, D, nao, fmu, fnu, fw, nf, nf_pad, rows, part, blockIdx.x, blockIdx.y);
+}
+
+// c[P] = sum of part[r][P] over the rows, in a fixed order: a workgroup sums 16
+// columns, row r in lane group r mod 64, then the groups pairwise.  Workgroups
+// past the columns zero J (the pairs that screening dropped keep it).
+constexpr int kCSumCols = 16, kCSumGroups = 64, kFillBlock = 8192;
+__device__ __forceinline__ void c_sum_block(const double *__restrict__ part, int64_t rows, int64_t ld,
+                                            double *__restrict__ c, double *__restrict__ J, int64_t njj, unsigned blk)
+{
+    __shared__ double red[kCSumGroups][kCSumCols];
+    const unsigned ncol = (unsigned)(ld / kCSumCols);
+    if (blk >= ncol) {
+        const int64_t i0 = (int64_t)(blk - ncol) * kFillBlock;
+        for (int64_t i = i0 + threadIdx.x; i < min(i0 + kFillBlock, njj); i += 1024) J[i] = 0.0;
+        return;
+    }
+    const int x = threadIdx.x % kCSumCols, g = threadIdx.x / kCSumCols;
+    const int64_t P = (int64_t)blk * kCSumCols + x;
     double s = 0.0;
 #pragma unroll 8
-    for (int k = 0; k < nsplit; ++k) s += cpart[k * ld + P];
-    c[P] = s;
+    for (int64_t r = g; r < rows; r += kCSumGroups) s += part[r * ld + P];
+    red[g][x] = s;
+    __syncthreads();
+    for (int w = kCSumGroups / 2; w > 0; w >>= 1) {
+        if (g < w) red[g][x] += red[g + w][x];
+        __syncthreads();
+    }
+    if (g == 0) c[P] = red[0][x];
+}
+static unsigned c_sum_blocks(int64_t ld, int64_t njj)
+{
+    return (unsigned)(ld / kCSumCols + (njj + kFillBlock - 1) / kFillBlock);
 }
 
-// J_f = sum_P B[f][P] c_P; one wave per row.  Diagonal blocks hold both
-// orientations as separate rows, so they write only their own element.
-__global__ __launch_bounds__(256) void k_j_rows(const double *__restrict__ B, int64_t ld,
-                                                const double *__restrict__ c, const int32_t *__restrict__ fmu,
-                                                const int32_t *__restrict__ fnu, const double *__restrict__ fw,
-                                                int64_t nf, int64_t nao, int32_t accumulate, double *__restrict__ J)
+__global__ __launch_bounds__(1024) void k_c_sum(const double *__restrict__ part, int64_t rows, int64_t ld,
+                                                double *__restrict__ c, double *__restrict__ J, int64_t njj)
 {
-    const int64_t f = blockIdx.x * 4 + (threadIdx.x >> 6);
+    c_sum_block(part, rows, ld, c, J, njj, blockIdx.x);
+}
+
+// J_f = sum_P B[f][P] c_P; one wave per row (ld a multiple of 128: 16-byte loads).
+// Diagonal blocks hold both orientations as separate rows, so they write only
+// their own element.  HBM-bound: B once.
+__device__ __forceinline__ void j_row(const double *__restrict__ B, int64_t ld, const double *__restrict__ c,
+                                      const int32_t *__restrict__ fmu, const int32_t *__restrict__ fnu,
+                                      const double *__restrict__ fw, int64_t nf, int64_t nao, bool accumulate,
+                                      double *__restrict__ J, int64_t f)
+{
     const int lane = threadIdx.x & 63;
     if (f >= nf) return;
-    const double *row = B + f * ld;
+    const double2 *row = reinterpret_cast<const double2 *>(B + f * ld);
+    const double2 *cc = reinterpret_cast<const double2 *>(c);
     double s = 0.0;
-    for (int64_t P = lane; P < ld; P += 64) s += row[P] * c[P];
+#pragma unroll 4
+    for (int64_t q = lane; q < ld / 2; q += 64) {
+        const double2 b = row[q], v = cc[q];
+        s += b.x * v.x;
+        s += b.y * v.y;
+    }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
     if (lane == 0) {
@@ -131,29 +203,79 @@ __global__ __launch_bounds__(256) void k_j_rows(const double *__restrict__ B, in
     }
 }
 
+__global__ __launch_bounds__(256) void k_j_rows(const double *__restrict__ B, int64_t ld,
+                                                const double *__restrict__ c, const int32_t *__restrict__ fmu,
+                                                const int32_t *__restrict__ fnu, const double *__restrict__ fw,
+                                                int64_t nf, int64_t nao, int32_t accumulate, double *__restrict__ J)
+{
+    j_row(B, ld, c, fmu, fnu, fw, nf, nao, accumulate != 0, J, (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6));
+}
+
 // ---------------------------------------------------------------------------
-// The same steps (density, zero-padded coefficients, J) for the molecules of a
-// batch in shared launches, one per step: workgroup b of a step belongs to
-// molecule m for blk_start[m] <= b < blk_start[m + 1] and runs what block
-// b - blk_start[m] of that molecule's own launch runs, with the same
-// arithmetic per element, so J and c are bitwise those of separate builds.
+// What a build prepares before the half transform, in one launch: the density
+// (dmode 1: D = scale C C^T; 2: D copied from the caller's; 0: none) and the
+// zero-padded coefficients Cp[nao + 1][ldc] that the half transform reads (C in the
+// first ncol columns of the first nao rows).
 struct PreArgs {
-    const double *C;          // nao x nocc orbitals
-    double *D, *Cp, *J;       // density (2 C C^T), padded coefficients, J
+    const double *C;          // nao x ncol coefficients (the density on the density route)
+    double *D, *Cp, *J;       // density, padded coefficients, J
     const int32_t *f_mu, *f_nu;
     const double *f_w, *B;
-    double *dvec, *cpart, *cvec;
+    double *cpart, *cvec;
+    double scale;
     int64_t nao, nf, nf_pad, ld;
-    int32_t nocc, ldc, nsplit_c, pad_;
+    int32_t ncol, ldc, dmode, crows, nsplit_c, pad_;   // crows: rows of B per partial sum of c
 };
+constexpr int kPadBlock = 1024;   // elements of Cp (or of a copied D) per workgroup
+
+static unsigned density_blocks(const PreArgs &a)
+{
+    const int64_t g = (a.nao + 15) / 16;
+    return (unsigned)(a.dmode == 1 ? g * g : a.dmode == 2 ? (a.nao * a.nao + kPadBlock - 1) / kPadBlock : 0);
+}
+static unsigned prep_blocks(const PreArgs &a)
+{
+    return density_blocks(a) + (unsigned)(((a.nao + 1) * a.ldc + kPadBlock - 1) / kPadBlock);
+}
+
+__device__ __forceinline__ void prep_block(const PreArgs &a, unsigned local, unsigned nd)
+{
+    if (local < nd) {
+        if (a.dmode == 1) {
+            const unsigned gx = (unsigned)((a.nao + 15) / 16);
+            density_block(a.C, a.nao, a.ncol, a.scale, a.D, local % gx, local / gx);
+        } else {
+            const int64_t i0 = (int64_t)local * kPadBlock;
+            for (int64_t i = i0 + threadIdx.x; i < min(i0 + kPadBlock, a.nao * a.nao); i += 256) a.D[i] = a.C[i];
+        }
+        return;
+    }
+    const int64_t i0 = (int64_t)(local - nd) * kPadBlock, n = (a.nao + 1) * a.ldc;
+    for (int64_t i = i0 + threadIdx.x; i < min(i0 + kPadBlock, n); i += 256) {
+        const int64_t r = i / a.ldc, c = i % a.ldc;
+        a.Cp[i] = (r < a.nao && c < a.ncol) ? a.C[r * a.ncol + c] : 0.0;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_prep(PreArgs a, unsigned nd)
+{
+    prep_block(a, blockIdx.x, nd);
+}
+
+// The steps around the half transform for the molecules of a batch in shared
+// launches, one per step: workgroup b of a step belongs to molecule m for
+// blk_start[m] <= b < blk_start[m + 1] and runs what block b - blk_start[m] of that
+// molecule's own launch runs, with the same arithmetic per element, so J and c are
+// bitwise those of separate builds.
 constexpr int kPreGroupMax = 16;
 struct PreGroup {
     int32_t n;
     uint32_t blk_start[kPreGroupMax + 1];
+    uint32_t nd[kPreGroupMax];
     PreArgs a[kPreGroupMax];
 };
 static_assert(sizeof(PreGroup) <= 4096, "kernel arguments are limited to 4 KB");
-enum { PRE_DENSITY, PRE_PAD, PRE_FILL_J, PRE_GATHER, PRE_CPART, PRE_CREDUCE, PRE_JROWS, PRE_STEPS };
+enum { PRE_PREP, PRE_CPART, PRE_CSUM, PRE_JROWS };
 
 __device__ __forceinline__ int pre_member(const PreGroup &g, unsigned &local)
 {
@@ -163,143 +285,60 @@ __device__ __forceinline__ int pre_member(const PreGroup &g, unsigned &local)
     return m;
 }
 
-// Workgroups of step `st` for one molecule (its own launch's grid, flattened
-// x fastest).
-static int64_t pre_blocks(int st, const PreArgs &a)
-{
-    switch (st) {
-    case PRE_DENSITY: { const int64_t g = (a.nao + 15) / 16; return g * g; }
-    case PRE_PAD: return ((a.nao + 1) * a.ldc + 255) / 256;
-    case PRE_FILL_J: return (a.nao * a.nao + 255) / 256;
-    case PRE_GATHER: return (a.nf_pad + 255) / 256;
-    case PRE_CPART: return ((a.ld + 255) / 256) * a.nsplit_c;
-    case PRE_CREDUCE: return (a.ld + 255) / 256;
-    default: return (a.nf + 3) / 4;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_density_group(PreGroup g)
+__global__ __launch_bounds__(256) void k_prep_group(PreGroup g)
 {
     unsigned local;
-    const PreArgs &a = g.a[pre_member(g, local)];
-    const unsigned gx = (unsigned)((a.nao + 15) / 16);
-    __shared__ double Ca[16][65], Cb[16][65];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int64_t m0 = (int64_t)(local / gx) * 16, n0 = (int64_t)(local % gx) * 16;
-    const int64_t nao = a.nao;
-    const int nocc = a.nocc;
-    double s = 0.0;
-    for (int i0 = 0; i0 < nocc; i0 += 64) {
-        for (int e = threadIdx.x; e < 16 * 64; e += 256) {
-            const int r = e / 64, c = e % 64;
-            const bool ok = i0 + c < nocc;
-            Ca[r][c] = (ok && m0 + r < nao) ? a.C[(m0 + r) * nocc + i0 + c] : 0.0;
-            Cb[r][c] = (ok && n0 + r < nao) ? a.C[(n0 + r) * nocc + i0 + c] : 0.0;
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int c = 0; c < 64; ++c) s += Ca[ty][c] * Cb[tx][c];
-        __syncthreads();
-    }
-    if (m0 + ty < nao && n0 + tx < nao) a.D[(m0 + ty) * nao + n0 + tx] = 2.0 * s;
-}
-
-__global__ __launch_bounds__(256) void k_pad_fill_group(PreGroup g, int step)
-{
-    unsigned local;
-    const PreArgs &a = g.a[pre_member(g, local)];
-    const int64_t i = (int64_t)local * 256 + threadIdx.x;
-    if (step == PRE_PAD) {
-        if (i >= (a.nao + 1) * a.ldc) return;
-        const int64_t r = i / a.ldc, c = i % a.ldc;
-        a.Cp[i] = (r < a.nao && c < a.nocc) ? a.C[r * a.nocc + c] : 0.0;
-    } else if (step == PRE_FILL_J) {
-        if (i < a.nao * a.nao) a.J[i] = 0.0;
-    } else {   // PRE_GATHER
-        if (i >= a.nf_pad) return;
-        a.dvec[i] = (i < a.nf) ? a.f_w[i] * a.D[(int64_t)a.f_mu[i] * a.nao + a.f_nu[i]] : 0.0;
-    }
+    const int m = pre_member(g, local);
+    prep_block(g.a[m], local, g.nd[m]);
 }
 
 __global__ __launch_bounds__(256) void k_c_partial_group(PreGroup g)
 {
     unsigned local;
     const PreArgs &a = g.a[pre_member(g, local)];
-    const unsigned gx = (unsigned)((a.ld + 255) / 256);
-    const int64_t P = (int64_t)(local % gx) * 256 + threadIdx.x;
-    const int64_t split = local / gx, ld = a.ld;
-    if (P >= ld) return;
-    const int64_t f0 = split * kCSplitRows;
-    int64_t f1 = f0 + kCSplitRows;
-    if (f1 > a.nf_pad) f1 = a.nf_pad;
-    const double *__restrict__ d = a.dvec;
-    const double *__restrict__ B = a.B;
-    double s0 = 0.0, s1 = 0.0;
-    int64_t f = f0;
-#pragma unroll 4
-    for (; f + 1 < f1; f += 2) {
-        s0 += d[f] * B[f * ld + P];
-        s1 += d[f + 1] * B[(f + 1) * ld + P];
-    }
-    if (f < f1) s0 += d[f] * B[f * ld + P];
-    a.cpart[split * ld + P] = s0 + s1;
+    const unsigned gx = (unsigned)((a.ld + kCCols - 1) / kCCols);
+    c_partial_block(a.B, a.ld, a.D, a.nao, a.f_mu, a.f_nu, a.f_w, a.nf, a.nf_pad, a.crows, a.cpart, local % gx,
+                    local / gx);
 }
 
-__global__ __launch_bounds__(256) void k_c_reduce_group(PreGroup g)
+__global__ __launch_bounds__(1024) void k_c_sum_group(PreGroup g)
 {
     unsigned local;
     const PreArgs &a = g.a[pre_member(g, local)];
-    const int64_t P = (int64_t)local * 256 + threadIdx.x;
-    if (P >= a.ld) return;
-    double s = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < a.nsplit_c; ++k) s += a.cpart[k * a.ld + P];
-    a.cvec[P] = s;
+    c_sum_block(a.cpart, a.nsplit_c, a.ld, a.cvec, a.J, a.nao * a.nao, local);
 }
 
 __global__ __launch_bounds__(256) void k_j_rows_group(PreGroup g)
 {
     unsigned local;
     const PreArgs &a = g.a[pre_member(g, local)];
-    const int64_t f = (int64_t)local * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (f >= a.nf) return;
-    const double *row = a.B + f * a.ld;
-    double s = 0.0;
-    for (int64_t P = lane; P < a.ld; P += 64) s += row[P] * a.cvec[P];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0) {
-        const int64_t mu = a.f_mu[f], nu = a.f_nu[f];
-        a.J[mu * a.nao + nu] = s;
-        if (a.f_w[f] > 1.5) a.J[nu * a.nao + mu] = s;
-    }
+    j_row(a.B, a.ld, a.cvec, a.f_mu, a.f_nu, a.f_w, a.nf, a.nao, false, a.J, (int64_t)local * 4 + (threadIdx.x >> 6));
 }
 
-// The steps in order, each as shared launches of up to kPreGroupMax molecules.
-static void launch_pre_groups(const std::vector<PreArgs> &as, hipStream_t s)
+// One step as shared launches of up to kPreGroupMax molecules.
+static void launch_pre_group(int st, const std::vector<PreArgs> &as, hipStream_t s)
 {
-    for (int st = 0; st < PRE_STEPS; ++st) {
-        for (size_t first = 0; first < as.size(); first += kPreGroupMax) {
-            PreGroup g{};
-            int64_t total = 0;
-            for (size_t i = first; i < as.size() && g.n < kPreGroupMax; ++i) {
-                g.blk_start[g.n] = (uint32_t)total;
-                g.a[g.n++] = as[i];
-                total += pre_blocks(st, as[i]);
-            }
+    for (size_t first = 0; first < as.size(); first += kPreGroupMax) {
+        PreGroup g{};
+        int64_t total = 0;
+        for (size_t i = first; i < as.size() && g.n < kPreGroupMax; ++i) {
+            const PreArgs &a = as[i];
             g.blk_start[g.n] = (uint32_t)total;
-            if (total <= 0) continue;
-            const dim3 grid((unsigned)total), block(256);
-            switch (st) {
-            case PRE_DENSITY: hipLaunchKernelGGL(k_density_group, grid, block, 0, s, g); break;
-            case PRE_PAD:
-            case PRE_FILL_J:
-            case PRE_GATHER: hipLaunchKernelGGL(k_pad_fill_group, grid, block, 0, s, g, st); break;
-            case PRE_CPART: hipLaunchKernelGGL(k_c_partial_group, grid, block, 0, s, g); break;
-            case PRE_CREDUCE: hipLaunchKernelGGL(k_c_reduce_group, grid, block, 0, s, g); break;
-            default: hipLaunchKernelGGL(k_j_rows_group, grid, block, 0, s, g); break;
-            }
+            g.nd[g.n] = density_blocks(a);
+            g.a[g.n++] = a;
+            total += st == PRE_PREP    ? prep_blocks(a)
+                     : st == PRE_CPART ? (a.ld + kCCols - 1) / kCCols * a.nsplit_c
+                     : st == PRE_CSUM  ? c_sum_blocks(a.ld, a.nao * a.nao)
+                                       : (a.nf + 3) / 4;
+        }
+        g.blk_start[g.n] = (uint32_t)total;
+        if (total <= 0) continue;
+        const dim3 grid((unsigned)total);
+        switch (st) {
+        case PRE_PREP: hipLaunchKernelGGL(k_prep_group, grid, dim3(256), 0, s, g); break;
+        case PRE_CPART: hipLaunchKernelGGL(k_c_partial_group, grid, dim3(256), 0, s, g); break;
+        case PRE_CSUM: hipLaunchKernelGGL(k_c_sum_group, grid, dim3(1024), 0, s, g); break;
+        default: hipLaunchKernelGGL(k_j_rows_group, grid, dim3(256), 0, s, g); break;
         }
     }
 }
@@ -688,20 +727,42 @@ static void dispatch_halftrans(int precision, const HTArgs &h, int64_t nao, hipS
 }
 
 // Dense expansion for the D route: Bt[mu][P][nu] = B[f(mu,nu)][P] (0 elsewhere).
+// Workgroup (32 aux rows, mu): 64 nu at a time through LDS, so that B is read along
+// P (256 bytes a row) and Bt written along nu (512 bytes a row); the partner list is
+// sorted by nu.  Bound by the write of Bt (7 waters, 226 MB: one thread per P and a
+// strided store per nu took 270-310 us).
+constexpr int kExpP = 32, kExpN = 64;
 __global__ __launch_bounds__(256) void k_expand_B(const double *__restrict__ B, int64_t ld,
                                                   const int32_t *__restrict__ hk_off,
                                                   const int32_t *__restrict__ hk_row,
                                                   const int32_t *__restrict__ hk_nu, int64_t nao,
                                                   int64_t p_begin, int64_t plen, double *__restrict__ Bt)
 {
-    const int mu = blockIdx.y;
-    const int64_t pl = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (pl >= plen) return;
-    const int64_t P = p_begin + pl;
-    double *dst = Bt + ((int64_t)mu * plen + pl) * nao;
-    for (int64_t n = 0; n < nao; ++n) dst[n] = 0.0;
-    for (int k = hk_off[mu]; k < hk_off[mu + 1]; ++k)
-        if (hk_nu[k] < nao) dst[hk_nu[k]] = B[(int64_t)hk_row[k] * ld + P];   // padding entries name row nao
+    __shared__ double tile[kExpN][kExpP + 1];
+    const int mu = blockIdx.y, tid = threadIdx.x;
+    const int64_t pl0 = (int64_t)blockIdx.x * kExpP;   // plen is a multiple of 128
+    const int px = tid % kExpP, kx = tid / kExpP, nx = tid % kExpN, py = tid / kExpN;
+    const double *src = B + p_begin + pl0 + px;
+    double *dst = Bt + ((int64_t)mu * plen + pl0) * nao;
+    int k = hk_off[mu];
+    const int ke = hk_off[mu + 1];
+    for (int64_t n0 = 0; n0 < nao; n0 += kExpN) {
+        for (int i = kx; i < kExpN; i += 256 / kExpP) tile[i][px] = 0.0;
+        __syncthreads();
+        // entries k .. of this chunk: at most kExpN of them (each nu once; padding
+        // entries name row nao, past every chunk)
+        int used = 0;
+        for (int i = kx; i < kExpN && k + i < ke; i += 256 / kExpP) {
+            const int64_t nu = hk_nu[k + i];
+            if (nu < n0 + kExpN && nu < nao) tile[nu - n0][px] = src[(int64_t)hk_row[k + i] * ld];
+        }
+        for (int i = 0; i < kExpN && k + i < ke && hk_nu[k + i] < n0 + kExpN; ++i) ++used;
+        k += used;
+        __syncthreads();
+        if (n0 + nx < nao)
+            for (int r = py; r < kExpP; r += 256 / kExpN) dst[(int64_t)r * nao + n0 + nx] = tile[nx][r];
+        __syncthreads();
+    }
 }
 
 // [U | W] = [C + C0 | C - C0] (nao x 2 nocc): 2(C C^T - C0 C0^T) = U W^T + W U^T.
@@ -891,9 +952,10 @@ __global__ __launch_bounds__(256) void k_energies_grouped(EnergyGroup grp, doubl
 
 // Split-K count for the K contraction: the largest count whose workgroups
 // (per_cu per CU) fit in one round, so no nearly empty last round idles the
-// chip; at least 256 k values per split, or 128 where that leaves fewer than four
-// workgroups per CU (30 AO x 640 k: 2 splits 15.8 us; a chunk of 16 k takes a lone
-// workgroup 0.6 us).
+// chip; at least 256 k values per split.  short_k: 512 where that still gives eight
+// workgroups per CU (390 AO x 74,880 k, 144 / 288 splits: 0.279 / 0.282 ms, and the
+// reduction reads half the partial tiles: 39 -> 20 us), 128 where 256 leaves fewer
+// than four (30 AO x 640 k, 2 / 5 splits: 15.8 / 7.9 us).
 int mixed_nsplit(int64_t nao, int64_t kdim, bool lower, int num_cus);
 int i8_fast_tile(int64_t nao);
 int i8_nsplit(int64_t nao, int64_t kdim, bool lower, int tile, int num_cus);
@@ -903,12 +965,16 @@ void launch_gemm_i8_group(bool fast, int tile, int n, const void *const *X, cons
                           const int64_t *nao, const int64_t *kdim, const int *nsplit, double *const *part,
                           hipStream_t s);
 
-static int choose_ksplit(int ntiles, int64_t kdim, int num_cus, int per_cu = 2)
+static int choose_ksplit(int ntiles, int64_t kdim, int num_cus, int per_cu, bool short_k)
 {
     const int slots = per_cu * (num_cus > 0 ? num_cus : 256);
     int ns = ntiles >= slots ? 1 : slots / ntiles;
-    const int64_t few = 4 * (int64_t)(num_cus > 0 ? num_cus : 256) / ntiles;
-    const int64_t maxs = std::max<int64_t>(kdim / 256, std::min<int64_t>(kdim / 128, few));
+    const int64_t cus = num_cus > 0 ? num_cus : 256;
+    int64_t maxs = kdim / 256;
+    if (short_k) {
+        if (ntiles * (kdim / 512) >= 8 * cus) maxs = kdim / 512;
+        else maxs = std::max<int64_t>(maxs, std::min<int64_t>(kdim / 128, 4 * cus / ntiles));
+    }
     if (ns > maxs) ns = (int)(maxs > 0 ? maxs : 1);
     if (ns < 1) ns = 1;
     return ns;
@@ -926,13 +992,22 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     L.ncol = with_D ? p.nao : nocc;
     L.precision = precision;
     L.with_D = with_D;
-    L.nsplit_c = (int)((p.nf_pad + kCSplitRows - 1) / kCSplitRows);
+    L.crows = c_split_rows(p.nf_pad, force_slab > 0);
+    L.nsplit_c = (int)((p.nf_pad + L.crows - 1) / L.crows);
     // Tile width of the K contraction: for FP64 (C and density routes) and FP32
     // the rule of syrk_tile_width, for int8_fast that of i8_fast_tile; for FP64
     // the autotuner's choice for the shape, or the caller's, wins.  int8, BF16x3
     // and every increment keep 128.
+    // With a forced slab (the static scratch) the shapes are those of the smallest
+    // partial tiles: 64-wide FP64 tiles where 128-wide ones execute over 14% more
+    // products, else 128, and no more splits than one per 256 k.
     L.ktile = kTileK;
-    if ((precision == DFJK_FP64 || precision == DFJK_MIXED_FP32) && !delta) {
+    const bool fixed = force_slab > 0;
+    if (fixed && precision == DFJK_FP64) {
+        auto executed = [&](int64_t t) { const int64_t n = (p.nao + t - 1) / t; return n * (n + 1) / 2 * t * t; };
+        if (p.k_tile == 64 || p.k_tile == 96) L.ktile = p.k_tile;
+        else if (p.k_tile == 0 && (double)executed(kTileK) > 1.14 * (double)executed(64)) L.ktile = 64;
+    } else if ((precision == DFJK_FP64 || precision == DFJK_MIXED_FP32) && !delta && !fixed) {
         int kt = ktile;
         if (kt == 0 && precision == DFJK_FP64) kt = p.k_tile;
         if (kt == 0 && nsplit == 0 && !with_D) {
@@ -941,7 +1016,7 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
         }
         L.ktile = kt == 64 || kt == 96 || kt == kTileK ? kt : syrk_tile_width(p.nao, precision == DFJK_FP64);
     }
-    if (precision == DFJK_MIXED_INT8_FAST && !delta) {
+    if (precision == DFJK_MIXED_INT8_FAST && !delta && !fixed) {
         int kt = ktile;
         if (kt == 0 && nsplit == 0) {
             const auto it = p.tuned_ktile.find((int64_t)nocc * 8 + precision);
@@ -1003,7 +1078,9 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     // split count of 8 or more is rounded down to a multiple of the XCD count,
     // so that the syrk runs whole splits per XCD.  In FP32 they are parts of the
     // mixed_nsplit ranges in which the FP32 sums fold.
-    const int many = xcd_round(choose_ksplit(ntiles, L.kdim, p.num_cus, L.ktile == kTileK ? 16 : precision == DFJK_FP64 ? 32 : 64));
+    const int many = xcd_round(choose_ksplit(ntiles, L.kdim, p.num_cus,
+                                             L.ktile == kTileK ? 16 : precision == DFJK_FP64 && !fixed ? 32 : 64,
+                                             !fixed));
     L.nsub = 1;
     if (precision == DFJK_FP64) {
         L.nsplit_k = many;
@@ -1011,7 +1088,7 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
         L.nsplit_k = i8_nsplit(p.nao, L.kdim, !delta, L.ktile, p.num_cus);
     } else {
         L.nsplit_k = mixed_nsplit(p.nao, L.kdim, !delta, p.num_cus);
-        if (precision == DFJK_MIXED_FP32) {
+        if (precision == DFJK_MIXED_FP32 && !fixed) {
             const int64_t folds = (L.kdim / L.nsplit_k + 511) / 512;
             L.nsub = (int)std::max<int64_t>(1, std::min<int64_t>((many + L.nsplit_k / 2) / L.nsplit_k, folds));
             L.nsplit_k *= L.nsub;
@@ -1034,7 +1111,6 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
         return o;
     };
     L.o_D = take((size_t)p.nao * p.nao * 8);
-    L.o_d = take((size_t)p.nf_pad * 8);
     L.o_cpart = take((size_t)L.nsplit_c * p.naux_pad * 8);
     L.o_c = take((size_t)p.naux_pad * 8);
     const size_t nx = (size_t)p.nao * L.kdim;
@@ -1070,23 +1146,59 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
 void launch_gemm_bf16x3(bool lower, const void *A, const void *Alo, const void *B, const void *Blo, int64_t nao,
                         int64_t kdim, int nsplit, double *part, hipStream_t s);
 
-// J from the resident B and the density in scratch (steps 2-4).
+// c for plen aux functions of B (rows ld = plen apart) from the density, and J
+// zeroed first where jzero is given.
+static void launch_c(const Plan &p, const BuildLayout &L, const double *B, int64_t plen, const double *D, double *c,
+                     double *jzero, char *scratch, hipStream_t s)
+{
+    double *cpart = reinterpret_cast<double *>(scratch + L.o_cpart);
+    const int64_t njj = jzero ? p.nao * p.nao : 0;
+    hipLaunchKernelGGL(k_c_partial, dim3((unsigned)((plen + kCCols - 1) / kCCols), L.nsplit_c), dim3(256), 0, s, B,
+                       plen, D, p.nao, p.d.f_mu, p.d.f_nu, p.d.f_w, p.nf, p.nf_pad, L.crows, cpart);
+    hipLaunchKernelGGL(k_c_sum, dim3(c_sum_blocks(plen, njj)), dim3(1024), 0, s, cpart, (int64_t)L.nsplit_c, plen, c,
+                       jzero, njj);
+}
+
+static void launch_j_rows(const Plan &p, const double *B, int64_t ld, const double *c, bool accumulate, double *J,
+                          hipStream_t s)
+{
+    if (p.nf > 0)
+        hipLaunchKernelGGL(k_j_rows, dim3((unsigned)((p.nf + 3) / 4)), dim3(256), 0, s, B, ld, c, p.d.f_mu, p.d.f_nu,
+                           p.d.f_w, p.nf, p.nao, accumulate ? 1 : 0, J);
+}
+
+// J from the resident B and the density (steps 2-3).
 static void launch_j(Plan &p, const BuildLayout &L, const double *D, double *J, char *scratch, hipStream_t s)
 {
-    const int64_t nao = p.nao, ld = p.naux_pad;
-    double *dvec = reinterpret_cast<double *>(scratch + L.o_d);
-    double *cpart = reinterpret_cast<double *>(scratch + L.o_cpart);
     double *cvec = reinterpret_cast<double *>(scratch + L.o_c);
-    hipLaunchKernelGGL(k_gather_d, dim3((unsigned)((p.nf_pad + 255) / 256)), dim3(256), 0, s, D, nao, p.d.f_mu,
-                       p.d.f_nu, p.d.f_w, p.nf, p.nf_pad, dvec);
-    hipLaunchKernelGGL(k_c_partial, dim3((unsigned)((ld + 255) / 256), L.nsplit_c), dim3(256), 0, s, p.d.B, ld,
-                       dvec, p.nf_pad, cpart);
-    hipLaunchKernelGGL(k_c_reduce, dim3((unsigned)((ld + 255) / 256)), dim3(256), 0, s, cpart, L.nsplit_c, ld,
-                       cvec);
-    fill(J, nao * nao, 0.0, s);
-    if (p.nf > 0)
-        hipLaunchKernelGGL(k_j_rows, dim3((unsigned)((p.nf + 3) / 4)), dim3(256), 0, s, p.d.B, ld, cvec, p.d.f_mu,
-                           p.d.f_nu, p.d.f_w, p.nf, nao, 0, J);
+    p.prof.stream = s;
+    p.prof.mark(ST_J, true);
+    launch_c(p, L, p.d.B, p.naux_pad, D, cvec, J, scratch, s);
+    launch_j_rows(p, p.d.B, p.naux_pad, cvec, false, J, s);
+    p.prof.mark(ST_J, false);
+}
+
+// Arguments of the steps around the half transform for one molecule with ncol
+// coefficient columns (dmode, scale: the density in D, see PreArgs).
+static PreArgs pre_args(const Plan &p, const BuildLayout &L, const double *C, int64_t ncol, int dmode, double scale,
+                        double *D, double *J, char *scratch)
+{
+    PreArgs a{};
+    a.C = C; a.D = D; a.J = J;
+    a.Cp = reinterpret_cast<double *>(scratch + L.o_Cp);
+    a.f_mu = p.d.f_mu; a.f_nu = p.d.f_nu; a.f_w = p.d.f_w; a.B = p.d.B;
+    a.cpart = reinterpret_cast<double *>(scratch + L.o_cpart);
+    a.cvec = reinterpret_cast<double *>(scratch + L.o_c);
+    a.scale = scale;
+    a.nao = p.nao; a.nf = p.nf; a.nf_pad = p.nf_pad; a.ld = p.naux_pad;
+    a.ncol = (int32_t)ncol; a.ldc = (int32_t)ht_ldc(ncol); a.dmode = dmode;
+    a.crows = L.crows; a.nsplit_c = L.nsplit_c;
+    return a;
+}
+
+static void launch_prep(const PreArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_prep, dim3(prep_blocks(a)), dim3(256), 0, s, a, density_blocks(a));
 }
 
 // The zero-padded copy of the coefficients that the half transform reads
@@ -1162,8 +1274,7 @@ static bool overlap_streams(Plan &p)
     return true;
 }
 
-static void contract_slabs_overlapped(Plan &p, const BuildLayout &L, const double *C, int64_t ncol, char *scratch,
-                                      hipStream_t s)
+static void contract_slabs_overlapped(Plan &p, const BuildLayout &L, int64_t ncol, char *scratch, hipStream_t s)
 {
     const int64_t nao = p.nao, ld = p.naux_pad;
     Profiler &pr = p.prof;
@@ -1173,7 +1284,7 @@ static void contract_slabs_overlapped(Plan &p, const BuildLayout &L, const doubl
     const int ntiles = L.ntile * (L.ntile + 1) / 2;
     const size_t slab_part = (size_t)L.nsplit_k * ntiles * L.ktile * L.ktile;
     hipStream_t hs = p.ht_stream;
-    const double *Cp = pad_coef(p, C, (int32_t)ncol, scratch, L.o_Cp, s);
+    const double *Cp = reinterpret_cast<const double *>(scratch + L.o_Cp);
     (void)hipEventRecord(p.ev_fork, s);
     (void)hipStreamWaitEvent(hs, p.ev_fork, 0);
     auto ht = [&](int64_t sl) {
@@ -1201,11 +1312,13 @@ static void contract_slabs_overlapped(Plan &p, const BuildLayout &L, const doubl
     }
 }
 
+// The coefficients are in the scratch, zero-padded (k_prep; the increment's two
+// here).
 static void contract_slabs(Plan &p, const BuildLayout &L, const double *C1, const double *C2, int64_t ncol,
                            char *scratch, hipStream_t s)
 {
     if (L.overlap && C2 == nullptr && overlap_streams(p)) {
-        contract_slabs_overlapped(p, L, C1, ncol, scratch, s);
+        contract_slabs_overlapped(p, L, ncol, scratch, s);
         return;
     }
     const int64_t nao = p.nao, ld = p.naux_pad;
@@ -1219,7 +1332,8 @@ static void contract_slabs(Plan &p, const BuildLayout &L, const double *C1, cons
     const size_t slab_part = (size_t)L.nsplit_k * ntiles * L.ktile * L.ktile;
     void *X2 = L.delta ? scratch + L.o_X2 : nullptr;
     void *X2lo = L.o_X2lo ? scratch + L.o_X2lo : nullptr;
-    const double *Cp1 = pad_coef(p, C1, (int32_t)ncol, scratch, L.o_Cp, s);
+    const double *Cp1 = L.delta ? pad_coef(p, C1, (int32_t)ncol, scratch, L.o_Cp, s)
+                                : reinterpret_cast<const double *>(scratch + L.o_Cp);
     const double *Cp2 = L.delta ? pad_coef(p, C2, (int32_t)ncol, scratch, L.o_Cp2, s) : nullptr;
     for (int64_t sl = 0; sl < L.nslab; ++sl) {
         const int64_t pb = sl * L.slab, plen = (ld - pb < L.slab) ? ld - pb : L.slab;
@@ -1232,7 +1346,7 @@ static void contract_slabs(Plan &p, const BuildLayout &L, const double *C1, cons
         if (L.delta)
             launch_ht(p, L.precision, p.d.B, ld, Cp2, (int32_t)ncol, pb, plen, X2, X2lo, s);
         else if (L.with_D)
-            hipLaunchKernelGGL(k_expand_B, dim3((unsigned)((plen + 255) / 256), (unsigned)nao), dim3(256), 0, s,
+            hipLaunchKernelGGL(k_expand_B, dim3((unsigned)(plen / kExpP), (unsigned)nao), dim3(256), 0, s,
                                p.d.B, ld, p.d.hk_off, p.d.hk_row, p.d.hk_nu, nao, pb, plen, Bt);
         pr.mark(ST_HALFTRANS, false);
         pr.mark(ST_K, true);
@@ -1276,48 +1390,44 @@ void launch_build(Plan &p, const BuildLayout &L, const double *C, const double *
     pr.stream = s;
     pr.mark(ST_BUILD, true);
 
-    // 1. density
-    pr.mark(ST_DENSITY, true);
-    if (!L.with_D) {
-        dim3 grid((unsigned)((nao + 15) / 16), (unsigned)((nao + 15) / 16));
-        hipLaunchKernelGGL(k_density, grid, dim3(256), 0, s, C, nao, (int32_t)L.ncol, 2.0, D);
-    } else {
-        (void)hipMemcpyAsync(D, Din, (size_t)nao * nao * 8, hipMemcpyDeviceToDevice, s);
-    }
-    if (L.delta) {   // U, W from C rotated onto C0 (D is unchanged by the rotation)
-        double *Cr = reinterpret_cast<double *>(scratch + L.o_Cr);
-        launch_align(C, L.C0, nao, (int32_t)L.ncol, reinterpret_cast<double *>(scratch + L.o_align), Cr, s);
-        hipLaunchKernelGGL(k_uw, dim3((unsigned)((nao * L.ncol + 255) / 256)), dim3(256), 0, s, Cr, L.C0, nao,
-                           (int32_t)L.ncol, reinterpret_cast<double *>(scratch + L.o_U),
-                           reinterpret_cast<double *>(scratch + L.o_W));
-    }
-    pr.mark(ST_DENSITY, false);
-    // 2-4. J (always FP64).  J streams B through HBM (bound there) while the
-    // half transform and K are bound by the FP64 MFMA pipes, so J runs on a
-    // side stream beside them and is joined before the energies: it reads
-    // D and B and writes only J and its own scratch (d, c partials, c).
-    const bool jside = L.j_side && side_stream(p);
+    // J streams B through HBM twice while the half transform and K are bound by the
+    // matrix pipes: with a B of kJSideBytes or more the density and J run on a side
+    // stream from the start, joined before the energies.  Beside the half
+    // transform, J costs 32 waters 0.3 ms (2.15 -> 2.47 ms); beside K it cost 0.7 (6.6 ->
+    // 7.35 ms), more than the 0.5 that it takes alone.  J reads D and B and writes
+    // only J and its own scratch.
+    const bool jside = L.j_side && (double)p.nf_pad * p.naux_pad * 8.0 >= kJSideBytes && side_stream(p);
     hipStream_t js = jside ? p.j_stream : s;
+    pr.mark(ST_DENSITY, true);
     if (jside) {
         (void)hipEventRecord(p.ev_jfork, s);
         (void)hipStreamWaitEvent(js, p.ev_jfork, 0);
-        pr.stream = js;
     }
-    pr.mark(ST_J, true);
+    const int dmode = L.with_D ? 2 : L.delta || jside ? 0 : 1;   // the density where k_prep does not form it
+    if (!L.with_D && dmode == 0) launch_density(C, nao, (int32_t)L.ncol, 2.0, D, js);
+    const double *C1 = nullptr, *C2 = nullptr;
+    if (L.delta) {   // U, W from C rotated onto C0 (D is unchanged by the rotation)
+        double *Cr = reinterpret_cast<double *>(scratch + L.o_Cr);
+        double *U = reinterpret_cast<double *>(scratch + L.o_U), *W = reinterpret_cast<double *>(scratch + L.o_W);
+        launch_align(C, L.C0, nao, (int32_t)L.ncol, reinterpret_cast<double *>(scratch + L.o_align), Cr, s);
+        hipLaunchKernelGGL(k_uw, dim3((unsigned)((nao * L.ncol + 255) / 256)), dim3(256), 0, s, Cr, L.C0, nao,
+                           (int32_t)L.ncol, U, W);
+        C1 = U;
+        C2 = W;
+    } else {
+        launch_prep(pre_args(p, L, L.with_D ? Din : C, L.ncol, dmode, 2.0, D, J, scratch), s);
+        if (jside && L.with_D) {   // D is copied by then
+            (void)hipEventRecord(p.ev_jfork, s);
+            (void)hipStreamWaitEvent(js, p.ev_jfork, 0);
+        }
+    }
+    pr.mark(ST_DENSITY, false);
     launch_j(p, L, D, J, scratch, js);
-    pr.mark(ST_J, false);
-    if (jside) {
-        (void)hipEventRecord(p.ev_jdone, js);
-        pr.stream = s;
-    }
-    // 5-6. per aux slab: half transform(s) and the slab's K contribution
-    if (!L.delta)
-        contract_slabs(p, L, L.with_D ? Din : C, nullptr, L.ncol, scratch, s);
-    else
-        contract_slabs(p, L, reinterpret_cast<double *>(scratch + L.o_U),
-                       reinterpret_cast<double *>(scratch + L.o_W), L.ncol, scratch, s);
-    // 7. split-K sum, mirror, energies (after J: the energies read c)
+    pr.stream = s;
+    if (jside) (void)hipEventRecord(p.ev_jdone, js);
+    contract_slabs(p, L, C1, C2, L.ncol, scratch, s);
     if (jside) (void)hipStreamWaitEvent(s, p.ev_jdone, 0);
+    // split-K sum, mirror, energies (after the side stream: they read D and c)
     pr.mark(ST_KREDUCE, true);
     const int nlower = L.ntile * (L.ntile + 1) / 2;
     const int64_t nep = (int64_t)nlower * (L.delta ? kTileK / 16 : reduce_chunks(L.ktile));   // energy partials
@@ -1374,28 +1484,36 @@ void launch_build_uks(Plan &p, const BuildLayout &L, const double *Ca, const dou
     pr.stream = s;
 
     pr.mark(ST_DENSITY, true);
-    const dim3 grid((unsigned)((nao + 15) / 16), (unsigned)((nao + 15) / 16));
     for (int sp = 0; sp < 2; ++sp) {
-        if (nocc[sp] > 0) hipLaunchKernelGGL(k_density, grid, dim3(256), 0, s, Cs[sp], nao, nocc[sp], 1.0, Ds[sp]);
+        if (nocc[sp] > 0) launch_density(Cs[sp], nao, nocc[sp], 1.0, Ds[sp], s);
         else fill(Ds[sp], nao * nao, 0.0, s);
     }
     hipLaunchKernelGGL(k_add, dim3((unsigned)((nao * nao + 255) / 256)), dim3(256), 0, s, Ds[0], Ds[1], nao * nao, D);
     pr.mark(ST_DENSITY, false);
-    pr.mark(ST_J, true);
-    launch_j(p, L, D, J, scratch, s);
-    pr.mark(ST_J, false);
+    // J on the side stream where B is large (as in launch_build)
+    const bool jside = L.j_side && (double)p.nf_pad * ld * 8.0 >= kJSideBytes && side_stream(p);
+    hipStream_t js = jside ? p.j_stream : s;
+    if (jside) {
+        (void)hipEventRecord(p.ev_jfork, s);
+        (void)hipStreamWaitEvent(js, p.ev_jfork, 0);
+    }
+    launch_j(p, L, D, J, scratch, js);
+    pr.stream = s;
+    if (jside) (void)hipEventRecord(p.ev_jdone, js);
     for (int sp = 0; sp < 2; ++sp) {
         if (nocc[sp] == 0) {
             fill(Ks[sp], nao * nao, 0.0, s);
             fill(Epart + sp * nep, nep, 0.0, s);
             continue;
         }
-        contract_slabs(p, L, Cs[sp], nullptr, nocc[sp], scratch, s);
+        launch_prep(pre_args(p, L, Cs[sp], nocc[sp], 0, 1.0, Ds[sp], J, scratch), s);
+        contract_slabs(p, L, nullptr, nullptr, nocc[sp], scratch, s);
         pr.mark(ST_KREDUCE, true);
         hipLaunchKernelGGL(k_k_reduce, dim3(nlower, reduce_chunks(L.ktile)), dim3(256), 0, s, Kpart,
                            (int)(L.nslab * L.nsplit_k), L.ntile, L.ktile, nao, 1.0, Ds[sp], Ks[sp], Epart + sp * nep);
         pr.mark(ST_KREDUCE, false);
     }
+    if (jside) (void)hipStreamWaitEvent(s, p.ev_jdone, 0);
     pr.mark(ST_KREDUCE, true);
     hipLaunchKernelGGL(k_energies, dim3(1), dim3(256), 0, s, cvec, ld, Epart, 2 * nep, -0.5, E);
     pr.mark(ST_KREDUCE, false);
@@ -1449,17 +1567,9 @@ void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const 
         const int64_t nao = p.nao;
         double *D = reinterpret_cast<double *>(sc + L.o_D);
         if (L.nslab == 1 && (L.precision == DFJK_FP64 || is_int8(L.precision))) {
-            // density, padded coefficients and J in the shared launches of
-            // launch_pre_groups, the half transform and K grouped after them
-            PreArgs a{};
-            a.C = C[i]; a.D = D; a.J = J[i];
-            a.Cp = reinterpret_cast<double *>(sc + L.o_Cp);
-            a.f_mu = p.d.f_mu; a.f_nu = p.d.f_nu; a.f_w = p.d.f_w; a.B = p.d.B;
-            a.dvec = reinterpret_cast<double *>(sc + L.o_d);
-            a.cpart = reinterpret_cast<double *>(sc + L.o_cpart);
-            a.cvec = reinterpret_cast<double *>(sc + L.o_c);
-            a.nao = nao; a.nf = p.nf; a.nf_pad = p.nf_pad; a.ld = p.naux_pad;
-            a.nocc = (int32_t)L.ncol; a.ldc = (int32_t)ht_ldc(L.ncol); a.nsplit_c = L.nsplit_c;
+            // density, padded coefficients, c and J in shared launches, the half
+            // transforms and K grouped between them
+            const PreArgs a = pre_args(p, L, C[i], L.ncol, 1, 2.0, D, J[i], sc);
             pre.push_back(a);
             if (is_int8(L.precision)) {
                 void *Xlo = sc + L.o_Xlo;   // block scales
@@ -1490,8 +1600,7 @@ void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const 
         }
         p.prof.stream = s;
         p.prof.mark(ST_DENSITY, true);
-        hipLaunchKernelGGL(k_density, dim3((unsigned)((nao + 15) / 16), (unsigned)((nao + 15) / 16)), dim3(256), 0,
-                           s, C[i], nao, (int32_t)L.ncol, 2.0, D);
+        launch_prep(pre_args(p, L, C[i], L.ncol, 1, 2.0, D, J[i], sc), s);
         p.prof.mark(ST_DENSITY, false);
         // J on the plan's side stream beside the other molecules' work,
         // joined before the energies (the only later step that reads c)
@@ -1502,18 +1611,18 @@ void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const 
             js = p.j_stream;
             joins.push_back(&p);
         }
-        p.prof.stream = js;
-        p.prof.mark(ST_J, true);
         launch_j(p, L, D, J[i], sc, js);
-        p.prof.mark(ST_J, false);
         p.prof.stream = s;
         if (js != s) (void)hipEventRecord(p.ev_jdone, js);
-        contract_slabs(p, L, C[i], nullptr, L.ncol, sc, s);
+        contract_slabs(p, L, nullptr, nullptr, L.ncol, sc, s);
     }
-    launch_pre_groups(pre, s);
+    launch_pre_group(PRE_PREP, pre, s);
     // the half transforms of the one-slab molecules, grouped by output and fragment count
     launch_halftrans_groups<OUT_F64>(hts, s);
     launch_halftrans_groups<OUT_I8>(hts8, s);
+    launch_pre_group(PRE_CPART, pre, s);
+    launch_pre_group(PRE_CSUM, pre, s);
+    launch_pre_group(PRE_JROWS, pre, s);
     for (int T : {64, 128}) {   // one grouped int8 K per tile width
         std::vector<const void *> gx;
         std::vector<const double *> gs;
@@ -1592,8 +1701,6 @@ void launch_build_hostB(Plan &p, const BuildLayout &L, const double *C, double *
 {
     const int64_t nao = p.nao, ld = p.naux_pad;
     double *D = reinterpret_cast<double *>(scratch + L.o_D);
-    double *dvec = reinterpret_cast<double *>(scratch + L.o_d);
-    double *cpart = reinterpret_cast<double *>(scratch + L.o_cpart);
     double *cvec = reinterpret_cast<double *>(scratch + L.o_c);
     double *Kpart = reinterpret_cast<double *>(scratch + L.o_Kpart);
     double *Epart = reinterpret_cast<double *>(scratch + L.o_Epart);
@@ -1622,32 +1729,23 @@ void launch_build_hostB(Plan &p, const BuildLayout &L, const double *C, double *
     if (L.nslab > 1) copy_slab(1);
 
     pr.mark(ST_DENSITY, true);
-    hipLaunchKernelGGL(k_density, dim3((unsigned)((nao + 15) / 16), (unsigned)((nao + 15) / 16)), dim3(256), 0, s, C,
-                       nao, (int32_t)L.ncol, 2.0, D);
+    launch_prep(pre_args(p, L, C, L.ncol, 1, 2.0, D, J, scratch), s);
     pr.mark(ST_DENSITY, false);
-    hipLaunchKernelGGL(k_gather_d, dim3((unsigned)((p.nf_pad + 255) / 256)), dim3(256), 0, s, D, nao, p.d.f_mu,
-                       p.d.f_nu, p.d.f_w, p.nf, p.nf_pad, dvec);
-    fill(J, nao * nao, 0.0, s);
-    const double *Cp = pad_coef(p, C, (int32_t)L.ncol, scratch, L.o_Cp, s);
+    const double *Cp = reinterpret_cast<const double *>(scratch + L.o_Cp);
     for (int64_t sl = 0; sl < L.nslab; ++sl) {
         const int b = (int)(sl & 1);
         const int64_t pb = sl * L.slab, plen = (ld - pb < L.slab) ? ld - pb : L.slab;
         (void)hipStreamWaitEvent(s, p.ev_ready[b], 0);
-        pr.mark(ST_J, true);
-        hipLaunchKernelGGL(k_c_partial, dim3((unsigned)((plen + 255) / 256), L.nsplit_c), dim3(256), 0, s, stage[b],
-                           plen, dvec, p.nf_pad, cpart);
-        hipLaunchKernelGGL(k_c_reduce, dim3((unsigned)((plen + 255) / 256)), dim3(256), 0, s, cpart, L.nsplit_c,
-                           plen, cvec + pb);
-        if (p.nf > 0)
-            hipLaunchKernelGGL(k_j_rows, dim3((unsigned)((p.nf + 3) / 4)), dim3(256), 0, s, stage[b], plen, cvec + pb,
-                               p.d.f_mu, p.d.f_nu, p.d.f_w, p.nf, nao, 1, J);
-        pr.mark(ST_J, false);
         pr.mark(ST_HALFTRANS, true);
         launch_ht(p, L.precision, stage[b], plen, Cp, (int32_t)L.ncol, 0, plen, X, Xlo, s);
         if (L.norms)
             launch_i8_norms(X, static_cast<const double *>(Xlo), nao, x_kdim(L.precision, plen, L.ncol),
                             reinterpret_cast<double *>(scratch + L.o_norms), s);
         pr.mark(ST_HALFTRANS, false);
+        pr.mark(ST_J, true);
+        launch_c(p, L, stage[b], plen, D, cvec + pb, pb == 0 ? J : nullptr, scratch, s);
+        launch_j_rows(p, stage[b], plen, cvec + pb, true, J, s);
+        pr.mark(ST_J, false);
         (void)hipEventRecord(p.ev_free[b], s);      // the staging buffer is read
         if (sl + 2 < L.nslab) copy_slab(sl + 2);
         pr.mark(ST_K, true);
