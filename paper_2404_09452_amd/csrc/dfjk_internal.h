@@ -372,7 +372,7 @@ void launch_build_hostB(Plan &p, const BuildLayout &L, const double *C, double *
 // density-weighted screen and adds the reference J0, K0.
 struct DirectLayout {
     bool with_D, delta;
-    size_t o_D, o_dsh, o_Dh, o_Jh, o_Epart, bytes;
+    size_t o_D, o_dsh, o_Dh, o_Dhv, o_Jh, o_Epart, bytes;
 };
 DirectLayout direct_layout(const Plan &p, bool with_D, bool delta = false);
 void launch_direct_build(const Plan &p, const DirectLayout &L, const double *C, int32_t nocc, const double *D,

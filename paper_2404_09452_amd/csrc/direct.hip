@@ -9,31 +9,36 @@
 //   (ab|cd) = pref sum_h E^{ab}_f[h] sum_k (-1)^{|k|} E^{cd}_g[k] R_{h+k}(alpha, P - Q),
 //   pref = 2 pi^{5/2} / (p q sqrt(p+q)),  alpha = p q / (p+q).
 //
-// J.  With the ket density in Hermite form, Dh_cd[k] = w (-1)^{|k|} sum_g E^{cd}_g[k] D_g
-// (w = 2 for c != d: both orders of the pair), every quartet adds
-// pref sum_k R_{h+k} Dh_cd[k] to a Hermite J vector Jh_ab[h] of the bra pair,
-// which a thread keeps in registers over its ket loop; J_f = sum_h E^{ab}_f[h] Jh_ab[h].
+// Work split.  Every unordered combination of two pairs is visited once.  A
+// workgroup holds one pair u = (a, b) of the class of higher angular momentum, the
+// same for all its lanes (its tables are scalar loads), and its lanes walk the
+// pairs v = (c, d) of the other class (both sorted by descending Schwarz factor,
+// so a wave stops at the first step whose leading v fails Q_u Q_v >= threshold, and
+// lanes whose own bound fails sit out).  With u and v of one class, v <= u.
 //
-// K.  K_{mu nu} = sum (mu la|nu si) D_{la si}.  A visit of bra pair {a,b}
-// and ket pair {c,d} forms the integral block and adds its contractions
-// to the blocks K_ac (with D_bd), K_ad (D_bc), K_bc (D_ad) and K_bd (D_ac),
-// leaving out the duplicates of a = b or c = d.  Every ordered (bra, ket)
-// combination of pairs is visited, so the block K_xy (x in {a,b}, y in
-// {c,d}) of shells x > y also arrives, transposed, from the visit with bra
-// and ket swapped: only blocks with shell x >= y are written (FP64 atomics)
-// and the upper triangle is mirrored at the end.
+// J.  With the densities in Hermite form, Dh_v[h] = w sum_f E_f[h] D_f and, signed,
+// Dh_u[k] = w (-1)^{|k|} sum_g E_g[k] D_g (w = 2 for two different shells: both orders
+// of the pair), a quartet adds pref sum_h R_{h+k} Dh_v[h] to the Hermite J vector of u,
+// which a lane keeps in registers over its walk, and pref sum_k R_{h+k} Dh_u[k] to
+// that of v, which goes out with FP64 atomics (adjacent lanes, adjacent addresses);
+// J_f = sum_h E_f[h] Jh[h].
 //
-// Mapping.  One wave of 64 lanes per launch block.  Light quartet classes:
-// lane = bra pair of one class, pairs sorted by descending Schwarz factor,
-// and the ket loop (pairs of one class, also sorted) is the same for every
-// lane, so its data are uniform loads.  Heavy classes (la+lb+lc+ld >= 5, or
-// la = 2 with few pairs: much work per quartet): a wave takes 8 bra pairs x 8 ket pairs
-// per step and blockIdx.z takes one row of the first bra shell.  The ket
-// loop stops for the whole wave at the first step whose leading ket pair
-// has Q_cd * Q_max(wave) below the threshold; lanes whose own bound fails
-// sit out that step.  blockIdx.y splits the ket range into short pieces so
-// that a launch has many waves; the Hermite J vectors of the splits are
-// summed with FP64 atomics.
+// K.  K_{mu nu} = sum (mu la|nu si) D_{la si}.  The integrals (ab|cd) give the blocks
+// K_ac (with D_bd), K_ad (D_bc), K_bc (D_ad) and K_bd (D_ac), leaving out the
+// duplicates of a = b or c = d.  All of them lie in the rows of a and b, which are the
+// workgroup's own: they are summed in LDS over the whole walk and added to memory
+// once, row by row.  The transposed blocks are the same numbers: the sum F over
+// the visits (half of it for u = v) gives K = F + F^T at the end.  The densities come
+// from the same rows of D, staged beside them: gathers from memory touch 64 cache
+// lines per load, and the heavy launch spent its time there (32 waters: 4.08 ms, 62
+// million vector loads; from LDS 2.79 ms, 21 million).
+//
+// What bounds it: the latency of FP64 chains (Boys function, Hermite recursion) and of
+// the table loads at 1 to 3 waves per SIMD; the instructions issued would fill 1.2 ms of
+// the 3.6 ms that the three launches take on 32 waters at threshold 1e-10.  Before, every
+// ordered combination was visited, in 36 launches, and every quartet added its K blocks
+// to memory with scattered FP64 atomics (16 of 31 ms).  Now against then: 3.8 ms
+// against 30, and 0.51 ms against 3.0 for an incremental build of 8 waters.
 #include "dfjk_internal.h"
 #include "hermite.h"
 
@@ -49,22 +54,22 @@ DirectLayout direct_layout(const Plan &p, bool with_D, bool delta)
     L.o_D = (with_D && !delta) ? 0 : take((size_t)p.nao * p.nao * 8);   // D from C, or D - D0
     L.o_dsh = delta ? take(((size_t)p.nsh_ao * p.nsh_ao + 1) * 8) : 0;   // block maxima, then the overall max
     L.o_Dh = take((size_t)std::max<int64_t>(p.dir.herm_total, 1) * 8);
+    L.o_Dhv = take((size_t)std::max<int64_t>(p.dir.herm_total, 1) * 8);
     L.o_Jh = take((size_t)std::max<int64_t>(p.dir.herm_total, 1) * 8);
     L.o_Epart = take((size_t)2 * 256 * 8);
     L.bytes = align_up(off, 256);
     return L;
 }
 
-__global__ void k_dfill(double *p, int64_t n, double v)
+// Zeros J, K and the Hermite J vectors.
+__global__ __launch_bounds__(256) void k_direct_zero(double *J, double *K, int64_t n, double *Jh, int64_t nh)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
-static void dfill(double *p, int64_t n, hipStream_t s)
-{
-    const int64_t nb = std::min<int64_t>((n + 255) / 256, 4096);
-    if (n > 0) hipLaunchKernelGGL(k_dfill, dim3((unsigned)std::max<int64_t>(nb, 1)), dim3(256), 0, s, p, n, 0.0);
+    const int64_t step = (int64_t)gridDim.x * 256;
+    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < 2 * n + nh; i += step) {
+        if (i < n) J[i] = 0.0;
+        else if (i < 2 * n) K[i - n] = 0.0;
+        else Jh[i - 2 * n] = 0.0;
+    }
 }
 
 // Read of a table entry whose index is the same for every lane of the wave,
@@ -114,128 +119,191 @@ __global__ __launch_bounds__(256) void k_dmax_all(double *__restrict__ dsh, int6
     if (threadIdx.x == 0) dsh[n] = red[0];
 }
 
-// Hermite density of every pair of one class (ket layout, signed).
+// Hermite density of the pairs of one class, entry (h, i), in both layouts: Dh[i][h]
+// times (-1)^{|h|} (the pair a workgroup shares) and Dhv[h][i] (a lane's own pair).
 template <int LA, int LB>
-__global__ __launch_bounds__(128) void k_dherm(DirectClassDev c, const double *__restrict__ D, int64_t nao,
-                                               double *__restrict__ Dh)
+__device__ __forceinline__ void pair_density(const DirectClassDev &c, const double *__restrict__ D, int64_t nao,
+                                             double *__restrict__ Dh, double *__restrict__ Dhv, int64_t t)
 {
     constexpr int NA = 2 * LA + 1, NB = 2 * LB + 1, LAB = LA + LB, NH = nherm(LAB);
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= c.n) return;
+    const int h = (int)(t / c.npad), i = (int)(t % c.npad);
+    if (h >= NH || i >= c.n) return;
     const int oa = c.off_a[i], ob = c.off_b[i];
     const bool same = c.sh_a[i] == c.sh_b[i];
-    double d[NA * NB];
+    double s = 0.0;
 #pragma unroll
-    for (int ma = 0; ma < NA; ++ma)
-#pragma unroll
-        for (int mb = 0; mb < NB; ++mb) {
-            const double v = D[(int64_t)(oa + ma) * nao + ob + mb];
-            d[ma * NB + mb] = same ? v : v + D[(int64_t)(ob + mb) * nao + oa + ma];
-        }
-    double *out = Dh + c.herm_off + (int64_t)i * NH;
-#pragma unroll
-    for (int t = 0; t <= LAB; ++t)
-#pragma unroll
-        for (int u = 0; u + t <= LAB; ++u)
-#pragma unroll
-            for (int v = 0; v + u + t <= LAB; ++v) {
-                const int h = hidx(t, u, v);
-                double s = 0.0;
-#pragma unroll
-                for (int f = 0; f < NA * NB; ++f) s += c.Eb[(int64_t)(f * NH + h) * c.npad + i] * d[f];
-                out[h] = ((t + u + v) & 1) ? -s : s;
-            }
+    for (int f = 0; f < NA * NB; ++f) {
+        const int ma = f / NB, mb = f % NB;
+        const double v = D[(int64_t)(oa + ma) * nao + ob + mb];
+        s += c.Eb[(int64_t)(f * NH + h) * c.npad + i] * (same ? v : v + D[(int64_t)(ob + mb) * nao + oa + ma]);
+    }
+    const int order = h == 0 ? 0 : h < 4 ? 1 : h < 10 ? 2 : h < 20 ? 3 : 4;   // |tuv|: hidx is grouped by it
+    Dhv[c.herm_off + t] = s;
+    Dh[c.herm_off + (int64_t)i * NH + h] = (order & 1) ? -s : s;
 }
 
-// Shape of the work of one quartet class: the plain shape gives each lane
-// its own bra pair against a ket pair that is the same for the whole wave;
-// the tiled shape (for heavy classes: few pairs, much work per quartet) gives
-// a wave an 8 x 8 tile of (bra, ket) pairs, so that a handful of pairs still
-// fills the lanes, and splits the rows of the first bra shell over blockIdx.z.
-template <bool TILED, int LA>
+// J_f = sum_h E_f[h] Jh[h] of the pairs of one class, entry (f, i), written to both
+// triangles (one triangle's positions for a = b: the block holds both).
+template <int LA, int LB>
+__device__ __forceinline__ void pair_coulomb(const DirectClassDev &c, const double *__restrict__ Jh, int64_t nao,
+                                             double *__restrict__ J, int64_t t)
+{
+    constexpr int NA = 2 * LA + 1, NB = 2 * LB + 1, NH = nherm(LA + LB);
+    const int f = (int)(t / c.npad), i = (int)(t % c.npad);
+    if (f >= NA * NB || i >= c.n) return;
+    double s = 0.0;
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+        s += c.Eb[(int64_t)(f * NH + h) * c.npad + i] * Jh[c.herm_off + (int64_t)h * c.npad + i];
+    const int64_t mu = c.off_a[i] + f / NB, nu = c.off_b[i] + f % NB;
+    J[mu * nao + nu] = s;
+    if (c.sh_a[i] != c.sh_b[i]) J[nu * nao + mu] = s;
+}
+
+// Both passes over every class in one launch: workgroup b belongs to class k for
+// start[k] <= b < start[k + 1].
+struct PairPass {
+    DirectClassDev cls[6];
+    uint32_t start[7];
+};
+template <bool JOUT>
+__global__ __launch_bounds__(256) void k_pair_pass(PairPass g, const double *__restrict__ D, int64_t nao,
+                                                   double *__restrict__ Dh, double *__restrict__ Dhv,
+                                                   const double *__restrict__ Jh, double *__restrict__ J)
+{
+    int k = 0;
+    while (k < 5 && blockIdx.x >= g.start[k + 1]) ++k;
+    const DirectClassDev &c = g.cls[k];
+    const int64_t t = (int64_t)(blockIdx.x - g.start[k]) * 256 + threadIdx.x;
+#define PASS(K, A, B)                                              \
+    case K:                                                        \
+        if (JOUT) pair_coulomb<A, B>(c, Jh, nao, J, t);            \
+        else pair_density<A, B>(c, D, nao, Dh, Dhv, t);            \
+        break;
+    switch (k) {
+        PASS(0, 0, 0) PASS(1, 1, 0) PASS(2, 1, 1) PASS(3, 2, 0) PASS(4, 2, 1) PASS(5, 2, 2)
+    }
+#undef PASS
+}
+
+// Shape of the quartets of u class (LA, LB) and v class (LC, LD).  Light ones: each of
+// a workgroup's waves has its own 64 v; every function of v unrolled.  Heavy ones
+// (4,000 multiply-adds a quartet and more: long chains on few pairs): four waves
+// share 64 v, each with its own copy of R, and are dealt the functions of v.  With the
+// line at 6,000, which moves (dp|pp) to the light side, 32 waters take 4.32 ms, not 4.04.
+template <int LA, int LB, int LC, int LD>
 struct QuartetShape {
-    static constexpr int NA = 2 * LA + 1;
-    static constexpr bool heavy = TILED;
-    static constexpr int TK = heavy ? 8 : 1;       // ket pairs per wave iteration
-    static constexpr int TB = 64 / TK;             // bra pairs per wave
-    static constexpr bool split_a = heavy && NA > 1;
+    static constexpr int NA = 2 * LA + 1, NB = 2 * LB + 1, NC = 2 * LC + 1, ND = 2 * LD + 1;
+    static constexpr int NHU = nherm(LA + LB), NHV = nherm(LC + LD);
+    static constexpr int work = NC * ND * NHU * (NHV + NA * NB);
+    static constexpr int NS = work < 4000 ? 1 : 4;   // waves that share 64 v
+};
+constexpr size_t kRowsBytes = 160 * 1024;   // LDS for the rows of a and b (all there is)
+
+// One launch of k_direct: combination k (u class cu[k], v class cv[k]) has the
+// workgroups start[k] <= b < start[k + 1]: pieces of vchunk v, for every u.
+constexpr int pair_class(int la, int lb) { return la == 0 ? 0 : la == 1 ? 1 + lb : 3 + lb; }
+constexpr int kMaxCombos = 13;
+struct DirectJob {
+    DirectClassDev cls[6];
+    uint32_t start[kMaxCombos + 1];
+    int32_t vchunk[kMaxCombos], lds[kMaxCombos];
+    double tau;
+    const double *boys, *D;
+    int64_t nao;
+    const double *Dh, *Dhv;
+    double *Jh, *K;
+    const double *dsh;
+    int32_t nsh;
 };
 
-// The integral kernel for bra class (LA, LB) and ket class (LC, LD).
-template <int LA, int LB, int LC, int LD, bool TILED>
-__global__ __launch_bounds__(64) void k_direct(DirectClassDev bra, DirectClassDev ket, int32_t kchunk, double tau,
-                                               const double *__restrict__ boys_tab, const double *__restrict__ D,
-                                               int64_t nao, const double *__restrict__ Dh, double *__restrict__ Jh,
-                                               double *__restrict__ K, int32_t with_k,
-                                               const double *__restrict__ dsh, int32_t nsh)
+// The quartets of one combination, as a function of its own: inlined side by side in
+// one kernel, the compiler loses the tables' uniformity and spills thousands of
+// registers.  A callee's arguments arrive in vector registers, hence the readfirstlanes;
+// the job is read where the launch put it, not from a copy in scratch.
+typedef const __attribute__((address_space(4))) DirectJob *JobPtr;
+typedef __attribute__((address_space(3))) double *LdsPtr;
+template <int LA, int LB, int LC, int LD, int WAVES, bool DLDS>
+__device__ __noinline__ void direct_quartets(JobPtr job_, int u_, int piece_, int k_, uint32_t lds_)
 {
-    constexpr int LAB = LA + LB, LCD = LC + LD, L = LAB + LCD;
-    constexpr int NHB = nherm(LAB), NHK = nherm(LCD);
-    constexpr int NA = 2 * LA + 1, NB = 2 * LB + 1, NC = 2 * LC + 1, ND = 2 * LD + 1;
-    constexpr int NFB = NA * NB, NFK = NC * ND;
-    using S = QuartetShape<TILED, LA>;
-    constexpr int TK = S::TK, TB = S::TB;
-    // Small bra classes: the rows of a unrolled and the bra Hermite table kept
-    // in registers over the ket loop; larger ones loop over the rows of a at
-    // run time (or take one row per blockIdx.z) and read the table per use.
-    constexpr int kUnrollA = NFB <= 3 ? NA : 1;
-    constexpr bool kHoist = NFB <= 3 && !S::split_a;
-
-    const int lane = threadIdx.x, ib = lane / TK, jk = lane % TK;
-    const int i = blockIdx.x * TB + ib;
-    const bool valid = i < bra.n;
-    const int j0 = blockIdx.y * kchunk;
-    const int j1 = min(ket.n, j0 + kchunk);
-    if (j0 >= j1) return;
-    // the Schwarz bound of the loop ends: Q_ab Q_cd, times the largest
-    // |D - D0| anywhere for an incremental build
-    const double qwave = uniform_load(bra.q + blockIdx.x * TB) *
-                         (dsh ? uniform_load(dsh + (int64_t)nsh * nsh) : 1.0);   // largest bound of this wave
-    if (!(uniform_load(ket.q + j0) * qwave >= tau)) return;
-    const int ma0 = S::split_a ? (int)blockIdx.z : 0;
-    const int ma1 = S::split_a ? ma0 + 1 : NA;
-    const bool do_j = !S::split_a || blockIdx.z == 0;
-
-    const int ic = valid ? i : blockIdx.x * TB;
-    const double qa = bra.q[ic];
-    const double p = bra.p[ic], Px = bra.px[ic], Py = bra.py[ic], Pz = bra.pz[ic];
-    const int oa = bra.off_a[ic], ob = bra.off_b[ic], sa = bra.sh_a[ic], sb = bra.sh_b[ic];
+    const uint64_t jp = (uint64_t)job_;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)jp), hi = __builtin_amdgcn_readfirstlane((uint32_t)(jp >> 32));
+    const JobPtr jobp = (JobPtr)(((uint64_t)hi << 32) | lo);
+    const int u = __builtin_amdgcn_readfirstlane(u_), piece = __builtin_amdgcn_readfirstlane(piece_), kk = __builtin_amdgcn_readfirstlane(k_);
+    const LdsPtr rows = (LdsPtr)(uint32_t)__builtin_amdgcn_readfirstlane(lds_);   // K rows of a, then of b
+    const __attribute__((address_space(4))) DirectJob &job = *jobp;
+    const __attribute__((address_space(4))) DirectClassDev &U = job.cls[pair_class(LA, LB)], &V = job.cls[pair_class(LC, LD)];
+    const int vchunk = job.vchunk[kk], rows_in_lds = job.lds[kk];
+    using S = QuartetShape<LA, LB, LC, LD>;
+    constexpr int NA = S::NA, NB = S::NB, NC = S::NC, ND = S::ND, NHU = S::NHU, NHV = S::NHV;
+    constexpr int LU = LA + LB, LV = LC + LD, L = LU + LV, NS = S::NS, G = WAVES / NS;
+    constexpr bool same = LA == LC && LB == LD;
+    const double tau = job.tau, *__restrict__ boys_tab = job.boys, *__restrict__ D = job.D;
+    const double *__restrict__ Dh = job.Dh, *__restrict__ Dhv = job.Dhv, *__restrict__ dsh = job.dsh;
+    double *__restrict__ Jh = job.Jh, *__restrict__ K = job.K;
+    const int64_t nao = job.nao;
+    const int nsh = job.nsh;
+    const int nv = same ? u + 1 : V.n;
+    const int v0 = piece * vchunk, v1 = min(nv, v0 + vchunk);
+    if (v0 >= v1) return;
+    const double qu = uniform_load(U.q + u);
+    // the Schwarz bound of the walk's end: Q_u Q_v, times the largest |D - D0|
+    // anywhere for an incremental build
+    const double qwalk = qu * (dsh ? uniform_load(dsh + (int64_t)nsh * nsh) : 1.0);
+    if (!(uniform_load(V.q + v0) * qwalk >= tau)) return;
+    const int oa = uniform_load(U.off_a + u), ob = uniform_load(U.off_b + u);
+    const int sa = uniform_load(U.sh_a + u), sb = uniform_load(U.sh_b + u);
     const bool ab_same = sa == sb;
-
-    double ebr[kHoist ? NFB * NHB : 1];
-    if constexpr (kHoist) {
-#pragma unroll
-        for (int x = 0; x < NFB * NHB; ++x) ebr[x] = bra.Eb[(int64_t)x * bra.npad + ic];
+    const int nao32 = (int)nao, nrows = (ab_same ? NA : NA + NB) * nao32;
+    const int brow = ab_same ? 0 : NA;
+    const LdsPtr drows = rows + (NA + NB) * nao32;   // D rows of a, then (if another shell) of b
+    if (DLDS || rows_in_lds) {
+        for (int i = threadIdx.x; i < nrows; i += 64 * WAVES) rows[i] = 0.0;
+        if constexpr (DLDS)
+            for (int r = 0; r < (ab_same ? NA : NA + NB); ++r)
+                for (int i = threadIdx.x; i < nao32; i += 64 * WAVES)
+                    drows[r * nao32 + i] = D[(int64_t)(r < NA ? oa + r : ob + r - NA) * nao + i];
+        __syncthreads();
     }
-    double jh[NHB];
-#pragma unroll
-    for (int h = 0; h < NHB; ++h) jh[h] = 0.0;
-    bool any = false;
+    // F[row][col] += x, row = a function of a (0 ..) or of b (NA ..)
+    auto add = [&](int row, int col, double x) {
+        if (DLDS || rows_in_lds)
+            __hip_atomic_fetch_add(rows + (row * nao32 + col), x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else
+            unsafeAtomicAdd(&K[(int64_t)(row < NA ? oa + row : ob + row - NA) * nao + col], x);
+    };
 
-    // ket entries: scalar loads when the whole wave reads the same pair
-    auto kd = [&](const double *t, int64_t x) -> double {
-        if constexpr (TK == 1) return uniform_load(t + x);
-        else return t[x];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = wave % NS, group = wave / NS;
+    const double q = uniform_load(U.p + u);
+    const double Qx = uniform_load(U.px + u), Qy = uniform_load(U.py + u), Qz = uniform_load(U.pz + u);
+    const double *ek = U.Ek + (int64_t)u * (NA * NB * NHU);   // [g][k], signed
+    const double *du = Dh + U.herm_off + (int64_t)u * NHU;
+    // D between a function of a (row < NA) or b and function col of v
+    auto dens = [&](int row, int col) -> double {
+        if constexpr (DLDS) return drows[(row < NA ? row : brow + row - NA) * nao32 + col];
+        return D[(int64_t)(row < NA ? oa + row : ob + row - NA) * nao + col];
     };
-    auto ki = [&](const int32_t *t, int64_t x) -> int32_t {
-        if constexpr (TK == 1) return uniform_load(t + x);
-        else return t[x];
-    };
-    for (int jt = j0; jt < j1; jt += TK) {
-        if (!(uniform_load(ket.q + jt) * qwave >= tau)) break;   // the first ket of a step is its largest
-        const int j = jt + jk;
-        if (!(valid && j < j1 && qa * kd(ket.q, j) >= tau)) continue;
+    double ju[NHU];
+#pragma unroll
+    for (int k = 0; k < NHU; ++k) ju[k] = 0.0;
+
+    for (int jb = v0 + 64 * group; jb < v1; jb += 64 * G) {
+        if (!(uniform_load(V.q + jb) * qwalk >= tau)) break;   // the first v of a step is its largest
+        const int j = jb + lane;
+        if (!(j < v1 && qu * V.q[j] >= tau)) continue;
+        const int sc = V.sh_a[j], sd = V.sh_b[j];
         if (dsh) {
-            // density-weighted bound: Q_ab Q_cd times the largest |dD| of the
-            // blocks this quartet contracts with (cd for J; bd, bc, ad, ac for K)
-            const int64_t jc = ki(ket.sh_a, j), jd = ki(ket.sh_b, j);
-            const double dm = fmax(fmax(dsh[jc * nsh + jd], fmax(dsh[(int64_t)sb * nsh + jd], dsh[(int64_t)sb * nsh + jc])),
-                                   fmax(dsh[(int64_t)sa * nsh + jd], dsh[(int64_t)sa * nsh + jc]));
-            if (!(qa * kd(ket.q, j) * dm >= tau)) continue;
+            // density-weighted bound: Q_u Q_v times the largest |dD| of the blocks
+            // this quartet contracts with (cd and ab for J; bd, bc, ad, ac for K)
+            auto m = [&](int x, int y) { return dsh[(int64_t)x * nsh + y]; };
+            const double dm = fmax(fmax(fmax(m(sc, sd), m(sa, sb)), fmax(m(sb, sd), m(sb, sc))),
+                                   fmax(m(sa, sd), m(sa, sc)));
+            if (!(qu * V.q[j] * dm >= tau)) continue;
         }
-        any = true;
-        const double q = kd(ket.p, j);
-        const double X = Px - kd(ket.px, j), Y = Py - kd(ket.py, j), Z = Pz - kd(ket.pz, j);
+        const bool cd_same = sc == sd, uv_same = same && j == u;
+        const double p = V.p[j];
+        const double X = V.px[j] - Qx, Y = V.py[j] - Qy, Z = V.pz[j] - Qz;
         const double pq = p + q, alpha = p * q / pq;
         double F[L + 1];
         boys<L>(alpha * (X * X + Y * Y + Z * Z), F, boys_tab);
@@ -243,184 +311,198 @@ __global__ __launch_bounds__(64) void k_direct(DirectClassDev bra, DirectClassDe
         hermite_R<L>(alpha, X, Y, Z, F, R);
         const double pref = kTwoPi52 / (p * q * sqrt(pq));
 
-        // Coulomb: Jh[h] += pref sum_k R[h + k] Dh[k]
-        if (do_j) {
-            const double *dh = Dh + ket.herm_off + (int64_t)j * NHK;
+        // Coulomb, both ways
+        if (NS == 1 || part == 0) {
 #pragma unroll
-            for (int t = 0; t <= LAB; ++t)
+            for (int t = 0; t <= LV; ++t)
 #pragma unroll
-                for (int u = 0; u + t <= LAB; ++u)
+                for (int x = 0; x + t <= LV; ++x)
 #pragma unroll
-                    for (int v = 0; v + u + t <= LAB; ++v) {
+                    for (int y = 0; y + x + t <= LV; ++y) {
+                        const int h = hidx(t, x, y);
+                        const double dv = pref * Dhv[V.herm_off + (int64_t)h * V.npad + j];
                         double s = 0.0;
 #pragma unroll
-                        for (int t2 = 0; t2 <= LCD; ++t2)
+                        for (int t2 = 0; t2 <= LU; ++t2)
 #pragma unroll
-                            for (int u2 = 0; u2 + t2 <= LCD; ++u2)
+                            for (int x2 = 0; x2 + t2 <= LU; ++x2)
 #pragma unroll
-                                for (int v2 = 0; v2 + u2 + t2 <= LCD; ++v2)
-                                    s += R[hidx(t + t2, u + u2, v + v2)] * kd(dh, hidx(t2, u2, v2));
-                        jh[hidx(t, u, v)] += pref * s;
+                                for (int y2 = 0; y2 + x2 + t2 <= LU; ++y2) {
+                                    const int k = hidx(t2, x2, y2);
+                                    const double r = R[hidx(t + t2, x + x2, y + y2)];
+                                    ju[k] += r * dv;
+                                    s += r * uniform_load(du + k);
+                                }
+                        if (!uv_same) unsafeAtomicAdd(&Jh[V.herm_off + (int64_t)h * V.npad + j], pref * s);
                     }
         }
-        if (!with_k) continue;
 
-        // Exchange
-        const int oc = ki(ket.off_a, j), od = ki(ket.off_b, j), sc = ki(ket.sh_a, j), sd = ki(ket.sh_b, j);
-        const bool cd_same = sc == sd;
-        const bool w_ac = sa >= sc, w_ad = !cd_same && sa >= sd;
-        const bool w_bc = !ab_same && sb >= sc, w_bd = !ab_same && !cd_same && sb >= sd;
-        if (!(w_ac || w_ad || w_bc || w_bd)) continue;
-        const double *ek = ket.Ek + (int64_t)j * NFK * NHK;
-        // rows of b: over every ma of this thread in registers (one row of a
-        // per thread: flushed per mb instead)
-        double kbc[S::split_a ? 1 : NB][NC], kbd[S::split_a ? 1 : NB][ND];
-        if constexpr (!S::split_a) {
+        // Exchange: function f = (mc, md) of v against every (ma, mb) of u
+        const double kpref = uv_same ? 0.5 * pref : pref;
+        const int oc = V.off_a[j], od = V.off_b[j];
+        auto integrals = [&](int f, double (&I)[NA * NB]) {
+            double W[NHU];
 #pragma unroll
-            for (int x = 0; x < NB; ++x) {
+            for (int k = 0; k < NHU; ++k) W[k] = 0.0;
 #pragma unroll
-                for (int y = 0; y < NC; ++y) kbc[x][y] = 0.0;
+            for (int t = 0; t <= LV; ++t)
 #pragma unroll
-                for (int y = 0; y < ND; ++y) kbd[x][y] = 0.0;
-            }
-        }
-#pragma unroll kUnrollA
-        for (int ma = ma0; ma < ma1; ++ma) {
-            double kac[NC], kad[ND];
+                for (int x = 0; x + t <= LV; ++x)
 #pragma unroll
-            for (int y = 0; y < NC; ++y) kac[y] = 0.0;
+                    for (int y = 0; y + x + t <= LV; ++y) {
+                        const double e = V.Eb[(int64_t)(f * NHV + hidx(t, x, y)) * V.npad + j];
 #pragma unroll
-            for (int y = 0; y < ND; ++y) kad[y] = 0.0;
+                        for (int t2 = 0; t2 <= LU; ++t2)
 #pragma unroll
-            for (int mb = 0; mb < NB; ++mb) {
-                const int f = ma * NB + mb;
-                // V[k] = sum_h E_f[h] R[h + k]
-                double V[NHK];
+                            for (int x2 = 0; x2 + t2 <= LU; ++x2)
 #pragma unroll
-                for (int k = 0; k < NHK; ++k) V[k] = 0.0;
-#pragma unroll
-                for (int t = 0; t <= LAB; ++t)
-#pragma unroll
-                    for (int u = 0; u + t <= LAB; ++u)
-#pragma unroll
-                        for (int v = 0; v + u + t <= LAB; ++v) {
-                            const int h = hidx(t, u, v);
-                            double e;
-                            if constexpr (kHoist) e = ebr[f * NHB + h];
-                            else e = bra.Eb[(int64_t)(f * NHB + h) * bra.npad + ic];
-#pragma unroll
-                            for (int t2 = 0; t2 <= LCD; ++t2)
-#pragma unroll
-                                for (int u2 = 0; u2 + t2 <= LCD; ++u2)
-#pragma unroll
-                                    for (int v2 = 0; v2 + u2 + t2 <= LCD; ++v2)
-                                        V[hidx(t2, u2, v2)] += e * R[hidx(t + t2, u + u2, v + v2)];
-                        }
-                double rbc[NC], rbd[ND];
-#pragma unroll
-                for (int y = 0; y < NC; ++y) rbc[y] = 0.0;
-#pragma unroll
-                for (int y = 0; y < ND; ++y) rbd[y] = 0.0;
-#pragma unroll
-                for (int mc = 0; mc < NC; ++mc)
-#pragma unroll
-                    for (int md = 0; md < ND; ++md) {
-                        const int g = mc * ND + md;
-                        double I = 0.0;
-#pragma unroll
-                        for (int k = 0; k < NHK; ++k) I += kd(ek, g * NHK + k) * V[k];
-                        I *= pref;
-                        kac[mc] += I * D[(int64_t)(ob + mb) * nao + od + md];
-                        kad[md] += I * D[(int64_t)(ob + mb) * nao + oc + mc];
-                        rbc[mc] += I * D[(int64_t)(oa + ma) * nao + od + md];
-                        rbd[md] += I * D[(int64_t)(oa + ma) * nao + oc + mc];
+                                for (int y2 = 0; y2 + x2 + t2 <= LU; ++y2)
+                                    W[hidx(t2, x2, y2)] += e * R[hidx(t + t2, x + x2, y + y2)];
                     }
-                if constexpr (S::split_a) {
-                    if (w_bc)
 #pragma unroll
-                        for (int y = 0; y < NC; ++y) unsafeAtomicAdd(&K[(int64_t)(ob + mb) * nao + oc + y], rbc[y]);
-                    if (w_bd)
+            for (int g = 0; g < NA * NB; ++g) {
+                double s = 0.0;
 #pragma unroll
-                        for (int y = 0; y < ND; ++y) unsafeAtomicAdd(&K[(int64_t)(ob + mb) * nao + od + y], rbd[y]);
-                } else {
+                for (int k = 0; k < NHU; ++k) s += uniform_load(ek + g * NHU + k) * W[k];
+                I[g] = kpref * s;
+            }
+        };
+        // contributions of one f to the columns c (kc) and d (kd): rows of a, then of b
+        auto contract = [&](const double (&I)[NA * NB], int c, int d, double (&kc)[NA + NB], double (&kd)[NA + NB]) {
+            double dac[NA], dad[NA], dbc[NB], dbd[NB];
 #pragma unroll
-                    for (int y = 0; y < NC; ++y) kbc[mb][y] += rbc[y];
+            for (int m = 0; m < NA; ++m) { dac[m] = dens(m, c); dad[m] = dens(m, d); }
 #pragma unroll
-                    for (int y = 0; y < ND; ++y) kbd[mb][y] += rbd[y];
+            for (int m = 0; m < NB; ++m) { dbc[m] = dens(NA + m, c); dbd[m] = dens(NA + m, d); }
+#pragma unroll
+            for (int ma = 0; ma < NA; ++ma)
+#pragma unroll
+                for (int mb = 0; mb < NB; ++mb) {
+                    const double v = I[ma * NB + mb];
+                    kc[ma] += v * dbd[mb];
+                    kd[ma] += v * dbc[mb];
+                    kc[NA + mb] += v * dad[ma];
+                    kd[NA + mb] += v * dac[ma];
                 }
+        };
+        auto flush = [&](const double (&x)[NA + NB], int col) {
+#pragma unroll
+            for (int m = 0; m < NA; ++m) add(m, col, x[m]);
+            if (!ab_same)
+#pragma unroll
+                for (int m = NA; m < NA + NB; ++m) add(m, col, x[m]);
+        };
+        if constexpr (NS == 1) {
+            double kd[ND][NA + NB];
+#pragma unroll
+            for (int md = 0; md < ND; ++md)
+#pragma unroll
+                for (int m = 0; m < NA + NB; ++m) kd[md][m] = 0.0;
+#pragma unroll
+            for (int mc = 0; mc < NC; ++mc) {
+                double kc[NA + NB];
+#pragma unroll
+                for (int m = 0; m < NA + NB; ++m) kc[m] = 0.0;
+#pragma unroll
+                for (int md = 0; md < ND; ++md) {
+                    double I[NA * NB];
+                    integrals(mc * ND + md, I);
+                    contract(I, oc + mc, od + md, kc, kd[md]);
+                }
+                flush(kc, oc + mc);
             }
-            if (w_ac)
+            if (!cd_same)
 #pragma unroll
-                for (int y = 0; y < NC; ++y) unsafeAtomicAdd(&K[(int64_t)(oa + ma) * nao + oc + y], kac[y]);
-            if (w_ad)
+                for (int md = 0; md < ND; ++md) flush(kd[md], od + md);
+        } else {
+#pragma unroll 1
+            for (int f = part; f < NC * ND; f += NS) {
+                double I[NA * NB], kc[NA + NB], kd[NA + NB];
 #pragma unroll
-                for (int y = 0; y < ND; ++y) unsafeAtomicAdd(&K[(int64_t)(oa + ma) * nao + od + y], kad[y]);
-        }
-        if constexpr (!S::split_a) {
-            if (w_bc)
-#pragma unroll
-                for (int x = 0; x < NB; ++x)
-#pragma unroll
-                    for (int y = 0; y < NC; ++y) unsafeAtomicAdd(&K[(int64_t)(ob + x) * nao + oc + y], kbc[x][y]);
-            if (w_bd)
-#pragma unroll
-                for (int x = 0; x < NB; ++x)
-#pragma unroll
-                    for (int y = 0; y < ND; ++y) unsafeAtomicAdd(&K[(int64_t)(ob + x) * nao + od + y], kbd[x][y]);
+                for (int m = 0; m < NA + NB; ++m) kc[m] = kd[m] = 0.0;
+                integrals(f, I);
+                contract(I, oc + f / ND, od + f % ND, kc, kd);
+                flush(kc, oc + f / ND);
+                if (!cd_same) flush(kd, od + f % ND);
+            }
         }
     }
-    if (!do_j) return;
-    if constexpr (TK > 1) {
-        // the TK lanes of one bra pair are adjacent: sum their Hermite J vectors
-        int a = any ? 1 : 0;
+
+    // Hermite J of u: over the wave, then one atomic per entry and wave
+    if (NS == 1 || part == 0) {
 #pragma unroll
-        for (int w = TK / 2; w > 0; w >>= 1) {
+        for (int t = 0; t <= LU; ++t)
 #pragma unroll
-            for (int h = 0; h < NHB; ++h) jh[h] += __shfl_xor(jh[h], w);
-            a |= __shfl_xor(a, w);
-        }
-        any = a != 0;
+            for (int x = 0; x + t <= LU; ++x)
+#pragma unroll
+                for (int y = 0; y + x + t <= LU; ++y) {
+                    const int k = hidx(t, x, y);
+                    double s = ju[k];
+#pragma unroll
+                    for (int w = 32; w > 0; w >>= 1) s += __shfl_xor(s, w);
+                    if (lane == 0 && s != 0.0)
+                        unsafeAtomicAdd(&Jh[U.herm_off + (int64_t)k * U.npad + u], ((t + x + y) & 1) ? -s : s);
+                }
     }
-    if (valid && any && jk == 0) {
-#pragma unroll
-        for (int h = 0; h < NHB; ++h)
-            unsafeAtomicAdd(&Jh[bra.herm_off + (int64_t)h * bra.npad + i], jh[h]);
+    if (DLDS || rows_in_lds) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < nrows; i += 64 * WAVES) {
+            const double x = rows[i];
+            if (x != 0.0) {
+                const int r = i / nao32, col = i - r * nao32;
+                unsafeAtomicAdd(&K[(int64_t)(r < NA ? oa + r : ob + r - NA) * nao + col], x);
+            }
+        }
     }
 }
 
-// J_f = sum_h E_f[h] Jh[h] for every pair of one class, written to both
-// triangles (one triangle's positions for a = b: the block holds both).
-template <int LA, int LB>
-__global__ __launch_bounds__(128) void k_jout(DirectClassDev c, const double *__restrict__ Jh, int64_t nao,
-                                              double *__restrict__ J)
+// The combinations by the registers they take, heaviest first within a launch: one
+// launch each for those of up to 512 (one wave per SIMD, workgroups of 4 waves), up to
+// 256 (2, 8 waves) and up to 168 (3, 6 waves).  Classes of one launch run side by
+// side: one launch per combination took 1.20 ms instead of 0.54 for the incremental build
+// of 8 waters.  Squeezing (dp|dp) and lighter ones of the first launch into 256 registers,
+// for a second wave, spills: 4.31 ms instead of 3.82 on 32 waters.  The row counts
+// keep two sets of rows (K and D) in LDS up to 1,024, 1,280 and 2,560 AO; beyond, K alone
+// up to twice that, and then neither.
+#define COMBOS_0(X) X(0, 2, 2, 2, 2) X(1, 2, 2, 2, 1) X(2, 2, 1, 2, 1) X(3, 2, 2, 1, 1) X(4, 2, 2, 2, 0)       \
+                    X(5, 2, 1, 1, 1) X(6, 2, 1, 2, 0) X(7, 2, 2, 1, 0) X(8, 1, 1, 1, 1) X(9, 2, 0, 1, 1)       \
+                    X(10, 2, 1, 1, 0) X(11, 2, 0, 2, 0) X(12, 2, 2, 0, 0)
+#define COMBOS_1(X) X(0, 2, 1, 0, 0) X(1, 1, 1, 1, 0) X(2, 2, 0, 1, 0) X(3, 1, 1, 0, 0) X(4, 2, 0, 0, 0)
+#define COMBOS_2(X) X(0, 1, 0, 1, 0) X(1, 1, 0, 0, 0) X(2, 0, 0, 0, 0)
+constexpr int group_waves(int group) { return group == 0 ? 4 : group == 1 ? 8 : 6; }
+constexpr int group_rows(int group) { return group == 0 ? 10 : group == 1 ? 8 : 4; }   // most rows of a and b
+constexpr int group_simd(int group) { return group == 2 ? 3 : group + 1; }             // waves per SIMD
+
+template <int GROUP, bool DLDS>
+__global__ __launch_bounds__(64 * group_waves(GROUP), group_simd(GROUP)) void k_direct(DirectJob job)
 {
-    constexpr int NA = 2 * LA + 1, NB = 2 * LB + 1, NH = nherm(LA + LB);
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= c.n) return;
-    const int oa = c.off_a[i], ob = c.off_b[i];
-    const bool same = c.sh_a[i] == c.sh_b[i];
-    double jh[NH];
-#pragma unroll
-    for (int h = 0; h < NH; ++h) jh[h] = Jh[c.herm_off + (int64_t)h * c.npad + i];
-#pragma unroll
-    for (int ma = 0; ma < NA; ++ma)
-#pragma unroll
-        for (int mb = 0; mb < NB; ++mb) {
-            const int f = ma * NB + mb;
-            double s = 0.0;
-#pragma unroll
-            for (int h = 0; h < NH; ++h) s += c.Eb[(int64_t)(f * NH + h) * c.npad + i] * jh[h];
-            J[(int64_t)(oa + ma) * nao + ob + mb] = s;
-            if (!same) J[(int64_t)(ob + mb) * nao + oa + ma] = s;
-        }
+    extern __shared__ double rows[];
+    uint32_t lds = (uint32_t)(uintptr_t)(LdsPtr)rows;
+    asm volatile("" : "+s"(lds));   // opaque: the callees take the address from here, not from the compiler's tables
+    const JobPtr args = (JobPtr)__builtin_amdgcn_kernarg_segment_ptr();   // job itself: the only argument
+    int k = 0;
+    while (k < kMaxCombos - 1 && blockIdx.x >= job.start[k + 1]) ++k;
+    const int local = (int)(blockIdx.x - job.start[k]);
+#define RUN(I, A, B, C, E)                                                                                    \
+    case I: {                                                                                                 \
+        const int n = job.cls[pair_class(A, B)].n;                                                            \
+        direct_quartets<A, B, C, E, group_waves(GROUP), DLDS>(args, local % n, local / n, I, lds);                                      \
+        break;                                                                                                \
+    }
+    if constexpr (GROUP == 0) {
+        switch (k) { COMBOS_0(RUN) }
+    } else if constexpr (GROUP == 1) {
+        switch (k) { COMBOS_1(RUN) }
+    } else {
+        switch (k) { COMBOS_2(RUN) }
+    }
+#undef RUN
 }
 
-// Symmetrise J (mean of the two triangles), complete K from its lower shell
-// triangle (mean on diagonal shell blocks), add the reference J0, K0 of an
-// incremental build, and form the block partials of sum D.J and sum D.K
+// Symmetrise J (mean of the two triangles), K = F + F^T, add the reference J0, K0
+// of an incremental build, and form the block partials of sum D.J and sum D.K
 // over the lower triangle mu >= nu.
-__global__ __launch_bounds__(256) void k_direct_finish(int64_t nao, const int32_t *__restrict__ fn_shell,
-                                                       const double *__restrict__ D, const double *__restrict__ J0,
+__global__ __launch_bounds__(256) void k_direct_finish(int64_t nao, const double *__restrict__ D, const double *__restrict__ J0,
                                                        const double *__restrict__ K0, double *__restrict__ J,
                                                        double *__restrict__ K, double *__restrict__ Epart)
 {
@@ -433,7 +515,7 @@ __global__ __launch_bounds__(256) void k_direct_finish(int64_t nao, const int32_
         const int64_t nu = e - mu * (mu + 1) / 2;
         const int64_t a = mu * nao + nu, b = nu * nao + mu;
         double jv = mu == nu ? J[a] : 0.5 * (J[a] + J[b]);
-        double kv = (fn_shell[mu] == fn_shell[nu] && mu != nu) ? 0.5 * (K[a] + K[b]) : K[a];
+        double kv = K[a] + K[b];
         if (J0) { jv += J0[a]; kv += K0[a]; }   // increment on top of the reference (symmetric) J0, K0
         J[a] = jv; J[b] = jv;
         K[a] = kv; K[b] = kv;
@@ -464,80 +546,66 @@ __global__ __launch_bounds__(256) void k_direct_energy(const double *__restrict_
     if (threadIdx.x == 0) { E[0] = 0.5 * sj[0]; E[1] = -0.25 * sk[0]; }
 }
 
-template <int LA, int LB, int LC, int LD, bool TILED>
-static void launch_shape(const DirectClassDev &bra, const DirectClassDev &ket, double tau, const double *boys,
-                         const double *D, int64_t nao, const double *Dh, double *Jh, double *K, const double *dsh,
-                         int nsh, hipStream_t s)
+// The walk over v is cut where a combination has fewer than kMinWalks u: a workgroup
+// costs the staging and the flush of its rows, so longer walks win (cut for 2,048
+// workgroups 5.35 ms, 512: 4.04, 256: 3.89, 128: 3.82 on 32 waters; 8 waters 0.54, 0.54,
+// 0.53, 0.51).
+constexpr int kMinWalks = 128;
+
+template <int LA, int LB, int LC, int LD, int WAVES>
+static uint32_t plan_combo(DirectJob &g, int k, size_t &lds)
 {
-    using S = QuartetShape<TILED, LA>;
-    const int gx = (bra.n + S::TB - 1) / S::TB;
-    const int gz = S::split_a ? 2 * LA + 1 : 1;
-    // split the ket range into about 32768 waves per launch, at least two
-    // ket pairs (or one tile step) per split: with pairs sorted by Schwarz
-    // factor, short splits let the many waves whose bound fails early end
-    // early, and the long loops of the leading pairs spread over the chip
-    // (measured against 4096 / 8192 / 16384 waves and 4-32 pairs)
-    const int minchunk = S::heavy ? S::TK : 2;
-    const int want = std::max(1, (32768 + gx * gz - 1) / (gx * gz));
-    const int nchunk = std::max(1, std::min(want, (ket.n + minchunk - 1) / minchunk));
-    int kchunk = (ket.n + nchunk - 1) / nchunk;
-    kchunk = (kchunk + S::TK - 1) / S::TK * S::TK;
-    const int gy = (ket.n + kchunk - 1) / kchunk;
-    hipLaunchKernelGGL((k_direct<LA, LB, LC, LD, TILED>), dim3((unsigned)gx, (unsigned)gy, (unsigned)gz), dim3(64), 0,
-                       s, bra, ket, kchunk, tau, boys, D, nao, Dh, Jh, K, 1, dsh, nsh);
+    using S = QuartetShape<LA, LB, LC, LD>;
+    const DirectClassDev &U = g.cls[pair_class(LA, LB)], &V = g.cls[pair_class(LC, LD)];
+    if (U.n <= 0 || V.n <= 0) return 0;
+    const int step = 64 * (WAVES / S::NS), steps = (V.n + step - 1) / step;
+    const int pieces = std::max(1, std::min(steps, (kMinWalks + U.n - 1) / U.n));
+    g.vchunk[k] = (steps + pieces - 1) / pieces * step;
+    const size_t bytes = (size_t)(S::NA + S::NB) * (size_t)g.nao * 8;
+    g.lds[k] = bytes <= kRowsBytes;
+    if (g.lds[k]) lds = std::max(lds, bytes);
+    return (uint32_t)U.n * (uint32_t)((V.n + g.vchunk[k] - 1) / g.vchunk[k]);
 }
 
-// Tiled shape for total angular momentum 5 and up; for a d shell first in the
-// bra (pairs few and costly) when that class has under 512 pairs; else plain.
-template <int LA, int LB, int LC, int LD>
-static void launch_quartets(const DirectClassDev &bra, const DirectClassDev &ket, double tau, const double *boys,
-                            const double *D, int64_t nao, const double *Dh, double *Jh, double *K, const double *dsh,
-                            int nsh, hipStream_t s)
+template <int GROUP>
+static void launch_group(DirectJob g, hipStream_t s)
 {
-    constexpr int L = LA + LB + LC + LD;
-    if constexpr (L >= 5) {
-        launch_shape<LA, LB, LC, LD, true>(bra, ket, tau, boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    } else if constexpr (LA == 2) {
-        if (bra.n < 512) launch_shape<LA, LB, LC, LD, true>(bra, ket, tau, boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-        else launch_shape<LA, LB, LC, LD, false>(bra, ket, tau, boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    } else {
-        launch_shape<LA, LB, LC, LD, false>(bra, ket, tau, boys, D, nao, Dh, Jh, K, dsh, nsh, s);
+    size_t lds = 0;
+    uint32_t total = 0;
+    int n = 0;
+#define PLAN(I, A, B, C, E)                          \
+    g.start[n++] = total;                            \
+    total += plan_combo<A, B, C, E, group_waves(GROUP)>(g, I, lds);
+    if constexpr (GROUP == 0) { COMBOS_0(PLAN) }
+    else if constexpr (GROUP == 1) { COMBOS_1(PLAN) }
+    else { COMBOS_2(PLAN) }
+#undef PLAN
+    for (; n <= kMaxCombos; ++n) g.start[n] = total;
+    if (total == 0) return;
+    const size_t both = (size_t)2 * group_rows(GROUP) * (size_t)g.nao * 8;
+    if (both <= kRowsBytes)
+        hipLaunchKernelGGL((k_direct<GROUP, true>), dim3(total), dim3(64 * group_waves(GROUP)), both, s, g);
+    else
+        hipLaunchKernelGGL((k_direct<GROUP, false>), dim3(total), dim3(64 * group_waves(GROUP)), lds, s, g);
+}
+
+// The Hermite densities (JOUT false) or J (true) of every class.
+template <bool JOUT>
+static void launch_pair_pass(const DirectClassDev *cls, const double *D, int64_t nao, double *Dh, double *Dhv,
+                             const double *Jh, double *J, hipStream_t s)
+{
+    PairPass g{};
+    uint32_t total = 0;
+    for (int k = 0; k < 6; ++k) {
+        const int la = kPairClassLa[k], lb = kPairClassLb[k];
+        const int64_t per = JOUT ? (2 * la + 1) * (2 * lb + 1) : nherm(la + lb);
+        g.cls[k] = cls[k];
+        g.start[k] = total;
+        if (cls[k].n > 0) total += (uint32_t)((per * cls[k].npad + 255) / 256);
     }
-}
-
-template <int LA, int LB>
-static void launch_bra(const DirectClassDev *cls, double tau, const double *boys, const double *D, int64_t nao,
-                       const double *Dh, double *Jh, double *K, const double *dsh, int nsh, hipStream_t s)
-{
-    const DirectClassDev &b = cls[LA == 0 ? 0 : (LA == 1 ? 1 + LB : 3 + LB)];
-    if (b.n <= 0) return;
-    if (cls[0].n > 0) launch_quartets<LA, LB, 0, 0>(b, cls[0], tau, boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    if (cls[1].n > 0) launch_quartets<LA, LB, 1, 0>(b, cls[1], tau, boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    if (cls[2].n > 0) launch_quartets<LA, LB, 1, 1>(b, cls[2], tau, boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    if (cls[3].n > 0) launch_quartets<LA, LB, 2, 0>(b, cls[3], tau, boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    if (cls[4].n > 0) launch_quartets<LA, LB, 2, 1>(b, cls[4], tau, boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    if (cls[5].n > 0) launch_quartets<LA, LB, 2, 2>(b, cls[5], tau, boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-}
-
-template <int LA, int LB>
-static void launch_pair_pass(const DirectClassDev &c, const double *D, int64_t nao, double *Dh, const double *Jh,
-                             double *J, bool jout, hipStream_t s)
-{
-    if (c.n <= 0) return;
-    const dim3 grid((unsigned)((c.n + 127) / 128));
-    if (jout) hipLaunchKernelGGL((k_jout<LA, LB>), grid, dim3(128), 0, s, c, Jh, nao, J);
-    else hipLaunchKernelGGL((k_dherm<LA, LB>), grid, dim3(128), 0, s, c, D, nao, Dh);
-}
-
-static void pair_passes(const DirectClassDev *cls, const double *D, int64_t nao, double *Dh, const double *Jh,
-                        double *J, bool jout, hipStream_t s)
-{
-    launch_pair_pass<0, 0>(cls[0], D, nao, Dh, Jh, J, jout, s);
-    launch_pair_pass<1, 0>(cls[1], D, nao, Dh, Jh, J, jout, s);
-    launch_pair_pass<1, 1>(cls[2], D, nao, Dh, Jh, J, jout, s);
-    launch_pair_pass<2, 0>(cls[3], D, nao, Dh, Jh, J, jout, s);
-    launch_pair_pass<2, 1>(cls[4], D, nao, Dh, Jh, J, jout, s);
-    launch_pair_pass<2, 2>(cls[5], D, nao, Dh, Jh, J, jout, s);
+    g.start[6] = total;
+    if (total > 0)
+        hipLaunchKernelGGL(k_pair_pass<JOUT>, dim3(total), dim3(256), 0, s, g, D, nao, Dh, Dhv, Jh, J);
 }
 
 void launch_direct_build(const Plan &p, const DirectLayout &L, const double *C, int32_t nocc, const double *Din,
@@ -567,23 +635,23 @@ void launch_direct_build(const Plan &p, const DirectLayout &L, const double *C, 
         D = dD;
         dsh = tab;
     }
-    const int nsh = p.nsh_ao;
     double *Dh = reinterpret_cast<double *>(scratch + L.o_Dh);
+    double *Dhv = reinterpret_cast<double *>(scratch + L.o_Dhv);
     double *Jh = reinterpret_cast<double *>(scratch + L.o_Jh);
     double *Epart = reinterpret_cast<double *>(scratch + L.o_Epart);
-    dfill(J, nao * nao, s);
-    dfill(K, nao * nao, s);
-    dfill(Jh, ds.herm_total, s);
-    pair_passes(ds.cls, D, nao, Dh, nullptr, nullptr, false, s);
-    const double tau = p.thresh;
-    launch_bra<0, 0>(ds.cls, tau, ds.boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    launch_bra<1, 0>(ds.cls, tau, ds.boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    launch_bra<1, 1>(ds.cls, tau, ds.boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    launch_bra<2, 0>(ds.cls, tau, ds.boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    launch_bra<2, 1>(ds.cls, tau, ds.boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    launch_bra<2, 2>(ds.cls, tau, ds.boys, D, nao, Dh, Jh, K, dsh, nsh, s);
-    pair_passes(ds.cls, D, nao, Dh, Jh, J, true, s);
-    hipLaunchKernelGGL(k_direct_finish, dim3(256), dim3(256), 0, s, nao, ds.fn_shell, Dfull, L.delta ? J0 : nullptr,
+    const int64_t nz = 2 * nao * nao + ds.herm_total;
+    hipLaunchKernelGGL(k_direct_zero, dim3((unsigned)std::min<int64_t>((nz + 1023) / 1024, 4096)), dim3(256), 0, s, J,
+                       K, nao * nao, Jh, ds.herm_total);
+    launch_pair_pass<false>(ds.cls, D, nao, Dh, Dhv, nullptr, nullptr, s);
+    DirectJob g{};
+    for (int k = 0; k < 6; ++k) g.cls[k] = ds.cls[k];
+    g.tau = p.thresh; g.boys = ds.boys; g.D = D; g.nao = nao;
+    g.Dh = Dh; g.Dhv = Dhv; g.Jh = Jh; g.K = K; g.dsh = dsh; g.nsh = p.nsh_ao;
+    launch_group<0>(g, s);
+    launch_group<1>(g, s);
+    launch_group<2>(g, s);
+    launch_pair_pass<true>(ds.cls, nullptr, nao, nullptr, nullptr, Jh, J, s);
+    hipLaunchKernelGGL(k_direct_finish, dim3(256), dim3(256), 0, s, nao, Dfull, L.delta ? J0 : nullptr,
                        L.delta ? K0 : nullptr, J, K, Epart);
     hipLaunchKernelGGL(k_direct_energy, dim3(1), dim3(256), 0, s, Epart, E);
 }

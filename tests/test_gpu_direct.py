@@ -260,3 +260,33 @@ def test_direct_errors():
     with pytest.raises(ValueError):
         plan.direct_build(C=np.zeros((mol.nao + 1, 2)))
     plan.close()
+
+
+@pytest.mark.parametrize("n", [35, 69, 86, 171])
+def test_direct_row_routes(n):
+    """Sizes at which the K and D rows of a pair stop fitting LDS, for each launch:
+    K alone in LDS for the heavy classes (35 waters, 1,050 AO), nothing (69), K alone
+    for the other two launches (69, 86) and nothing (171).  Three close waters
+    and n - 3 far ones, 40 bohr apart, whose part of D is zero: the near block of J and K is
+    that of the three alone, and K has no other entry (no pair joins near and far)."""
+    z, x = W.water_cluster(3, W.cluster_box(3), 1)
+    z1, x1 = W.water_monomer()
+    zs, xs = [z], [x]
+    for i in range(n - 3):
+        zs.append(z1)
+        xs.append(x1 + np.array([40.0 * (1 + i % 6), 40.0 * (1 + (i // 6) % 6), 40.0 * (1 + i // 36)]))
+    near = W.make_molecule(z, x)
+    mol = W.make_molecule(np.concatenate(zs), np.concatenate(xs))
+    C = W.occupied_orbitals(W.overlap_by_quadrature(near), near.nelec // 2, 1)
+    Dn = oracle.density(C)
+    Jr, Kr, EJr, EKr = oracle.exact_jk(near, Dn)
+    m = near.nao
+    D = np.zeros((mol.nao, mol.nao))
+    D[:m, :m] = Dn
+    plan = _plan(mol)
+    J, K, E = _np(*plan.direct_build(D=D))
+    assert np.abs(J[:m, :m] - Jr).max() <= TOL * np.abs(Jr).max()
+    assert np.abs(K[:m, :m] - Kr).max() <= TOL * np.abs(Kr).max()
+    assert abs(E[0] - EJr) <= TOL * abs(EJr) and abs(E[1] - EKr) <= TOL * abs(EKr)
+    assert not K[m:].any() and not K[:, m:].any()
+    plan.close()
