@@ -709,7 +709,8 @@ static int setup(Plan &p, void *ws, size_t bytes, hipStream_t s)
     // stream beside the metric and its factor (a chain of small,
     // latency-bound launches); the inverse follows them there, each block
     // row of L^{-1} as soon as its factor step is done, and the side stream
-    // is joined before the whitening.
+    // is joined before the whitening.  The chain is the longer of the two for a
+    // small molecule, so its first steps are enqueued before the integrals' launches.
     Profiler &pr = p.prof;
     pr.stream = s;
     pr.mark(ST_SETUP, true);
@@ -719,14 +720,16 @@ static int setup(Plan &p, void *ws, size_t bytes, hipStream_t s)
         HIP_OR_FAIL(hipEventRecord(p.ev_jfork, s));
         HIP_OR_FAIL(hipStreamWaitEvent(is, p.ev_jfork, 0));
     }
-    pr.stream = is;
-    pr.mark(ST_INT3C, true);
-    zero_u_pads(p, is);
-    launch_pair_records(p, is);
-    launch_int3c(p, is);
-    pr.mark(ST_INT3C, false);
-    trtri_begin(d.Linv, p.naux_pad, is);
-    pr.stream = s;
+    auto integrals = [&] {
+        pr.stream = is;
+        pr.mark(ST_INT3C, true);
+        zero_u_pads(p, is);
+        launch_pair_records(p, is);
+        launch_int3c(p, is);
+        pr.mark(ST_INT3C, false);
+        pr.stream = s;
+    };
+    if (!side) integrals();
     pr.mark(ST_METRIC, true);
     launch_metric_pad(d.V, p.naux, p.naux_pad, s);
     launch_int2c(p, s);
@@ -736,12 +739,19 @@ static int setup(Plan &p, void *ws, size_t bytes, hipStream_t s)
     // which read only what the factor steps up to theirs wrote; handed over
     // kInvGroup steps at a time (fewer cross-stream events).  The stage of the
     // inverse is then the span of its steps, beside the factor.
+    // Up to kInvGroup * 2 steps (512 auxiliary functions) the integrals end last, and
+    // the inverse follows the factor on s.
     constexpr int64_t kInvGroup = 4;
     const int64_t nblk = p.naux_pad / 64;
+    const bool inv_on_s = !side || nblk <= 2 * kInvGroup;
     pr.mark(ST_CHOL, true);
     for (int64_t k = 0, done = 0; k < nblk; ++k) {
         cholesky_step(d.L, p.naux_pad, k, d.status, d.Dinv, s);
-        if (!side || ((k + 1) % kInvGroup != 0 && k + 1 != nblk)) continue;
+        if (inv_on_s || ((k + 1) % kInvGroup != 0 && k + 1 != nblk)) continue;
+        if (done == 0) {
+            integrals();
+            trtri_begin(d.Linv, p.naux_pad, is);
+        }
         HIP_OR_FAIL(hipEventRecord(p.ev_jfork, s));
         HIP_OR_FAIL(hipStreamWaitEvent(is, p.ev_jfork, 0));
         pr.stream = is;
@@ -751,16 +761,20 @@ static int setup(Plan &p, void *ws, size_t bytes, hipStream_t s)
     }
     launch_zero_upper(d.L, p.naux_pad, s);
     pr.mark(ST_CHOL, false);
-    if (side) {
+    if (inv_on_s) {
+        if (side) integrals();
+        pr.mark(ST_TRTRI, true);
+        trtri_begin(d.Linv, p.naux_pad, s);
+        for (int64_t k = 0; k < nblk; ++k) trtri_step(d.L, d.Linv, d.Dinv, p.naux_pad, k, s);
+        pr.mark(ST_TRTRI, false);
+    } else {
         pr.stream = is;
         pr.mark(ST_TRTRI, false);
         pr.stream = s;
+    }
+    if (side) {
         HIP_OR_FAIL(hipEventRecord(p.ev_jdone, is));
         HIP_OR_FAIL(hipStreamWaitEvent(s, p.ev_jdone, 0));
-    } else {
-        pr.mark(ST_TRTRI, true);
-        for (int64_t k = 0; k < nblk; ++k) trtri_step(d.L, d.Linv, d.Dinv, p.naux_pad, k, s);
-        pr.mark(ST_TRTRI, false);
     }
     pr.mark(ST_WHITEN, true);
     launch_whiten(d.U, d.Linv, d.B, p.nf_pad, p.naux_pad, s);

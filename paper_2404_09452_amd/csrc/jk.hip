@@ -13,7 +13,7 @@
 //   6. E_J = 1/2 sum_P c_P^2 (= 1/2 Tr DJ), E_K = -1/4 sum D K
 // No floating-point atomics anywhere, so results are bitwise reproducible.
 #include "dfjk_internal.h"
-#include "gemm_f64.h"
+#include "mfma_f64.h"
 
 #include <algorithm>
 

@@ -441,19 +441,23 @@ void launch_syrk_f64_group(int T, int n, const double *const *A, const int64_t *
 
 // C = A B^T with B lower triangular in (n, k) (B(n, k) = 0 for k > n), both
 // row-major over ld = k: the whitening B_fP = sum_{Q <= P} U_fQ Linv_PQ.  M
-// rows of A, N rows of B (a multiple of 128), 128-wide tiles, no split.
+// rows of A, N rows of B (a multiple of 128), no split.  128-wide tiles, 64-wide
+// ones where those would be fewer than four a CU (4 waters: 228 workgroups whose k
+// differs threefold take 54 us, 912 small ones 27).
 void launch_gemm_nt_tri(const double *A, const double *B, double *C, int64_t M, int64_t N, int64_t ld,
                         hipStream_t s)
 {
     SyrkArgs g{};
     g.A = A; g.B = B; g.ld = ld; g.M = M; g.N = N; g.kdim = ld; g.ksplit = g.ksub = ld; g.nsub = 1;
-    g.ntm = (int)((M + 127) / 128);
-    g.ntn = (int)((N + 127) / 128);
+    const int T = ((M + 127) / 128) * (N / 128) < 1024 ? 64 : 128;
+    g.ntm = (int)((M + T - 1) / T);
+    g.ntn = (int)((N + T - 1) / T);
     g.lower = 0; g.tri_k = 1; g.nsplit = 1;
     g.C = C; g.ldc = ld;
     const int ntiles = g.ntm * g.ntn;
     if (ntiles <= 0) return;
-    launch_tiles<double, 128>(g, (unsigned)ntiles, s);
+    if (T == 64) launch_tiles<double, 64>(g, (unsigned)ntiles, s);
+    else launch_tiles<double, 128>(g, (unsigned)ntiles, s);
 }
 
 }  // namespace dfjk

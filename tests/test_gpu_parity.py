@@ -76,6 +76,25 @@ def test_metric_and_cholesky_water(water1):
     assert rel(L, Lref) <= 1e-11
 
 
+@pytest.mark.parametrize("n", [5, 6, 9])
+def test_setup_chain_sizes(n):
+    """The factor, its inverse and the whitening at the sizes where their schedule changes:
+    5 waters (8 blocks of 64 aux functions: the inverse follows the factor on the caller's
+    stream), 6 (10 blocks: beside it on the side stream) and 9 (128-wide whitening tiles
+    instead of 64-wide): L L^T = V and L B = U, with the tolerances of the monomer."""
+    z, x = W.water_cluster(n, W.cluster_box(n), 1)
+    plan = G.Plan.from_molecule(W.make_molecule(z, x), schwarz_thresh=TAU).screen().setup()
+    order = torch.as_tensor(plan.aux_order().astype(np.int64))
+    V = plan.export(G.EXPORT_METRIC).cpu()[order][:, order].numpy()
+    L = plan.export(G.EXPORT_CHOL).cpu().numpy()
+    assert not np.triu(L, 1).any()
+    assert rel(L, np.linalg.cholesky(V)) <= 1e-11
+    U = plan.export(G.EXPORT_INT3C).cpu()[order].numpy().reshape(len(order), -1)
+    B = plan.export(G.EXPORT_B).cpu().numpy().reshape(len(order), -1)
+    assert rel(L @ B, U) <= 1e-11
+    plan.close()
+
+
 def test_whitened_water(water1):
     """B = L^{-1} U depends on the aux order through L: compare against the
     oracle's whitening of the metric permuted into the library's order."""
