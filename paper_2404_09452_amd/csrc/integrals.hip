@@ -185,10 +185,10 @@ __device__ __forceinline__ double schwarz_form(const double (&Es)[nherm(LAB)], d
     return sqrt(fabs(s) * pref);
 }
 
-// Largest sqrt|(ab|ab)| over the function pairs of one shell pair (classes
-// below (d d)): the Hermite tables once, then each function pair's bra.
+// Largest sqrt|(ab|ab)| over function pairs k, k + step, ... of one shell pair
+// (classes below (d d)): the Hermite tables once, then each function pair's bra.
 template <int LA, int LB>
-__device__ double schwarz_pair_max(double ea, double eb, double ax_, double ay_, double az_, double bx_, double by_,
+__device__ double schwarz_pair_max(int first, int step, double ea, double eb, double ax_, double ay_, double az_, double bx_, double by_,
                                    double bz_, double na, double nb)
 {
     constexpr int LAB = LA + LB, NB = 2 * LB + 1;
@@ -202,7 +202,7 @@ __device__ double schwarz_pair_max(double ea, double eb, double ax_, double ay_,
     hermite_E<LA, LB>(Pz - az_, Pz - bz_, 0.5 * ip, exp(-mu * (az_ - bz_) * (az_ - bz_)), Ez);
     double best = 0.0;
 #pragma unroll 1
-    for (int k = 0; k < (2 * LA + 1) * NB; ++k) {
+    for (int k = first; k < (2 * LA + 1) * NB; k += step) {
         double Es[nherm(LAB)];
         bra_sph<LA, LB>(k / NB, k % NB, Ex, Ey, Ez, Es);
         best = fmax(best, schwarz_form<LAB>(Es, p, na, nb));
@@ -211,12 +211,12 @@ __device__ double schwarz_pair_max(double ea, double eb, double ax_, double ay_,
 }
 
 // Schwarz factor of every shell pair a >= b other than (d d): the largest
-// (ab|ab) over its function pairs, one thread per pair; (d d) pairs get 0
-// here and their value from k_schwarz_dd.
-__global__ __launch_bounds__(256) void k_schwarz_pairs(int64_t npair, ShellsDev ao, double *__restrict__ q)
+// (ab|ab) over its function pairs, PL lanes per pair.
+template <int PL>
+__device__ void schwarz_pairs(int64_t gid, int64_t npair, const ShellsDev &ao, double *__restrict__ q)
 {
-    const int64_t ab = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (ab >= npair) return;
+    const int64_t ab = min(gid / PL, npair - 1);
+    const int k = (int)(gid % PL);
     int a = (int)((sqrt(8.0 * (double)ab + 1.0) - 1.0) * 0.5);
     while ((int64_t)a * (a + 1) / 2 > ab) --a;
     while ((int64_t)(a + 1) * (a + 2) / 2 <= ab) ++a;
@@ -224,29 +224,28 @@ __global__ __launch_bounds__(256) void k_schwarz_pairs(int64_t npair, ShellsDev 
     if (ao.l[a] < ao.l[b]) { const int t = a; a = b; b = t; }
     const int la = ao.l[a], lb = ao.l[b];
     double r = 0.0;
-#define SCH(LA, LB)                                                                                   \
-    r = schwarz_pair_max<LA, LB>(ao.exp[a], ao.exp[b], ao.x[a], ao.y[a], ao.z[a], ao.x[b], ao.y[b], \
+#define SCH(LA, LB)                                                                                              \
+    r = schwarz_pair_max<LA, LB>(k, PL, ao.exp[a], ao.exp[b], ao.x[a], ao.y[a], ao.z[a], ao.x[b], ao.y[b], \
                                  ao.z[b], ao.norm[a], ao.norm[b]);
     if (la == 0) { SCH(0, 0) }
     else if (la == 1) { if (lb == 0) { SCH(1, 0) } else { SCH(1, 1) } }
     else if (lb == 0) { SCH(2, 0) }
     else if (lb == 1) { SCH(2, 1) }
 #undef SCH
-    q[ab] = r;
+#pragma unroll
+    for (int w = PL / 2; w > 0; w >>= 1) r = fmax(r, __shfl_xor(r, w));
+    if (k == 0 && gid / PL < npair && !(la == 2 && lb == 2)) q[ab] = r;
 }
 
 // (d d) pairs: pair (i >= j) of the ascending d-shell list dsh, 32 lanes per
 // pair, lane k < 25 taking function pair k.  Lane 0 forms the three Hermite
-// tables into LDS, each lane builds its bra from them, and the largest value
-// is kept with an integer maximum on the bits (non-negative values order as
-// their bit patterns do) in q, which k_schwarz_pairs has set to 0.
-__global__ __launch_bounds__(256) void k_schwarz_dd(int64_t ndd, const int32_t *__restrict__ dsh, ShellsDev ao,
-                                                    double *__restrict__ q)
+// tables into LDS, each lane builds its bra from them (lanes beyond the 25th
+// repeat it), and lane 0 writes the largest.
+__device__ void schwarz_dd(int64_t gid, int64_t ndd, const int32_t *__restrict__ dsh, const ShellsDev &ao,
+                           double *__restrict__ q)
 {
-    const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t ij = gid >> 5;
-    const int k = (int)(gid & 31);
-    if (ij >= ndd || k >= 25) return;
+    const int64_t ij = min(gid >> 5, ndd - 1);
+    const int k = min((int)(gid & 31), 24);
     int i = (int)((sqrt(8.0 * (double)ij + 1.0) - 1.0) * 0.5);
     while ((int64_t)i * (i + 1) / 2 > ij) --i;
     while ((int64_t)(i + 1) * (i + 2) / 2 <= ij) ++i;
@@ -297,19 +296,10 @@ __global__ __launch_bounds__(256) void k_schwarz_dd(int64_t ndd, const int32_t *
                 }
         }
     }
-    const double r = schwarz_form<4>(Es, p, ao.norm[a], ao.norm[b]);
-    const int64_t ab = (int64_t)a * (a + 1) / 2 + b;
-    atomicMax(reinterpret_cast<unsigned long long *>(q) + ab, (unsigned long long)__double_as_longlong(r));
-}
-
-// dsh: the nd d shells in ascending order (device memory)
-void launch_schwarz_pairs(int64_t npair, const ShellsDev &ao, const int32_t *dsh, int32_t nd, double *q,
-                          hipStream_t s)
-{
-    hipLaunchKernelGGL(k_schwarz_pairs, dim3((unsigned)((npair + 255) / 256)), dim3(256), 0, s, npair, ao, q);
-    const int64_t ndd = (int64_t)nd * (nd + 1) / 2;
-    if (ndd > 0)
-        hipLaunchKernelGGL(k_schwarz_dd, dim3((unsigned)((ndd * 32 + 255) / 256)), dim3(256), 0, s, ndd, dsh, ao, q);
+    double r = schwarz_form<4>(Es, p, ao.norm[a], ao.norm[b]);
+#pragma unroll
+    for (int w = 16; w > 0; w >>= 1) r = fmax(r, __shfl_xor(r, w));
+    if ((gid & 31) == 0 && gid >> 5 < ndd) q[(int64_t)a * (a + 1) / 2 + b] = r;
 }
 
 // (c|c) of one solid-harmonic Gaussian, largest over m (all equal in exact
@@ -340,9 +330,8 @@ __device__ double schwarz_aux(double g, double nc)
     return sqrt(best);
 }
 
-__global__ void k_schwarz_aux(int32_t nsh, ShellsDev ax, double *__restrict__ q)
+__device__ void schwarz_aux_shell(int64_t c, int32_t nsh, const ShellsDev &ax, double *__restrict__ q)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= nsh) return;
     const double g = ax.exp[c], nc = ax.norm[c];
     double r;
@@ -355,10 +344,38 @@ __global__ void k_schwarz_aux(int32_t nsh, ShellsDev ax, double *__restrict__ q)
     q[c] = r;
 }
 
-void launch_schwarz_aux(int32_t nsh, const ShellsDev &ax, double *q, hipStream_t s)
+// All Schwarz factors in one launch: workgroups [0, wdd) the (d d) pairs, [wdd, wdd + wax)
+// the aux shells, the rest the other pairs.  Each part is one latency-bound chain;
+// one after the other they took 55 us on 4 waters, and the pairs alone 40 with a
+// lane a pair (up to 15 function pairs in turn, the classes of a wave one after
+// the other).
+template <int PL>
+__global__ __launch_bounds__(256) void k_schwarz(uint32_t wdd, uint32_t wax, int64_t ndd, int64_t npair, int32_t naux,
+                                                 const int32_t *__restrict__ dsh, ShellsDev ao, ShellsDev ax,
+                                                 double *__restrict__ qp, double *__restrict__ qa)
 {
-    const int bs = 128;
-    hipLaunchKernelGGL(k_schwarz_aux, dim3((nsh + bs - 1) / bs), dim3(bs), 0, s, nsh, ax, q);
+    const uint32_t b = blockIdx.x;
+    if (b < wdd) schwarz_dd(b * (int64_t)256 + threadIdx.x, ndd, dsh, ao, qp);
+    else if (b < wdd + wax) schwarz_aux_shell((b - wdd) * (int64_t)256 + threadIdx.x, naux, ax, qa);
+    else schwarz_pairs<PL>((b - wdd - wax) * (int64_t)256 + threadIdx.x, npair, ao, qp);
+}
+
+// dsh: the nd d shells in ascending order (device memory).  16 lanes a pair while
+// they all fit on the chip at once (2,048 waves of 4 pairs a round): 8 us instead of 40 for
+// the 2,080 pairs of 4 waters, but 108 instead of 70 for the 131,328 of 32.
+void launch_schwarz(int64_t npair, const ShellsDev &ao, const int32_t *dsh, int32_t nd, int32_t naux,
+                    const ShellsDev &ax, double *qp, double *qa, hipStream_t s)
+{
+    const int64_t ndd = (int64_t)nd * (nd + 1) / 2;
+    const uint32_t wdd = (uint32_t)((ndd * 32 + 255) / 256), wax = (uint32_t)((naux + 255) / 256);
+    const bool wide = npair <= 32768;
+    const uint32_t wpair = (uint32_t)((npair * (wide ? 16 : 1) + 255) / 256);
+    if (wide)
+        hipLaunchKernelGGL(k_schwarz<16>, dim3(wdd + wax + wpair), dim3(256), 0, s, wdd, wax, ndd, npair, naux, dsh, ao,
+                           ax, qp, qa);
+    else
+        hipLaunchKernelGGL(k_schwarz<1>, dim3(wdd + wax + wpair), dim3(256), 0, s, wdd, wax, ndd, npair, naux, dsh, ao,
+                           ax, qp, qa);
 }
 
 // --------------------------------------------------------------------------
