@@ -382,7 +382,7 @@ void launch_schwarz(int64_t npair, const ShellsDev &ao, const int32_t *dsh, int3
 // Three-centre integrals.
 //
 // Work split.  Everything that depends only on the shell pair (a, b) is formed
-// once per pair by k_pair_rec: the Gaussian product p, P and the spherical bra
+// once per pair by k_pair_rec_all: the Gaussian product p, P and the spherical bra
 // Hermite coefficients
 //   Eh[tuv][ab] = 2 pi^{5/2} N_a N_b / p * t! u! v! * sum_{ca,cb} s_a s_b E^x E^y E^z.
 // k_int3c then gives each lane one output column, an (aux shell c, m_c)
@@ -483,12 +483,6 @@ __device__ __forceinline__ void pair_rec(const Int3cArgs &g, double *__restrict_
 #pragma unroll
             for (int v = 0; v + u + t <= LAB; ++v)
                 r[8 + hidx(t, u, v) * NAB + ab] = pref * (kFact[t] * kFact[u] * kFact[v]) * Es[hidx(t, u, v)];
-}
-
-template <int LA, int LB>
-__global__ __launch_bounds__(256) void k_pair_rec(Int3cArgs g, double *__restrict__ rec)
-{
-    pair_rec<LA, LB>(g, rec, blockIdx.x * (int64_t)blockDim.x + threadIdx.x);
 }
 
 // The pair records of one class for several molecules in one launch
@@ -694,15 +688,6 @@ __global__ __launch_bounds__(256) void k_int3c_sh(Int3cArgs g)
     int3c_shells<LA, LB, LC>(g, blockIdx.x, buf);
 }
 
-template <int LA, int LB>
-static void launch_pair_class(Int3cArgs g, double *rec, hipStream_t s)
-{
-    constexpr int NAB = (2 * LA + 1) * (2 * LB + 1);
-    const int64_t n = (int64_t)(g.p_end - g.p_begin) * NAB;
-    if (n <= 0) return;
-    hipLaunchKernelGGL((k_pair_rec<LA, LB>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g, rec);
-}
-
 // Lane per aux shell while the outputs of a triplet, (2la+1)(2lb+1)(2lc+1),
 // fit in registers beside the tables and the wave's pass over the pair record
 // per m_c stays short; lane per (aux shell, m_c) otherwise (chosen per class
@@ -815,24 +800,48 @@ static Int3cArgs int3c_args(const Plan &p)
     return g;
 }
 
+#define PAIR_CLASSES(X) X(0, 0, 0) X(1, 1, 0) X(2, 1, 1) X(3, 2, 0) X(4, 2, 1) X(5, 2, 2)
+
+// Records of all classes in one launch: workgroup b belongs to class k for
+// start[k] <= b < start[k + 1].  Each is a few microseconds at any size.
+struct PairRecAll {
+    Int3cArgs g;
+    int32_t begin[6], end[6];
+    uint32_t start[7];
+    double *rec[6];
+};
+
+__global__ __launch_bounds__(256) void k_pair_rec_all(PairRecAll r)
+{
+    int k = 0;
+    while (k < 5 && blockIdx.x >= r.start[k + 1]) ++k;
+    Int3cArgs g = r.g;
+    g.p_begin = r.begin[k]; g.p_end = r.end[k];
+    const int64_t tid = (blockIdx.x - r.start[k]) * (int64_t)256 + threadIdx.x;
+    switch (k) {
+#define REC(K, A, B) case K: pair_rec<A, B>(g, r.rec[K], tid); break;
+        PAIR_CLASSES(REC)
+#undef REC
+    }
+}
+
 // Records of every kept pair into p.d.pair_rec (before any int3c launch).
 void launch_pair_records(const Plan &p, hipStream_t s)
 {
     int64_t off[7];
     pair_rec_offsets(p, off);
-    Int3cArgs g = int3c_args(p);
+    PairRecAll r{};
+    r.g = int3c_args(p);
+    uint32_t total = 0;
     for (int pc = 0; pc < 6; ++pc) {
-        g.p_begin = p.sp_class[pc].begin; g.p_end = p.sp_class[pc].end;
-        double *rec = p.d.pair_rec + off[pc];
-        switch (pc) {
-        case 0: launch_pair_class<0, 0>(g, rec, s); break;
-        case 1: launch_pair_class<1, 0>(g, rec, s); break;
-        case 2: launch_pair_class<1, 1>(g, rec, s); break;
-        case 3: launch_pair_class<2, 0>(g, rec, s); break;
-        case 4: launch_pair_class<2, 1>(g, rec, s); break;
-        default: launch_pair_class<2, 2>(g, rec, s); break;
-        }
+        const int nab = (2 * kPairClassLa[pc] + 1) * (2 * kPairClassLb[pc] + 1);
+        r.begin[pc] = p.sp_class[pc].begin; r.end[pc] = p.sp_class[pc].end;
+        r.rec[pc] = p.d.pair_rec + off[pc];
+        r.start[pc] = total;
+        total += (uint32_t)(((int64_t)(r.end[pc] - r.begin[pc]) * nab + 255) / 256);
     }
+    r.start[6] = total;
+    if (total > 0) hipLaunchKernelGGL(k_pair_rec_all, dim3(total), dim3(256), 0, s, r);
 }
 
 template <int LA, int LB>
@@ -889,8 +898,80 @@ void launch_pair_records_plans(const Plan *const *plans, int n, hipStream_t s)
     }
 }
 
+#define AUX_CLASSES(X, K, A, B) X(K, A, B, 0) X(K, A, B, 1) X(K, A, B, 2) X(K, A, B, 3)
+#define TRIPLET_CLASSES(X) \
+    AUX_CLASSES(X, 0, 0, 0) AUX_CLASSES(X, 1, 1, 0) AUX_CLASSES(X, 2, 1, 1) \
+    AUX_CLASSES(X, 3, 2, 0) AUX_CLASSES(X, 4, 2, 1) AUX_CLASSES(X, 5, 2, 2)
+
+// All 24 triplet classes of a small molecule in one launch, heaviest pair class first:
+// workgroup b belongs to class k = 4 (5 - pair class) + lc for start[k] <= b < start[k + 1].
+struct Int3cAll {
+    Int3cArgs g;
+    int32_t p_begin[6], p_end[6], c_begin[4], c_end[4];
+    uint32_t start[25];
+    const double *rec[6];
+};
+
+__global__ __launch_bounds__(256, 2) void k_int3c_all(Int3cAll r)
+{
+    __shared__ double buf[4 * 64 * (2 * kMaxLAux + 1)];
+    int k = 0;
+    while (k < 23 && blockIdx.x >= r.start[k + 1]) ++k;
+    const unsigned blk = blockIdx.x - r.start[k];
+    const int pc = 5 - k / 4, lc = k % 4;
+    Int3cArgs g = r.g;
+    g.p_begin = g.rec_first = r.p_begin[pc]; g.p_end = r.p_end[pc];
+    g.c_begin = r.c_begin[lc]; g.c_end = r.c_end[lc];
+    g.rec = r.rec[pc];
+    switch (k) {
+#define TRI(K, A, B, C)                                                              \
+    case 4 * (5 - K) + C:                                                            \
+        if constexpr (shell_lanes_for(A, B, C)) int3c_shells<A, B, C>(g, blk, buf);  \
+        else int3c_cols<A, B, C>(g, blk);                                            \
+        break;
+        TRIPLET_CLASSES(TRI)
+#undef TRI
+    }
+}
+
+// The merged launch, for up to 8,192 workgroups; false beyond.  It needs the registers
+// of the largest class (two workgroups a CU), but it is one launch of 32 us for
+// 4 waters (4,000 workgroups) where the 24 take 190 in turn.  Whole setups, merged against
+// separate: one water 215 and 365 us, 2: 326 and 420, 4: 415 and 452, 6 (9,100): 575 and
+// 580, 12: 1,240 and 1,200.
+static bool launch_int3c_small(const Plan &p, hipStream_t s)
+{
+    int64_t off[7];
+    pair_rec_offsets(p, off);
+    Int3cAll r{};
+    r.g = int3c_args(p);
+    r.g.U = p.d.U;
+    for (int pc = 0; pc < 6; ++pc) {
+        r.p_begin[pc] = p.sp_class[pc].begin; r.p_end[pc] = p.sp_class[pc].end;
+        r.rec[pc] = p.d.pair_rec + off[pc];
+    }
+    for (int lc = 0; lc <= kMaxLAux; ++lc) { r.c_begin[lc] = p.ax_class[lc].begin; r.c_end[lc] = p.ax_class[lc].end; }
+    int64_t nb[24], total = 0;
+    Int3cArgs g = r.g;
+#define COUNT(K, A, B, C)                                  \
+    g.p_begin = r.p_begin[K]; g.p_end = r.p_end[K];        \
+    g.c_begin = r.c_begin[C]; g.c_end = r.c_end[C];        \
+    nb[4 * (5 - K) + C] = class_blocks<A, B, C>(g);
+    TRIPLET_CLASSES(COUNT)
+#undef COUNT
+    for (int k = 0; k < 24; ++k) {
+        r.start[k] = (uint32_t)total;
+        total += nb[k];
+        if (total > 8192) return false;
+    }
+    r.start[24] = (uint32_t)total;
+    if (total > 0) hipLaunchKernelGGL(k_int3c_all, dim3((unsigned)total), dim3(256), 0, s, r);
+    return true;
+}
+
 void launch_int3c(const Plan &p, hipStream_t s)
 {
+    if (launch_int3c_small(p, s)) return;
     launch_int3c_rows(p, p.d.U, 0, 0, (int32_t)p.sp_a.size(), s);
 }
 
