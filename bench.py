@@ -809,7 +809,7 @@ def main():
     k_launches = f64["stage_launches"]["build.K"] / (args.steps * NBUILDS)
     k_ms = f64["stages_ms_per_launch"]["build.K"]
     achieved = k_flops / k_launches / (k_ms * 1e-3) / 1e12
-    roofline = {"kernel": "build.K (FP64 MFMA X X^T, k_syrk_f64<%d>, %d splits)" % (shape["k_tile"], shape["nsplit"]),
+    roofline = {"kernel": "build.K (FP64 MFMA X X^T, k_syrk<double, %d>, %d splits)" % (shape["k_tile"], shape["nsplit"]),
                 "bound": "mfma",
                 "achieved": round(achieved, 3), "peak": PEAK_F64_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_F64_TFLOPS, 4), "traffic": committed_traffic(shape),

@@ -108,9 +108,10 @@ typedef struct {
                                     Negative values are DFJK_INVALID.         */
     int32_t k_tile;              /* output tile of the FP64 K contraction
                                     (syrk): 0 = dfjk_autotune's choice for the
-                                    shape, else 64 where 128-wide tiles would
-                                    execute over 14% more products (ragged
-                                    nao), else 128; 64, 96 or 128 = that
+                                    shape, else the width that executes the
+                                    fewest products at the rate it reaches
+                                    (64 up to 1,440 AO mostly, else 96 or
+                                    128); 64, 96 or 128 = that
                                     tile for every FP64 syrk of the plan.
                                     Other values are DFJK_E_INVALID.          */
 } dfjk_options;
@@ -289,9 +290,9 @@ int dfjk_build_batch(int32_t n, dfjk_plan *const *plans, const double *const *d_
 /* Autotuner for the K contraction of the closed-shell C-route build
  * (dfjk_build with d_C, this nocc and precision): its tile shape and split
  * count.  Candidates are half, one, two and four times the built-in split
- * count (within the contraction length) of the 128-wide output tiles and,
- * for FP64, of 64-wide tiles (which leave less of the syrk's work above the
- * diagonal or past nao).  Each runs one warm-up and three timed builds with
+ * count (within the contraction length) of the 128-wide output tiles, for
+ * FP64 and FP32 of 64- and 96-wide and for int8_fast of 64-wide tiles too (which
+ * leave less of the syrk's work above the diagonal or past nao).  Each runs one warm-up and three timed builds with
  * d_C on `stream` (HIP events; synchronises the stream), and the fastest is
  * kept in the plan for later builds of that shape.  Tile and split count
  * only reorder the FP64 sums of the split-K reduction, which stays fixed and
@@ -333,7 +334,7 @@ int dfjk_build_checked(dfjk_plan *plan, const double *d_C, int32_t nocc, double 
 
 /* The launch shape a closed-shell C-route dfjk_build with this nocc and
  * precision will use (after dfjk_screen; the autotuner's or dfjk_options'
- * choice included): shape[0] the K output tile (64 or 128), shape[1] the
+ * choice included): shape[0] the K output tile (64, 96 or 128), shape[1] the
  * split count of the K contraction, shape[2] aux functions per slab,
  * shape[3] the number of slabs.  shape is a host array of 4.  For profiling
  * and reporting; no device work. */

@@ -1812,10 +1812,9 @@ int dfjk_offload(dfjk_plan *plan, void *h_pinned, size_t host_bytes, void *d_tab
     return DFJK_OK;
 }
 
-// Candidate split counts of the K contraction around the built-in choice.
 // Autotuner candidates: (K GEMM tile, split count).  Split counts are half,
-// one, two and four times the built-in choice of each tile; the FP64 syrk
-// also tries 64-wide tiles (written into the 128-wide partials), which leave
+// one, two and four times the built-in choice of each tile; the FP64 and FP32 syrk
+// also try 64- and 96-wide tiles and int8_fast 64-wide ones, which leave
 // less of the work above the diagonal or past nao.  A candidate is encoded
 // as 1000 * tile + split count.
 static std::vector<int> autotune_candidates(const Plan &p, int32_t nocc, int32_t precision)
