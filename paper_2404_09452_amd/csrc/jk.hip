@@ -1071,15 +1071,19 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     L.j_side = allow_overlap && !p.host_B;
     L.kdim = x_kdim(precision, slab, L.ncol);
     const int ntiles = delta ? L.ntile * L.ntile : L.ntile * (L.ntile + 1) / 2;
-    // FP64 and FP32 syrk: enough splits for 32 workgroups per CU with 64- and
-    // 96-wide tiles and 16 with 128-wide ones (FP64, 960 AO on 64-wide tiles, 64 /
-    // 136 / 272 splits: 6.14 / 6.19 / 6.23 ms; 1,920 AO on 96-wide, 16 / 32 / 72: 89.9 /
-    // 85.4 / 84.1 ms; 3,840 AO on 128-wide, 4 / 8 / 16: 179 / 168 / 168 ms).  A
+    // FP64 and FP32 syrk: enough splits for 32 workgroups per CU with 96-wide tiles, 64
+    // with 64-wide ones (32 in FP64 up to 640 AO, where more lengthen the reduction by as much)
+    // and 16 with 128-wide ones.  Whole builds, ms: 64-wide 600 AO 144 / 288 splits 1.90 /
+    // 1.93, 840 AO 72 / 144 6.62 / 6.35, 960 AO 64 / 128 9.24 / 9.13, 1,080 AO 48 / 96 16.05 /
+    // 15.84; 96-wide 960 AO 72 / 144 / 288 9.13 / 8.92 / 9.08; K alone: 1,920 AO on 96-wide,
+    // 16 / 32 / 72 89.9 / 85.4 / 84.1; 3,840 AO on 128-wide, 4 / 8 / 16 179 / 168 / 168.  A
     // split count of 8 or more is rounded down to a multiple of the XCD count,
     // so that the syrk runs whole splits per XCD.  In FP32 they are parts of the
     // mixed_nsplit ranges in which the FP32 sums fold.
     const int many = xcd_round(choose_ksplit(ntiles, L.kdim, p.num_cus,
-                                             L.ktile == kTileK ? 16 : precision == DFJK_FP64 && !fixed ? 32 : 64,
+                                             L.ktile == kTileK ? 16
+                                             : precision == DFJK_FP64 && !fixed && (L.ktile == 96 || p.nao <= 640) ? 32
+                                                                                                                   : 64,
                                              !fixed));
     L.nsub = 1;
     if (precision == DFJK_FP64) {
