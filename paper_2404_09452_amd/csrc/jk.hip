@@ -955,7 +955,10 @@ __global__ __launch_bounds__(256) void k_energies_grouped(EnergyGroup grp, doubl
 // chip; at least 256 k values per split.  short_k: 512 where that still gives eight
 // workgroups per CU (390 AO x 74,880 k, 144 / 288 splits: 0.279 / 0.282 ms, and the
 // reduction reads half the partial tiles: 39 -> 20 us), 128 where 256 leaves fewer
-// than four (30 AO x 640 k, 2 / 5 splits: 15.8 / 7.9 us).
+// than four (30 AO x 640 k, 2 / 5 splits: 15.8 / 7.9 us).  The increment takes no
+// splits below 256 k: its reduction reads both triangles of every split, one of them
+// across rows (whole increments of 150 / 210 AO with and without: 0.72 and 0.63, 1.44 and
+// 1.12 ms; the split of 480 AO at 512 k gains, 4.41 -> 4.13).
 int mixed_nsplit(int64_t nao, int64_t kdim, bool lower, int num_cus);
 int i8_fast_tile(int64_t nao);
 int i8_nsplit(int64_t nao, int64_t kdim, bool lower, int tile, int num_cus);
@@ -965,7 +968,7 @@ void launch_gemm_i8_group(bool fast, int tile, int n, const void *const *X, cons
                           const int64_t *nao, const int64_t *kdim, const int *nsplit, double *const *part,
                           hipStream_t s);
 
-static int choose_ksplit(int ntiles, int64_t kdim, int num_cus, int per_cu, bool short_k)
+static int choose_ksplit(int ntiles, int64_t kdim, int num_cus, int per_cu, bool short_k, bool delta)
 {
     const int slots = per_cu * (num_cus > 0 ? num_cus : 256);
     int ns = ntiles >= slots ? 1 : slots / ntiles;
@@ -973,7 +976,7 @@ static int choose_ksplit(int ntiles, int64_t kdim, int num_cus, int per_cu, bool
     int64_t maxs = kdim / 256;
     if (short_k) {
         if (ntiles * (kdim / 512) >= 8 * cus) maxs = kdim / 512;
-        else maxs = std::max<int64_t>(maxs, std::min<int64_t>(kdim / 128, 4 * cus / ntiles));
+        else if (!delta) maxs = std::max<int64_t>(maxs, std::min<int64_t>(kdim / 128, 4 * cus / ntiles));
     }
     if (ns > maxs) ns = (int)(maxs > 0 ? maxs : 1);
     if (ns < 1) ns = 1;
@@ -1079,12 +1082,14 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     // 16 / 32 / 72 89.9 / 85.4 / 84.1; 3,840 AO on 128-wide, 4 / 8 / 16 179 / 168 / 168.  A
     // split count of 8 or more is rounded down to a multiple of the XCD count,
     // so that the syrk runs whole splits per XCD.  In FP32 they are parts of the
-    // mixed_nsplit ranges in which the FP32 sums fold.
+    // mixed_nsplit ranges in which the FP32 sums fold; the increment, whose reduction
+    // costs more per split, keeps whole ranges (360 / 480 / 600 AO with parts 2.28 / 3.73 /
+    // 5.48 ms, without 1.63 / 2.46 / 4.10).
     const int many = xcd_round(choose_ksplit(ntiles, L.kdim, p.num_cus,
                                              L.ktile == kTileK ? 16
                                              : precision == DFJK_FP64 && !fixed && (L.ktile == 96 || p.nao <= 640) ? 32
                                                                                                                    : 64,
-                                             !fixed));
+                                             !fixed, delta));
     L.nsub = 1;
     if (precision == DFJK_FP64) {
         L.nsplit_k = many;
@@ -1092,7 +1097,7 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
         L.nsplit_k = i8_nsplit(p.nao, L.kdim, !delta, L.ktile, p.num_cus);
     } else {
         L.nsplit_k = mixed_nsplit(p.nao, L.kdim, !delta, p.num_cus);
-        if (precision == DFJK_MIXED_FP32 && !fixed) {
+        if (precision == DFJK_MIXED_FP32 && !fixed && !delta) {
             const int64_t folds = (L.kdim / L.nsplit_k + 511) / 512;
             L.nsub = (int)std::max<int64_t>(1, std::min<int64_t>((many + L.nsplit_k / 2) / L.nsplit_k, folds));
             L.nsplit_k *= L.nsub;

@@ -1,0 +1,33 @@
+// Prints the launch shapes that the library plans for a molecule of given sizes: host
+// code only, linked against the library.  One query per line on stdin:
+//   layout nao naux_pad nf_pad aux_slab k_tile nocc precision with_D delta nsplit overlap force_slab ktile
+// answered by "ktile nsplit_k nsub slab nslab kdim bytes kpart_bytes".
+#include <iostream>
+#include <string>
+
+#include "dfjk_internal.h"
+
+using namespace dfjk;
+
+int main()
+{
+    std::string what;
+    while (std::cin >> what) {
+        Plan p;
+        p.stage = 1;
+        int nocc, precision;
+        std::cin >> p.nao >> p.naux_pad >> p.nf_pad >> p.aux_slab >> p.k_tile >> nocc >> precision;
+        p.naux = p.naux_pad;
+        p.nf = p.nf_pad;
+        if (what == "layout") {
+            int with_D, delta, nsplit, overlap, ktile;
+            int64_t force_slab;
+            std::cin >> with_D >> delta >> nsplit >> overlap >> force_slab >> ktile;
+            const BuildLayout L = build_layout(p, nocc, precision, with_D, delta, nsplit, overlap, force_slab, ktile);
+            const int64_t tiles = delta ? (int64_t)L.ntile * L.ntile : (int64_t)L.ntile * (L.ntile + 1) / 2;
+            std::cout << L.ktile << ' ' << L.nsplit_k << ' ' << L.nsub << ' ' << L.slab << ' ' << L.nslab << ' '
+                      << L.kdim << ' ' << L.bytes << ' ' << L.nslab * L.nsplit_k * tiles * L.ktile * L.ktile * 8
+                      << '\n';
+        }
+    }
+}

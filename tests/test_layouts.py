@@ -1,0 +1,68 @@
+"""Launch shapes that the library plans on the host (tile width, split counts, slabs, scratch), for sizes
+from one water to 128, through a small program linked against the library (no GPU)."""
+import os
+import subprocess
+
+import pytest
+
+N = pytest.importorskip("paper_2404_09452_amd._native")
+if not os.path.exists(N.LIB_PATH):
+    pytest.skip("libdfjk.so not built", allow_module_level=True)
+from paper_2404_09452_amd import build as B  # noqa: E402
+
+FP64, FP32, BF16X3, INT8, INT8_FAST = range(5)
+CUS = 256          # compute units a plan assumes
+T = 128            # tile of the increment
+WATERS = (1, 2, 3, 5, 7, 10, 12, 16, 20, 24, 25, 28, 31, 32, 35, 37, 44, 48, 55, 64, 96, 128)
+
+
+@pytest.fixture(scope="module")
+def query(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("layout") / "layout_query")
+    here = os.path.dirname(os.path.abspath(__file__))
+    lib = os.path.dirname(N.LIB_PATH)
+    cmd = [B.HIPCC] + B.FLAGS + [os.path.join(here, "layout_query.cpp"), "-L" + lib,
+                                 "-l:" + os.path.basename(N.LIB_PATH), "-Wl,-rpath," + lib, "-o", exe]
+    subprocess.run(cmd, check=True, capture_output=True)
+
+    def ask(lines):
+        r = subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, check=True)
+        return [[int(x) for x in line.split()] for line in r.stdout.splitlines()]
+    return ask
+
+
+def sizes(n):
+    """nao, naux_pad and nf_pad (every pair kept) of n waters in the test basis."""
+    nao = 30 * n
+    return nao, -(-87 * n // 128) * 128, -(-nao * (nao + 1) // 2 // 64) * 64
+
+
+class Layout:
+    def __init__(self, v):
+        self.ktile, self.nsplit, self.nsub, self.slab, self.nslab, self.kdim, self.bytes, self.kpart = v
+
+
+def layouts(query, asked):
+    """asked: dicts with n, nocc, precision and any of the options below."""
+    lines = []
+    for a in asked:
+        o = dict(aux_slab=0, k_tile=0, with_D=0, delta=0, nsplit=0, overlap=1, force_slab=0, ktile=0)
+        o.update(a)
+        nao, naux, nf = sizes(o["n"])
+        lines.append("layout %d %d %d %d %d %d %d %d %d %d %d %d %d" % (
+            nao, naux, nf, o["aux_slab"], o["k_tile"], o["nocc"], o["precision"], o["with_D"], o["delta"],
+            o["nsplit"], o["overlap"], o["force_slab"], o["ktile"]))
+    return [Layout(v) for v in query(lines)]
+
+
+@pytest.mark.parametrize("precision", [FP64, FP32])
+def test_increment_splits(query, precision):
+    """The increment's reduction reads both triangles of every split, one of them across rows, so an extra
+    split costs it more than it gives the product: no more splits than one per 256 k (FP64) and than fill the
+    chip twice (FP32), and no parts."""
+    for n in WATERS:
+        L, = layouts(query, [dict(n=n, nocc=5 * n, precision=precision, delta=1)])
+        tiles = (-(-30 * n // T)) ** 2
+        assert L.ktile == T and L.nsub == 1
+        assert L.nsplit <= max(1, L.kdim // 256)
+        assert L.nsplit <= max(1, (16 if precision == FP64 else 2) * CUS // tiles)
