@@ -291,16 +291,20 @@ int dfjk_build_batch(int32_t n, dfjk_plan *const *plans, const double *const *d_
  * (dfjk_build with d_C, this nocc and precision): its tile shape and split
  * count.  Candidates are half, one, two and four times the built-in split
  * count (within the contraction length) of the 128-wide output tiles, for
- * FP64 and FP32 of 64- and 96-wide and for int8_fast of 64-wide tiles too (which
- * leave less of the syrk's work above the diagonal or past nao).  Each runs one warm-up and three timed builds with
- * d_C on `stream` (HIP events; synchronises the stream), and the fastest is
- * kept in the plan for later builds of that shape.  Tile and split count
- * only reorder the FP64 sums of the split-K reduction, which stays fixed and
- * deterministic for a given choice.  dfjk_build_bytes may grow afterwards.
+ * FP64 and FP32 of 64- and 96-wide and for int8_fast of 64-wide tiles too
+ * (which leave less of the syrk's work above the diagonal or past nao).
+ * Each runs one warm-up and three timed builds with d_C on `stream` (HIP
+ * events; synchronises the stream), and the fastest is kept in the plan for
+ * later builds of that shape.  Tile and split count only reorder the FP64
+ * sums of the split-K reduction (FP32 counts are whole parts of the ranges in
+ * which its FP32 sums fold), which stays fixed and deterministic for a given
+ * choice.  dfjk_build_bytes may grow afterwards.
  * d_scratch must hold dfjk_autotune_bytes.  A candidate is reported as
- * 1000 * tile + split count: on return *chosen is the kept one; with
- * ncand != NULL, *ncand (capacity in, count out) candidates and their ms per
- * build are written to cand and ms (host arrays, may be NULL). */
+ * 1000 * tile + split count, where the count may pass 999: the tile is the
+ * largest of 64, 96 and 128 whose thousandfold does not pass the code.  On
+ * return *chosen is the kept one; with ncand != NULL, *ncand (capacity in,
+ * count out) candidates and their ms per build are written to cand and ms
+ * (host arrays, may be NULL). */
 int dfjk_autotune_bytes(const dfjk_plan *plan, int32_t nocc, int32_t precision, size_t *bytes);
 int dfjk_autotune(dfjk_plan *plan, const double *d_C, int32_t nocc, int32_t precision, void *d_scratch,
                   size_t scratch_bytes, void *stream, int32_t *chosen, int32_t *ncand, int32_t *cand,

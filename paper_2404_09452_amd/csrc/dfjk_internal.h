@@ -167,6 +167,12 @@ struct Profiler {
     void mark(int stage, bool begin);   // records one event on `stream`
 };
 
+// Shape of a K contraction as dfjk_autotune chooses it: output tile and splits
+// (of one slab), which the ABI reports as 1000 * tile + splits.
+struct KShape {
+    int tile, nsplit;
+};
+
 struct Plan {
     Profiler prof;
     // ---- molecule (host copies, caller order) ----
@@ -198,10 +204,9 @@ struct Plan {
     hipEvent_t ev_fork = nullptr, ev_ht[2] = {nullptr, nullptr}, ev_kdone[2] = {nullptr, nullptr};
     hipStream_t j_stream = nullptr;     // side stream: J of a build, the integrals of a setup
     hipEvent_t ev_jfork = nullptr, ev_jdone = nullptr;
-    // split counts chosen by dfjk_autotune for the closed-shell C-route build,
+    // K shapes chosen by dfjk_autotune for the closed-shell C-route build,
     // keyed by nocc * 8 + precision
-    std::map<int64_t, int> tuned_nsplit;
-    std::map<int64_t, int> tuned_ktile;   // the FP64 K GEMM tile kept with that split count
+    std::map<int64_t, KShape> tuned;
     int device = 0;
     int num_cus = 256;
     int stage = 0;
@@ -348,12 +353,14 @@ struct BuildLayout {
     size_t o_Xb, o_Xblo;                // the second X buffer of the overlapped schedule
 };
 // nsplit: 0 = the autotuned count when there is one, else the built-in
-// choice; -1 = the built-in choice; > 0 = that count (capped by the length)
+// choice; -1 = the built-in choice; > 0 = that count (capped by the length or the
+// built-in choice, whichever allows more; FP32: whole parts of its ranges)
 // force_slab > 0: that many aux functions per slab (a multiple of kPadAux);
-// ktile: 0 = the autotuned FP64 K tile when there is one (with nsplit 0),
-// else 128; 64 or 128 = that tile
+// ktile: 0 = the caller's (FP64) or the autotuned tile (with nsplit 0), else the
+// built-in choice; 64, 96 or 128 = that tile, where the precision has it
 BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool with_D, bool delta = false,
                          int nsplit = 0, bool allow_overlap = true, int64_t force_slab = 0, int ktile = 0);
+std::vector<KShape> autotune_candidates(const Plan &p, int32_t nocc, int32_t precision);
 void batch_nsplits(const Plan *const *plans, int n, const BuildLayout *Ls, int *ns);
 void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const double *const *C, double *const *J,
                         double *const *K, double *const *E, char *const *scratch, hipStream_t s);

@@ -1812,32 +1812,6 @@ int dfjk_offload(dfjk_plan *plan, void *h_pinned, size_t host_bytes, void *d_tab
     return DFJK_OK;
 }
 
-// Autotuner candidates: (K GEMM tile, split count).  Split counts are half,
-// one, two and four times the built-in choice of each tile; the FP64 and FP32 syrk
-// also try 64- and 96-wide tiles and int8_fast 64-wide ones, which leave
-// less of the work above the diagonal or past nao.  A candidate is encoded
-// as 1000 * tile + split count.
-static std::vector<int> autotune_candidates(const Plan &p, int32_t nocc, int32_t precision)
-{
-    std::vector<int> c;
-    std::vector<int> tiles = {kTileK};
-    if (precision == DFJK_FP64 || precision == DFJK_MIXED_FP32) { tiles.push_back(64); tiles.push_back(96); }
-    if (precision == DFJK_MIXED_INT8_FAST) tiles.push_back(64);
-    for (int kt : tiles) {
-        const BuildLayout L = build_layout(p, nocc, precision, false, false, -1, true, 0, kt);   // built-in split
-        const int64_t maxs = L.kdim / 256 > 0 ? L.kdim / 256 : 1;
-        for (int f : {-2, 1, 2, 4}) {
-            int n = f < 0 ? L.nsplit_k / 2 : L.nsplit_k * f;
-            if (n < 1) n = 1;
-            if (n > maxs) n = (int)maxs;
-            if (precision == DFJK_FP64 && n >= kXcds) n = n / kXcds * kXcds;   // whole splits per XCD
-            const int code = 1000 * kt + n;
-            if (std::find(c.begin(), c.end(), code) == c.end()) c.push_back(code);
-        }
-    }
-    return c;
-}
-
 int dfjk_autotune_bytes(const dfjk_plan *plan, int32_t nocc, int32_t precision, size_t *bytes)
 {
     if (!plan || !bytes) return fail(DFJK_E_INVALID, "NULL argument");
@@ -1846,8 +1820,8 @@ int dfjk_autotune_bytes(const dfjk_plan *plan, int32_t nocc, int32_t precision, 
     if (!valid_precision(precision)) return fail(DFJK_E_INVALID, "unknown precision");
     if (nocc < 1 || nocc > p.nao) return fail(DFJK_E_INVALID, "nocc must be in [1, nao]");
     size_t most = 0;
-    for (int c : autotune_candidates(p, nocc, precision))
-        most = std::max(most, build_layout(p, nocc, precision, false, false, c % 1000, true, 0, c / 1000).bytes);
+    for (const KShape &c : autotune_candidates(p, nocc, precision))
+        most = std::max(most, build_layout(p, nocc, precision, false, false, c.nsplit, true, 0, c.tile).bytes);
     *bytes = align_up(most, 256) + (size_t)2 * p.nao * p.nao * 8 + 256;   // + J, K and E of the trial builds
     return DFJK_OK;
 }
@@ -1882,10 +1856,10 @@ int dfjk_autotune(dfjk_plan *plan, const double *d_C, int32_t nocc, int32_t prec
     if (rc) return rc;
     if (dev != p.device) return fail(DFJK_E_STATE, "autotune called on a different device than setup");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const std::vector<int> cands = autotune_candidates(p, nocc, precision);
+    const std::vector<KShape> cands = autotune_candidates(p, nocc, precision);
     size_t most = 0;
-    for (int c : cands)
-        most = std::max(most, build_layout(p, nocc, precision, false, false, c % 1000, true, 0, c / 1000).bytes);
+    for (const KShape &c : cands)
+        most = std::max(most, build_layout(p, nocc, precision, false, false, c.nsplit, true, 0, c.tile).bytes);
     char *scr = static_cast<char *>(d_scratch);
     double *J = reinterpret_cast<double *>(scr + align_up(most, 256));
     double *K = J + (size_t)p.nao * p.nao;
@@ -1898,7 +1872,7 @@ int dfjk_autotune(dfjk_plan *plan, const double *d_C, int32_t nocc, int32_t prec
     std::vector<double> t(cands.size(), 0.0);
     hipError_t err = hipSuccess;
     for (size_t i = 0; i < cands.size() && err == hipSuccess; ++i) {
-        const BuildLayout L = build_layout(p, nocc, precision, false, false, cands[i] % 1000, true, 0, cands[i] / 1000);
+        const BuildLayout L = build_layout(p, nocc, precision, false, false, cands[i].nsplit, true, 0, cands[i].tile);
         const int reps = 3;
         for (int r = 0; r <= reps; ++r) {            // the first build warms up
             if (r == 1) err = hipEventRecord(e0, s);
@@ -1917,14 +1891,14 @@ int dfjk_autotune(dfjk_plan *plan, const double *d_C, int32_t nocc, int32_t prec
     HIP_OR_FAIL(err);
     HIP_OR_FAIL(hipGetLastError());
     const size_t best = (size_t)(std::min_element(t.begin(), t.end()) - t.begin());
-    p.tuned_nsplit[(int64_t)nocc * 8 + precision] = cands[best] % 1000;
-    p.tuned_ktile[(int64_t)nocc * 8 + precision] = cands[best] / 1000;
-    if (chosen) *chosen = cands[best];
+    p.tuned[(int64_t)nocc * 8 + precision] = cands[best];
+    const auto code = [](const KShape &k) { return (int32_t)(1000 * k.tile + k.nsplit); };
+    if (chosen) *chosen = code(cands[best]);
     if (ncand) {
         const int nmax = *ncand;
         *ncand = (int32_t)cands.size();
         for (int i = 0; i < (int)cands.size() && i < nmax; ++i) {
-            if (cand) cand[i] = cands[i];
+            if (cand) cand[i] = code(cands[i]);
             if (ms) ms[i] = t[i];
         }
     }

@@ -1006,6 +1006,11 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     // products, else 128, and no more splits than one per 256 k.
     L.ktile = kTileK;
     const bool fixed = force_slab > 0;
+    KShape tuned{0, 0};
+    if (nsplit == 0 && !with_D && !delta) {
+        const auto it = p.tuned.find((int64_t)nocc * 8 + precision);
+        if (it != p.tuned.end()) tuned = it->second;
+    }
     if (fixed && precision == DFJK_FP64) {
         auto executed = [&](int64_t t) { const int64_t n = (p.nao + t - 1) / t; return n * (n + 1) / 2 * t * t; };
         if (p.k_tile == 64 || p.k_tile == 96) L.ktile = p.k_tile;
@@ -1013,18 +1018,11 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     } else if ((precision == DFJK_FP64 || precision == DFJK_MIXED_FP32) && !delta && !fixed) {
         int kt = ktile;
         if (kt == 0 && precision == DFJK_FP64) kt = p.k_tile;
-        if (kt == 0 && nsplit == 0 && !with_D) {
-            const auto it = p.tuned_ktile.find((int64_t)nocc * 8 + precision);
-            if (it != p.tuned_ktile.end()) kt = it->second;
-        }
+        if (kt == 0) kt = tuned.tile;
         L.ktile = kt == 64 || kt == 96 || kt == kTileK ? kt : syrk_tile_width(p.nao, precision == DFJK_FP64);
     }
     if (precision == DFJK_MIXED_INT8_FAST && !delta && !fixed) {
-        int kt = ktile;
-        if (kt == 0 && nsplit == 0) {
-            const auto it = p.tuned_ktile.find((int64_t)nocc * 8 + precision);
-            if (it != p.tuned_ktile.end()) kt = it->second;
-        }
+        const int kt = ktile != 0 ? ktile : tuned.tile;
         L.ktile = kt == 64 || kt == kTileK ? kt : i8_fast_tile(p.nao);
     }
     L.ntile = (int)((p.nao + L.ktile - 1) / L.ktile);
@@ -1103,14 +1101,16 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
             L.nsplit_k *= L.nsub;
         }
     }
-    if (nsplit == 0 && !with_D && !delta) {   // a split count the autotuner measured for this shape
-        const auto it = p.tuned_nsplit.find((int64_t)nocc * 8 + precision);
-        if (it != p.tuned_nsplit.end()) nsplit = it->second;
-    }
+    if (nsplit == 0) nsplit = tuned.nsplit;   // a split count the autotuner measured for this shape
     if (nsplit > 0) {   // a batch (or the autotuner) chooses the split count
-        const int64_t maxs = L.kdim / 256 > 0 ? L.kdim / 256 : 1;
-        L.nsplit_k = nsplit < maxs ? nsplit : (int)maxs;
-        L.nsub = 1;
+        if (precision == DFJK_MIXED_FP32 && !fixed && !delta) {   // parts of the same ranges: no fold moves
+            const int ranges = L.nsplit_k / L.nsub;
+            const int64_t folds = (L.kdim / ranges + 511) / 512;
+            L.nsub = (int)std::max<int64_t>(1, std::min<int64_t>(nsplit / ranges, folds));
+            L.nsplit_k = ranges * L.nsub;
+        } else {
+            L.nsplit_k = (int)std::min<int64_t>(nsplit, std::max<int64_t>(L.kdim / 256, L.nsplit_k));
+        }
     }
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -1150,6 +1150,30 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     L.o_Epart = take((size_t)L.ntile * (L.ntile + 1) / 2 * reduce_chunks(L.ktile) * 8);
     L.bytes = align_up(off, 256);
     return L;
+}
+
+// Autotuner candidates.  Split counts are half, one, two and four times the built-in
+// choice of each tile, below 28,000 (the ABI's code is 1000 * tile + splits, and the
+// tiles 96 and 128 are that far apart); the FP64 and FP32 syrk also try 64- and 96-wide tiles and int8_fast 64-wide ones, which leave
+// less of the work above the diagonal or past nao.  Each is the shape that its own
+// layout has.
+std::vector<KShape> autotune_candidates(const Plan &p, int32_t nocc, int32_t precision)
+{
+    std::vector<KShape> c;
+    std::vector<int> tiles = {kTileK};
+    if (precision == DFJK_FP64 || precision == DFJK_MIXED_FP32) { tiles.push_back(64); tiles.push_back(96); }
+    if (precision == DFJK_MIXED_INT8_FAST) tiles.push_back(64);
+    for (int kt : tiles) {
+        const int built_in = build_layout(p, nocc, precision, false, false, -1, true, 0, kt).nsplit_k;
+        for (int f : {-2, 1, 2, 4}) {
+            int n = std::min(std::max(f < 0 ? built_in / 2 : built_in * f, 1), 27999);
+            if (precision == DFJK_FP64 && n >= kXcds) n = n / kXcds * kXcds;   // whole splits per XCD
+            n = build_layout(p, nocc, precision, false, false, n, true, 0, kt).nsplit_k;
+            if (std::none_of(c.begin(), c.end(), [&](const KShape &k) { return k.tile == kt && k.nsplit == n; }))
+                c.push_back({kt, n});
+        }
+    }
+    return c;
 }
 
 void launch_gemm_bf16x3(bool lower, const void *A, const void *Alo, const void *B, const void *Blo, int64_t nao,
@@ -1545,7 +1569,8 @@ void batch_nsplits(const Plan *const *plans, int n, const BuildLayout *Ls, int *
     const double per = std::max(256.0, work / (24.0 * cus));   // k of a 64-wide tile's workgroup
     for (int i = 0; i < n; ++i) {
         const double k = std::max(256.0, per * 4096.0 / ((double)Ls[i].ktile * Ls[i].ktile));
-        ns[i] = xcd_round((int)std::max(1.0, (double)Ls[i].kdim / k + 0.5));
+        ns[i] = (int)std::min<int64_t>(xcd_round((int)std::max(1.0, (double)Ls[i].kdim / k + 0.5)),
+                                       std::max<int64_t>(1, Ls[i].kdim / 256));
     }
 }
 

@@ -61,6 +61,12 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
 
 
+def k_shape(code):
+    """(tile, splits) of a K shape that dfjk_autotune reports as 1000 * tile + splits."""
+    tile = max(t for t in (64, 96, 128) if 1000 * t <= code)
+    return tile, int(code) - 1000 * tile
+
+
 class Plan:
     """One molecule: host preparation at construction, then screen/setup once
     and build any number of times.
@@ -332,8 +338,7 @@ class Plan:
         _check(N.lib().dfjk_autotune(self._h, _ptr(C), int(nocc), PRECISION[precision], _ptr(scr), scr.numel(),
                                      _stream_handle(stream), ctypes.byref(chosen), ctypes.byref(ncand), cand, ms))
         self._scratch = {}          # build sizes may have changed
-        dec = lambda c: (int(c) // 1000, int(c) % 1000)   # noqa: E731  (1000 * tile + split)
-        return dec(chosen.value), {dec(cand[i]): float(ms[i]) for i in range(ncand.value)}
+        return k_shape(chosen.value), {k_shape(cand[i]): float(ms[i]) for i in range(ncand.value)}
 
     @_on_stream
     def offload(self, stream=None):

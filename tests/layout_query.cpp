@@ -1,7 +1,9 @@
 // Prints the launch shapes that the library plans for a molecule of given sizes: host
 // code only, linked against the library.  One query per line on stdin:
 //   layout nao naux_pad nf_pad aux_slab k_tile nocc precision with_D delta nsplit overlap force_slab ktile
-// answered by "ktile nsplit_k nsub slab nslab kdim bytes kpart_bytes".
+// answered by "ktile nsplit_k nsub slab nslab kdim bytes kpart_bytes", and
+//   candidates nao naux_pad nf_pad aux_slab k_tile nocc precision
+// by the autotuner's "tile splits" pairs.
 #include <iostream>
 #include <string>
 
@@ -28,6 +30,9 @@ int main()
             std::cout << L.ktile << ' ' << L.nsplit_k << ' ' << L.nsub << ' ' << L.slab << ' ' << L.nslab << ' '
                       << L.kdim << ' ' << L.bytes << ' ' << L.nslab * L.nsplit_k * tiles * L.ktile * L.ktile * 8
                       << '\n';
+        } else {
+            for (const KShape &c : autotune_candidates(p, nocc, precision)) std::cout << c.tile << ' ' << c.nsplit << ' ';
+            std::cout << '\n';
         }
     }
 }

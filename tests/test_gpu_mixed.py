@@ -284,3 +284,20 @@ def test_fp32_tile_widths(n, nocc, slab, tile):
     # the increment (from K0 back to itself with C0 = -C: U = 0 after the rotation, so K0 comes back)
     _, Kd, _ = plan.build_delta(C, -C, K0, precision="fp32")
     assert ((Kd - K0).abs() / tol).max().item() <= 1.0
+
+
+def test_autotune_codes_at_large_split_counts():
+    """FP32 at 32 waters, where four times the built-in split count of 96-wide tiles passes 999: every
+    candidate names a real tile and the kept one is the shape of later builds, whose K differs from the
+    untuned one's by the order of FP64 sums only: at most 1,100 additions (882 splits, 63 folds in each of
+    14 ranges) of terms whose sizes sum to 2 sum_k |x||x| <= sqrt(K_mu,mu K_nu,nu)."""
+    mol, S, C = case(32)
+    plan = G.Plan.from_molecule(mol, schwarz_thresh=TAU).screen().setup()
+    K0 = plan.build(C=C, precision="fp32")[1]
+    chosen, times = plan.autotune(C, precision="fp32")
+    assert chosen in times and {t for t, _ in times} == {64, 96, 128}
+    shape = plan.build_shape(C.shape[1], "fp32")
+    assert (shape["k_tile"], shape["nsplit"]) == chosen
+    K = plan.build(C=C, precision="fp32")[1]
+    d = torch.sqrt(torch.diagonal(K0).clamp(min=0))
+    assert ((K - K0).abs() <= 1100 * 2.0 ** -53 * torch.outer(d, d)).all()

@@ -9,6 +9,7 @@ N = pytest.importorskip("paper_2404_09452_amd._native")
 if not os.path.exists(N.LIB_PATH):
     pytest.skip("libdfjk.so not built", allow_module_level=True)
 from paper_2404_09452_amd import build as B  # noqa: E402
+from paper_2404_09452_amd import dfjk as G  # noqa: E402
 
 FP64, FP32, BF16X3, INT8, INT8_FAST = range(5)
 CUS = 256          # compute units a plan assumes
@@ -66,3 +67,22 @@ def test_increment_splits(query, precision):
         assert L.ktile == T and L.nsub == 1
         assert L.nsplit <= max(1, L.kdim // 256)
         assert L.nsplit <= max(1, (16 if precision == FP64 else 2) * CUS // tiles)
+
+
+@pytest.mark.parametrize("precision", [FP64, FP32, BF16X3, INT8, INT8_FAST])
+def test_autotune_candidates(query, precision):
+    """Every candidate of the autotuner survives its code (1000 tile + splits), is the shape that its own
+    layout has, and leaves the ranges of the FP32 folds where they are; the built-in shape is among them."""
+    for n in WATERS:
+        for nocc in (1, 5 * n, 30 * n):
+            nao, naux, nf = sizes(n)
+            row, = query(["candidates %d %d %d 0 0 %d %d" % (nao, naux, nf, nocc, precision)])
+            cands = list(zip(row[::2], row[1::2]))
+            assert len(cands) <= 16 and len(set(cands)) == len(cands)
+            built = layouts(query, [dict(n=n, nocc=nocc, precision=precision, nsplit=-1)])[0]
+            assert (built.ktile, built.nsplit) in cands
+            own = layouts(query, [dict(n=n, nocc=nocc, precision=precision, nsplit=s, ktile=t) for t, s in cands])
+            for (t, s), L in zip(cands, own):
+                assert s > 0 and G.k_shape(1000 * t + s) == (t, s)
+                assert (L.ktile, L.nsplit) == (t, s)
+                assert L.nsplit // L.nsub == built.nsplit // built.nsub or precision != FP32
