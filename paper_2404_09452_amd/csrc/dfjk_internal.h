@@ -360,6 +360,10 @@ struct BuildLayout {
 // built-in choice; 64, 96 or 128 = that tile, where the precision has it
 BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool with_D, bool delta = false,
                          int nsplit = 0, bool allow_overlap = true, int64_t force_slab = 0, int ktile = 0);
+// Layout of dfjk_build_static: the widest aux slab (single stream, no second X buffer) whose
+// scratch fits the static array, with the autotuned K shape if any slab fits with it,
+// else the built-in one; false (L: the narrowest slab) where neither fits.
+bool static_layout(const Plan &p, int32_t nocc, int32_t precision, bool with_D, BuildLayout &L);
 std::vector<KShape> autotune_candidates(const Plan &p, int32_t nocc, int32_t precision);
 void batch_nsplits(const Plan *const *plans, int n, const BuildLayout *Ls, int *ns);
 void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const double *const *C, double *const *J,

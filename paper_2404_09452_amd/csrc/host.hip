@@ -1390,18 +1390,9 @@ int dfjk_build_static(dfjk_plan *plan, const double *d_C, int32_t nocc, const do
     if (rc) return rc;
     if (dev != p.device) return fail(DFJK_E_STATE, "build called on a different device than setup");
     if (withD && p.host_B) return fail(DFJK_E_UNSUPPORTED, "the density route needs a device-resident B");
-    // the widest aux slab (single stream, no second X buffer) whose scratch fits
     BuildLayout L{};
-    bool fits = false;
-    size_t least = 0;
-    for (int64_t slab = p.naux_pad; slab >= kPadAux && !fits; slab -= kPadAux) {
-        L = build_layout(p, nocc, precision, withD, false, 0, false, slab);
-        fits = L.bytes <= kStaticScratchBytes;
-        least = L.bytes;
-        if (p.host_B) break;   // the slab of a host-resident B is fixed
-    }
-    if (!fits)
-        return fail(DFJK_E_OOM, "dfjk_build_static: this build needs " + std::to_string(least) +
+    if (!static_layout(p, nocc, precision, withD, L))
+        return fail(DFJK_E_OOM, "dfjk_build_static: this build needs " + std::to_string(L.bytes) +
                                     " bytes of scratch even with the narrowest aux slab; the static scratch holds " +
                                     std::to_string(kStaticScratchBytes) + " (use dfjk_build with a workspace)");
     char *ws = nullptr;

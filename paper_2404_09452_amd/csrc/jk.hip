@@ -1001,9 +1001,9 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     // the rule of syrk_tile_width, for int8_fast that of i8_fast_tile; for FP64
     // the autotuner's choice for the shape, or the caller's, wins.  int8, BF16x3
     // and every increment keep 128.
-    // With a forced slab (the static scratch) the shapes are those of the smallest
-    // partial tiles: 64-wide FP64 tiles where 128-wide ones execute over 14% more
-    // products, else 128, and no more splits than one per 256 k.
+    // With a forced slab (the static scratch) the built-in shapes are those of the
+    // smallest partial tiles: 64-wide FP64 tiles where 128-wide ones execute over 14%
+    // more products, else 128, and no more splits than one per 256 k.
     L.ktile = kTileK;
     const bool fixed = force_slab > 0;
     KShape tuned{0, 0};
@@ -1013,14 +1013,17 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     }
     if (fixed && precision == DFJK_FP64) {
         auto executed = [&](int64_t t) { const int64_t n = (p.nao + t - 1) / t; return n * (n + 1) / 2 * t * t; };
-        if (p.k_tile == 64 || p.k_tile == 96) L.ktile = p.k_tile;
-        else if (p.k_tile == 0 && (double)executed(kTileK) > 1.14 * (double)executed(64)) L.ktile = 64;
+        const int kt = p.k_tile != 0 ? p.k_tile : tuned.tile;
+        if (kt == 64 || kt == 96) L.ktile = kt;
+        else if (kt == 0 && (double)executed(kTileK) > 1.14 * (double)executed(64)) L.ktile = 64;
     } else if ((precision == DFJK_FP64 || precision == DFJK_MIXED_FP32) && !delta && !fixed) {
         int kt = ktile;
         if (kt == 0 && precision == DFJK_FP64) kt = p.k_tile;
         if (kt == 0) kt = tuned.tile;
         L.ktile = kt == 64 || kt == 96 || kt == kTileK ? kt : syrk_tile_width(p.nao, precision == DFJK_FP64);
     }
+    if (fixed && (precision == DFJK_MIXED_FP32 || precision == DFJK_MIXED_INT8_FAST) && tuned.tile != 0)
+        L.ktile = tuned.tile;
     if (precision == DFJK_MIXED_INT8_FAST && !delta && !fixed) {
         const int kt = ktile != 0 ? ktile : tuned.tile;
         L.ktile = kt == 64 || kt == kTileK ? kt : i8_fast_tile(p.nao);
@@ -1150,6 +1153,18 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     L.o_Epart = take((size_t)L.ntile * (L.ntile + 1) / 2 * reduce_chunks(L.ktile) * 8);
     L.bytes = align_up(off, 256);
     return L;
+}
+
+bool static_layout(const Plan &p, int32_t nocc, int32_t precision, bool with_D, BuildLayout &L)
+{
+    for (const int nsplit : {0, -1}) {   // the tuned shape, then the built-in one
+        for (int64_t slab = p.naux_pad; slab >= kPadAux; slab -= kPadAux) {
+            L = build_layout(p, nocc, precision, with_D, false, nsplit, false, slab);
+            if (L.bytes <= DFJK_STATIC_SCRATCH_BYTES) return true;
+            if (p.host_B) break;   // the slab of a host-resident B is fixed
+        }
+    }
+    return false;
 }
 
 // Autotuner candidates.  Split counts are half, one, two and four times the built-in

@@ -47,11 +47,11 @@ def layouts(query, asked):
     """asked: dicts with n, nocc, precision and any of the options below."""
     lines = []
     for a in asked:
-        o = dict(aux_slab=0, k_tile=0, with_D=0, delta=0, nsplit=0, overlap=1, force_slab=0, ktile=0)
+        o = dict(aux_slab=0, k_tile=0, tuned=(0, 0), with_D=0, delta=0, nsplit=0, overlap=1, force_slab=0, ktile=0)
         o.update(a)
         nao, naux, nf = sizes(o["n"])
-        lines.append("layout %d %d %d %d %d %d %d %d %d %d %d %d %d" % (
-            nao, naux, nf, o["aux_slab"], o["k_tile"], o["nocc"], o["precision"], o["with_D"], o["delta"],
+        lines.append("layout %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d" % (
+            nao, naux, nf, o["aux_slab"], o["k_tile"], *o["tuned"], o["nocc"], o["precision"], o["with_D"], o["delta"],
             o["nsplit"], o["overlap"], o["force_slab"], o["ktile"]))
     return [Layout(v) for v in query(lines)]
 
@@ -76,7 +76,7 @@ def test_autotune_candidates(query, precision):
     for n in WATERS:
         for nocc in (1, 5 * n, 30 * n):
             nao, naux, nf = sizes(n)
-            row, = query(["candidates %d %d %d 0 0 %d %d" % (nao, naux, nf, nocc, precision)])
+            row, = query(["candidates %d %d %d 0 0 0 0 %d %d" % (nao, naux, nf, nocc, precision)])
             cands = list(zip(row[::2], row[1::2]))
             assert len(cands) <= 16 and len(set(cands)) == len(cands)
             built = layouts(query, [dict(n=n, nocc=nocc, precision=precision, nsplit=-1)])[0]
@@ -86,3 +86,23 @@ def test_autotune_candidates(query, precision):
                 assert s > 0 and G.k_shape(1000 * t + s) == (t, s)
                 assert (L.ktile, L.nsplit) == (t, s)
                 assert L.nsplit // L.nsub == built.nsplit // built.nsub or precision != FP32
+
+
+@pytest.mark.parametrize("precision", [FP64, FP32, BF16X3, INT8, INT8_FAST])
+def test_static_build_after_autotuning(query, precision):
+    """A build that fits the 64 MiB static scratch untuned also fits it whichever candidate the autotuner
+    keeps, on that candidate's tile where the tuned shape fits and as untuned otherwise."""
+    fitted = 0
+    for n in range(1, 15):
+        for nocc in (1, 5 * n, 15 * n):
+            size = "%d %d %d" % sizes(n)
+            row, = query(["candidates %s 0 0 0 0 %d %d" % (size, nocc, precision)])
+            shapes = [(0, 0)] + list(zip(row[::2], row[1::2]))
+            got = query(["static %s 0 0 %d %d %d %d" % (size, t, s, nocc, precision) for t, s in shapes])
+            if not got[0][0]:
+                continue
+            fitted += 1
+            for (t, s), g in zip(shapes, got):
+                assert g[0] == 1 and g[4] <= 64 << 20, (n, nocc, t, s)
+                assert s == 0 or g[1] == t or g == got[0]
+    assert fitted >= 20

@@ -66,6 +66,22 @@ def test_static_build_int8_and_density_route():
     plan.close()
 
 
+@pytest.mark.parametrize("n,prec", [(3, "fp64"), (3, "int8_fast"), (10, "int8_fast")])
+def test_static_build_after_autotuning(n, prec):
+    """The autotuner's tile and splits in the static scratch (3 waters: one slab, as in the workspace
+    build), and a size at which many tuned shapes no longer fit it while the built-in one does."""
+    mol, C = case(n)
+    plan = G.Plan.from_molecule(mol).screen().setup()
+    plan.autotune(C, precision=prec)
+    if n == 3:
+        _compare(plan, prec, C=C)
+    else:   # other slabs, so other scale blocks: the format's 1e-6 Eh
+        E = plan.build_static(C=C, precision=prec)[2]
+        ref = plan.build(C=C)[2]
+        assert abs(float(E[1] - ref[1])) <= 1e-6
+    plan.close()
+
+
 def test_static_build_refuses_a_molecule_beyond_the_array():
     mol, C = case(12)
     plan = G.Plan.from_molecule(mol).screen().setup()
