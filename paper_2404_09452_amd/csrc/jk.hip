@@ -983,6 +983,16 @@ static int choose_ksplit(int ntiles, int64_t kdim, int num_cus, int per_cu, bool
     return ns;
 }
 
+// Parts of each of `ranges` k ranges of the FP32 syrk: as many as asked for, each of whole
+// folds (512 k), none empty (24 waters: 9 parts asked of 10,880 k are 8 of 1,536; the
+// ninth was 24 of 216 splits of zeros, written and read back).
+static int f32_parts(int64_t kdim, int ranges, int64_t want)
+{
+    const int64_t len = (kdim + ranges - 1) / ranges, n = std::max<int64_t>(1, want);
+    const int64_t part = (int64_t)align_up((size_t)((len + n - 1) / n), 512);
+    return (int)((len + part - 1) / part);
+}
+
 static int xcd_round(int ns) { return ns >= kXcds ? ns / kXcds * kXcds : ns; }
 
 BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool with_D, bool delta, int nsplit,
@@ -1099,8 +1109,7 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     } else {
         L.nsplit_k = mixed_nsplit(p.nao, L.kdim, !delta, p.num_cus);
         if (precision == DFJK_MIXED_FP32 && !fixed && !delta) {
-            const int64_t folds = (L.kdim / L.nsplit_k + 511) / 512;
-            L.nsub = (int)std::max<int64_t>(1, std::min<int64_t>((many + L.nsplit_k / 2) / L.nsplit_k, folds));
+            L.nsub = f32_parts(L.kdim, L.nsplit_k, (many + L.nsplit_k / 2) / L.nsplit_k);
             L.nsplit_k *= L.nsub;
         }
     }
@@ -1108,8 +1117,7 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     if (nsplit > 0) {   // a batch (or the autotuner) chooses the split count
         if (precision == DFJK_MIXED_FP32 && !fixed && !delta) {   // parts of the same ranges: no fold moves
             const int ranges = L.nsplit_k / L.nsub;
-            const int64_t folds = (L.kdim / ranges + 511) / 512;
-            L.nsub = (int)std::max<int64_t>(1, std::min<int64_t>(nsplit / ranges, folds));
+            L.nsub = f32_parts(L.kdim, ranges, nsplit / ranges);
             L.nsplit_k = ranges * L.nsub;
         } else {
             L.nsplit_k = (int)std::min<int64_t>(nsplit, std::max<int64_t>(L.kdim / 256, L.nsplit_k));

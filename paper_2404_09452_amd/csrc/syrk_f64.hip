@@ -126,7 +126,10 @@ __device__ __forceinline__ void syrk_tile(SyrkArgs g, unsigned blk)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sub = EDGES ? (wave + (int)(blk / kXcds)) % NW : wave;
     const int wm = sub / WGN, wn = sub % WGN;
-    const int64_t kr = (int64_t)(split / g.nsub) * g.ksplit, kb = kr + (split % g.nsub) * g.ksub;
+    // a range's parts rotate over its splits: the last one, which may be short, would
+    // else be one XCD's in every range (8 parts)
+    const int range = split / g.nsub, part = (split + range) % g.nsub;
+    const int64_t kr = (int64_t)range * g.ksplit, kb = kr + part * g.ksub;
     int64_t ke = min(min(kb + g.ksub, kr + g.ksplit), g.kdim);
     if (g.tri_k) ke = min(ke, (int64_t)(tn + 1) * T);
     const int nch = (int)((ke - kb) / KC);

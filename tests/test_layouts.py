@@ -106,3 +106,19 @@ def test_static_build_after_autotuning(query, precision):
                 assert g[0] == 1 and g[4] <= 64 << 20, (n, nocc, t, s)
                 assert s == 0 or g[1] == t or g == got[0]
     assert fitted >= 20
+
+
+def test_fp32_parts_are_not_empty(query):
+    """No part of an FP32 k range is empty: built-in splits and the autotuner's, one slab and several."""
+    for n in WATERS:
+        for nocc, slab in ((1, 0), (5 * n, 0), (30 * n, 0), (5 * n, 128), (5 * n, 640)):
+            nao, naux, nf = sizes(n)
+            row, = query(["candidates %d %d %d %d 0 0 0 %d %d" % (nao, naux, nf, slab, nocc, FP32)])
+            asked = [(0, -1)] + list(zip(row[::2], row[1::2]))
+            for L in layouts(query, [dict(n=n, nocc=nocc, precision=FP32, aux_slab=slab, nsplit=s, ktile=t)
+                                     for t, s in asked]):
+                ranges = L.nsplit // L.nsub
+                part = -(-(-(-L.kdim // ranges)) // L.nsub)       # k of a part ...
+                part = -(-part // 512) * 512 if L.nsub > 1 else part   # ... in whole folds
+                assert ranges * L.nsub == L.nsplit
+                assert (L.nsub - 1) * part < -(-L.kdim // ranges)
