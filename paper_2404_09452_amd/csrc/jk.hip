@@ -22,6 +22,7 @@ namespace dfjk {
 
 constexpr int kCSplitRows = 512; // f rows per partial of c
 constexpr double kAutoSlabBytes = 48e9;  // automatic aux slab: slab-sized K buffers up to this
+constexpr double kPartBytes = 6e9;       // FP32 parts while the partial tiles of all slabs stay within this
 constexpr double kJSideBytes = 64e6;     // J beside K from this size of B on (below, the fork costs more)
 
 // ---------------------------------------------------------------------------
@@ -1095,7 +1096,9 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     // so that the syrk runs whole splits per XCD.  In FP32 they are parts of the
     // mixed_nsplit ranges in which the FP32 sums fold; the increment, whose reduction
     // costs more per split, keeps whole ranges (360 / 480 / 600 AO with parts 2.28 / 3.73 /
-    // 5.48 ms, without 1.63 / 2.46 / 4.10).
+    // 5.48 ms, without 1.63 / 2.46 / 4.10), and a build in many slabs, whose k ranges are
+    // short already, takes fewer parts (1,920 AO in 44 slabs: 28 splits a slab 19.4 GB and
+    // 78.8 ms, 8 splits 5.5 GB and 75.3).
     const int many = xcd_round(choose_ksplit(ntiles, L.kdim, p.num_cus,
                                              L.ktile == kTileK ? 16
                                              : precision == DFJK_FP64 && !fixed && (L.ktile == 96 || p.nao <= 640) ? 32
@@ -1109,7 +1112,9 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     } else {
         L.nsplit_k = mixed_nsplit(p.nao, L.kdim, !delta, p.num_cus);
         if (precision == DFJK_MIXED_FP32 && !fixed && !delta) {
-            L.nsub = f32_parts(L.kdim, L.nsplit_k, (many + L.nsplit_k / 2) / L.nsplit_k);
+            const double whole = (double)L.nslab * L.nsplit_k * ntiles * L.ktile * L.ktile * 8;   // bytes without parts
+            const int64_t fit = (int64_t)std::min(1e6, kPartBytes / whole);
+            L.nsub = f32_parts(L.kdim, L.nsplit_k, std::min<int64_t>((many + L.nsplit_k / 2) / L.nsplit_k, fit));
             L.nsplit_k *= L.nsub;
         }
     }

@@ -122,3 +122,12 @@ def test_fp32_parts_are_not_empty(query):
                 part = -(-part // 512) * 512 if L.nsub > 1 else part   # ... in whole folds
                 assert ranges * L.nsub == L.nsplit
                 assert (L.nsub - 1) * part < -(-L.kdim // ranges)
+
+
+def test_fp32_partials_stay_small(query):
+    """FP32 parts do not multiply the partial tiles of many aux slabs: within 6 GB wherever whole ranges (one
+    round of two 128-wide workgroups a CU for every slab) are."""
+    for n in WATERS:
+        for slab in (0, 128, 256, 640, 1024):
+            L, = layouts(query, [dict(n=n, nocc=5 * n, precision=FP32, aux_slab=slab)])
+            assert L.kpart <= max(6e9, L.kpart // L.nsub), (n, slab)
