@@ -219,7 +219,10 @@ int dfjk_setup_batch(int32_t n, dfjk_plan *const *plans, void *const *d_workspac
  * needs several aux slabs (C route), the half transform of the next slab runs
  * on a second stream owned by the plan, forked from and joined back into
  * `stream`; such builds of one plan must not run concurrently on different
- * streams. */
+ * streams.  J of a build whose B is 64 MB or larger runs on another stream of
+ * the plan, forked and joined alike; such builds (dfjk_build_uks too), each
+ * with its own scratch and outputs, may run at once on several streams and
+ * threads, also beside a stream capture of one of them. */
 int dfjk_build_bytes(const dfjk_plan *plan, int32_t nocc, int32_t precision,
                      int32_t with_density, size_t *bytes);
 int dfjk_build(dfjk_plan *plan, const double *d_C, int32_t nocc, const double *d_D,

@@ -7,7 +7,9 @@
 #include <cstddef>
 #include <cstdint>
 #include <map>
+#include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "dfjk.h"
@@ -203,7 +205,11 @@ struct Plan {
     hipStream_t ht_stream = nullptr;
     hipEvent_t ev_fork = nullptr, ev_ht[2] = {nullptr, nullptr}, ev_kdone[2] = {nullptr, nullptr};
     hipStream_t j_stream = nullptr;     // side stream: J of a build, the integrals of a setup
-    hipEvent_t ev_jfork = nullptr, ev_jdone = nullptr;
+    hipEvent_t ev_jfork = nullptr, ev_jdone = nullptr;   // of a setup
+    // of builds, which calls on several streams and threads may run at once: each call
+    // has a pair of events of its own, and one call's work on the side stream stays together
+    std::mutex side_mu;
+    std::vector<std::pair<hipEvent_t, hipEvent_t>> side_events;   // free pairs: fork, done
     // K shapes chosen by dfjk_autotune for the closed-shell C-route build,
     // keyed by nocc * 8 + precision
     std::map<int64_t, KShape> tuned;

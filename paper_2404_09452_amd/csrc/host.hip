@@ -1982,6 +1982,10 @@ int dfjk_plan_destroy(dfjk_plan *plan)
         for (hipEvent_t e : {p.ev_ready[0], p.ev_ready[1], p.ev_free[0], p.ev_free[1], p.ev_start, p.ev_fork,
                              p.ev_ht[0], p.ev_ht[1], p.ev_kdone[0], p.ev_kdone[1], p.ev_jfork, p.ev_jdone})
             if (e) (void)hipEventDestroy(e);
+        for (const auto &e : p.side_events) {
+            (void)hipEventDestroy(e.first);
+            (void)hipEventDestroy(e.second);
+        }
         if (p.copy_stream) (void)hipStreamDestroy(p.copy_stream);
         if (p.ht_stream) (void)hipStreamDestroy(p.ht_stream);
         if (p.j_stream) (void)hipStreamDestroy(p.j_stream);

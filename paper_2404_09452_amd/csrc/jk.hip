@@ -1439,6 +1439,73 @@ bool side_stream(Plan &p)
     return true;
 }
 
+// J of one call on the plan's side stream, from side_begin to side_end (the lock is
+// held between them), joined into the caller's stream by side_join.  js is the
+// caller's stream where the side stream is not wanted or not to be had.
+struct SideJ {
+    hipStream_t js;
+    bool on = false;
+    std::pair<hipEvent_t, hipEvent_t> ev{};
+    std::unique_lock<std::mutex> lock;
+};
+
+// Whether a stream capture that s is not part of holds the side stream.
+static bool captured_elsewhere(hipStream_t js, hipStream_t s)
+{
+    hipStreamCaptureStatus cj = hipStreamCaptureStatusNone, cs = hipStreamCaptureStatusNone;
+    unsigned long long ij = 0, is = 0;
+    if (hipStreamGetCaptureInfo(js, &cj, &ij) != hipSuccess) return true;
+    if (cj == hipStreamCaptureStatusNone) return false;
+    if (s == nullptr || hipStreamGetCaptureInfo(s, &cs, &is) != hipSuccess) return true;
+    return cs != hipStreamCaptureStatusActive || ij != is;
+}
+
+// js waits for what s holds by now.
+static void side_wait(const SideJ &j, hipStream_t s)
+{
+    (void)hipEventRecord(j.ev.first, s);
+    (void)hipStreamWaitEvent(j.js, j.ev.first, 0);
+}
+
+static SideJ side_begin(Plan &p, hipStream_t s, bool want)
+{
+    SideJ j;
+    j.js = s;
+    if (!want) return j;
+    std::unique_lock<std::mutex> lock(p.side_mu);
+    if (!side_stream(p) || captured_elsewhere(p.j_stream, s)) return j;
+    if (!p.side_events.empty()) {
+        j.ev = p.side_events.back();
+        p.side_events.pop_back();
+    } else {
+        if (hipEventCreateWithFlags(&j.ev.first, hipEventDisableTiming) != hipSuccess) return j;
+        if (hipEventCreateWithFlags(&j.ev.second, hipEventDisableTiming) != hipSuccess) {
+            (void)hipEventDestroy(j.ev.first);
+            return j;
+        }
+    }
+    j.on = true;
+    j.js = p.j_stream;
+    j.lock = std::move(lock);
+    side_wait(j, s);
+    return j;
+}
+
+static void side_end(SideJ &j)
+{
+    if (!j.on) return;
+    (void)hipEventRecord(j.ev.second, j.js);
+    j.lock.unlock();
+}
+
+static void side_join(Plan &p, SideJ &j, hipStream_t s)
+{
+    if (!j.on) return;
+    (void)hipStreamWaitEvent(s, j.ev.second, 0);
+    std::lock_guard<std::mutex> lock(p.side_mu);
+    p.side_events.push_back(j.ev);
+}
+
 void launch_build(Plan &p, const BuildLayout &L, const double *C, const double *Din, double *J, double *K,
                   double *E, char *scratch, hipStream_t s)
 {
@@ -1457,13 +1524,10 @@ void launch_build(Plan &p, const BuildLayout &L, const double *C, const double *
     // transform, J costs 32 waters 0.3 ms (2.15 -> 2.47 ms); beside K it cost 0.7 (6.6 ->
     // 7.35 ms), more than the 0.5 that it takes alone.  J reads D and B and writes
     // only J and its own scratch.
-    const bool jside = L.j_side && (double)p.nf_pad * p.naux_pad * 8.0 >= kJSideBytes && side_stream(p);
-    hipStream_t js = jside ? p.j_stream : s;
+    SideJ side = side_begin(p, s, L.j_side && (double)p.nf_pad * p.naux_pad * 8.0 >= kJSideBytes);
+    const bool jside = side.on;
+    hipStream_t js = side.js;
     pr.mark(ST_DENSITY, true);
-    if (jside) {
-        (void)hipEventRecord(p.ev_jfork, s);
-        (void)hipStreamWaitEvent(js, p.ev_jfork, 0);
-    }
     const int dmode = L.with_D ? 2 : L.delta || jside ? 0 : 1;   // the density where k_prep does not form it
     if (!L.with_D && dmode == 0) launch_density(C, nao, (int32_t)L.ncol, 2.0, D, js);
     const double *C1 = nullptr, *C2 = nullptr;
@@ -1477,17 +1541,14 @@ void launch_build(Plan &p, const BuildLayout &L, const double *C, const double *
         C2 = W;
     } else {
         launch_prep(pre_args(p, L, L.with_D ? Din : C, L.ncol, dmode, 2.0, D, J, scratch), s);
-        if (jside && L.with_D) {   // D is copied by then
-            (void)hipEventRecord(p.ev_jfork, s);
-            (void)hipStreamWaitEvent(js, p.ev_jfork, 0);
-        }
+        if (jside && L.with_D) side_wait(side, s);   // D is copied by then
     }
     pr.mark(ST_DENSITY, false);
     launch_j(p, L, D, J, scratch, js);
     pr.stream = s;
-    if (jside) (void)hipEventRecord(p.ev_jdone, js);
+    side_end(side);
     contract_slabs(p, L, C1, C2, L.ncol, scratch, s);
-    if (jside) (void)hipStreamWaitEvent(s, p.ev_jdone, 0);
+    side_join(p, side, s);
     // split-K sum, mirror, energies (after the side stream: they read D and c)
     pr.mark(ST_KREDUCE, true);
     const int nlower = L.ntile * (L.ntile + 1) / 2;
@@ -1552,15 +1613,10 @@ void launch_build_uks(Plan &p, const BuildLayout &L, const double *Ca, const dou
     hipLaunchKernelGGL(k_add, dim3((unsigned)((nao * nao + 255) / 256)), dim3(256), 0, s, Ds[0], Ds[1], nao * nao, D);
     pr.mark(ST_DENSITY, false);
     // J on the side stream where B is large (as in launch_build)
-    const bool jside = L.j_side && (double)p.nf_pad * ld * 8.0 >= kJSideBytes && side_stream(p);
-    hipStream_t js = jside ? p.j_stream : s;
-    if (jside) {
-        (void)hipEventRecord(p.ev_jfork, s);
-        (void)hipStreamWaitEvent(js, p.ev_jfork, 0);
-    }
-    launch_j(p, L, D, J, scratch, js);
+    SideJ side = side_begin(p, s, L.j_side && (double)p.nf_pad * ld * 8.0 >= kJSideBytes);
+    launch_j(p, L, D, J, scratch, side.js);
     pr.stream = s;
-    if (jside) (void)hipEventRecord(p.ev_jdone, js);
+    side_end(side);
     for (int sp = 0; sp < 2; ++sp) {
         if (nocc[sp] == 0) {
             fill(Ks[sp], nao * nao, 0.0, s);
@@ -1574,7 +1630,7 @@ void launch_build_uks(Plan &p, const BuildLayout &L, const double *Ca, const dou
                            (int)(L.nslab * L.nsplit_k), L.ntile, L.ktile, nao, 1.0, Ds[sp], Ks[sp], Epart + sp * nep);
         pr.mark(ST_KREDUCE, false);
     }
-    if (jside) (void)hipStreamWaitEvent(s, p.ev_jdone, 0);
+    side_join(p, side, s);
     pr.mark(ST_KREDUCE, true);
     hipLaunchKernelGGL(k_energies, dim3(1), dim3(256), 0, s, cvec, ld, Epart, 2 * nep, -0.5, E);
     pr.mark(ST_KREDUCE, false);
@@ -1609,7 +1665,7 @@ void batch_nsplits(const Plan *const *plans, int n, const BuildLayout *Ls, int *
 void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const double *const *C, double *const *J,
                         double *const *K, double *const *E, char *const *scratch, hipStream_t s)
 {
-    std::vector<Plan *> joins;
+    std::vector<std::pair<Plan *, SideJ>> joins;
     std::vector<PreArgs> pre;
     std::vector<std::pair<HTArgs, int64_t>> hts, hts8;   // arguments and AO count of each grouped half transform
     std::vector<const void *> i8x;                        // grouped int8 K: slices, scales, sizes, splits, partials
@@ -1666,16 +1722,11 @@ void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const 
         p.prof.mark(ST_DENSITY, false);
         // J on the plan's side stream beside the other molecules' work,
         // joined before the energies (the only later step that reads c)
-        hipStream_t js = s;
-        if (side_stream(p)) {
-            (void)hipEventRecord(p.ev_jfork, s);
-            (void)hipStreamWaitEvent(p.j_stream, p.ev_jfork, 0);
-            js = p.j_stream;
-            joins.push_back(&p);
-        }
-        launch_j(p, L, D, J[i], sc, js);
+        SideJ side = side_begin(p, s, true);
+        launch_j(p, L, D, J[i], sc, side.js);
         p.prof.stream = s;
-        if (js != s) (void)hipEventRecord(p.ev_jdone, js);
+        side_end(side);
+        joins.emplace_back(&p, std::move(side));
         contract_slabs(p, L, nullptr, nullptr, L.ncol, sc, s);
     }
     launch_pre_group(PRE_PREP, pre, s);
@@ -1734,7 +1785,7 @@ void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const 
         grp.blk_start[grp.n] = total;
         hipLaunchKernelGGL(k_k_reduce_grouped, dim3(total, reduce_chunks(kTileK)), dim3(256), 0, s, grp, 2.0);
     }
-    for (Plan *p : joins) (void)hipStreamWaitEvent(s, p->ev_jdone, 0);
+    for (auto &j : joins) side_join(*j.first, j.second, s);
     for (int first = 0; first < n; first += kEnergyGroupMax) {
         EnergyGroup grp{};
         int m = 0;
