@@ -153,7 +153,6 @@ struct DirectState {
     int64_t quartets = 0;                // (bra, ket) pair combinations that pass the screen
     size_t table_bytes = 0;
     char *tables = nullptr;
-    const int32_t *fn_shell = nullptr;   // AO function -> shell (device)
     const int32_t *shell_off = nullptr;  // first AO function of each shell, nsh + 1 entries (device)
     const double *boys = nullptr;
     int device = -1;

@@ -946,7 +946,7 @@ static constexpr int kDirLA[6] = {0, 1, 1, 2, 2, 2}, kDirLB[6] = {0, 0, 1, 0, 1,
 
 struct DirectTables {
     size_t o_int[6][4], o_dbl[6][5], o_Eb[6], o_Ek[6];
-    size_t o_sh[5], o_fnsh, o_shoff, bytes;
+    size_t o_sh[5], o_shoff, bytes;
     int32_t npad[6];
     int64_t herm_off[6], herm_total;
 };
@@ -972,7 +972,6 @@ static DirectTables direct_tables(const Plan &p, const DirectLists &d)
         T.herm_total += nh * npad;
     }
     for (int k = 0; k < 5; ++k) T.o_sh[k] = take((size_t)std::max(p.nsh_ao, 1) * 8);
-    T.o_fnsh = take((size_t)std::max<int64_t>(p.nao, 1) * 4);
     T.o_shoff = take((size_t)(p.nsh_ao + 1) * 4);
     T.bytes = align_up(off, 256);
     return T;
@@ -1548,10 +1547,6 @@ int dfjk_direct_setup(dfjk_plan *plan, void *d_tables, size_t bytes, void *strea
     const double *sh_src[5] = {p.ao_exp.data(), p.ao_x.data(), p.ao_y.data(), p.ao_z.data(), p.ao_norm.data()};
     for (int k = 0; k < 5; ++k)
         HIP_OR_FAIL(hipMemcpyAsync(b + T.o_sh[k], sh_src[k], (size_t)p.nsh_ao * 8, hipMemcpyHostToDevice, s));
-    std::vector<int32_t> fnsh(p.nao, 0);
-    for (int a = 0; a < p.nsh_ao; ++a)
-        for (int m = p.ao_off[a]; m < p.ao_off[a + 1]; ++m) fnsh[m] = a;
-    HIP_OR_FAIL(hipMemcpyAsync(b + T.o_fnsh, fnsh.data(), (size_t)p.nao * 4, hipMemcpyHostToDevice, s));
     HIP_OR_FAIL(hipMemcpyAsync(b + T.o_shoff, p.ao_off.data(), (size_t)(p.nsh_ao + 1) * 4, hipMemcpyHostToDevice, s));
     const ShellsDev ao{(const double *)(b + T.o_sh[0]), (const double *)(b + T.o_sh[1]),
                        (const double *)(b + T.o_sh[2]), (const double *)(b + T.o_sh[3]),
@@ -1564,7 +1559,6 @@ int dfjk_direct_setup(dfjk_plan *plan, void *d_tables, size_t bytes, void *strea
     p.dir.quartets = d.quartets;
     p.dir.table_bytes = T.bytes;
     p.dir.tables = b;
-    p.dir.fn_shell = (const int32_t *)(b + T.o_fnsh);
     p.dir.shell_off = (const int32_t *)(b + T.o_shoff);
     p.dir.boys = boys_dev;
     p.dir.device = dev;

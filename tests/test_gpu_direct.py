@@ -290,3 +290,21 @@ def test_direct_row_routes(n):
     assert abs(E[0] - EJr) <= TOL * abs(EJr) and abs(E[1] - EKr) <= TOL * abs(EKr)
     assert not K[m:].any() and not K[:, m:].any()
     plan.close()
+
+
+@pytest.mark.parametrize("n", [1, 3])
+def test_direct_tables_hold_what_the_kernels_read(n):
+    """dfjk_direct_bytes: per class the pairs' offsets, shells, factors, centres, exponents and both Hermite
+    expansions, then the AO shells and their offsets, each on 256 bytes, and nothing else."""
+    z, x = W.water_cluster(n, W.cluster_box(n), 1) if n > 1 else W.water_monomer()
+    plan = _plan(W.make_molecule(z, x))
+    nsh = len(W.make_molecule(z, x).ao_l)
+    sizes = []
+    for (la, lb), pairs in zip(((0, 0), (1, 0), (1, 1), (2, 0), (2, 1), (2, 2)), plan.direct_stats()["pairs"]):
+        npad = -(-max(pairs, 1) // 64) * 64
+        lab, nf = la + lb, (2 * la + 1) * (2 * lb + 1)
+        nh = (lab + 1) * (lab + 2) * (lab + 3) // 6
+        sizes += [4 * npad] * 4 + [8 * npad] * 5 + [8 * nf * nh * npad] * 2
+    sizes += [8 * nsh] * 5 + [4 * (nsh + 1)]
+    assert plan._dtables.numel() == sum(-(-b // 256) * 256 for b in sizes)
+    plan.close()
