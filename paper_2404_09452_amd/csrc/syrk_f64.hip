@@ -387,8 +387,18 @@ void launch_syrk_f32(bool lower, const float *A, const float *B, int64_t M, int6
 // panels stay in L2; above, 64-wide tiles fall back (FP64 executed TFLOP/s at 960 /
 // 1,440 / 1,920 / 3,840 AO: 64-wide 72 / 70 / 65 / 64, 96-wide 72 / 73 / 71 / 71,
 // 128-wide 72 / 72 / 71 / 71; FP32: 121 / 111 / 106 / 103, 127 / 130 / 121 / 118,
-// 132 / 127 / 129 / 123).  The FP64 96-wide rate is that of whole builds: 960 AO, which both
-// widths tile without a ragged edge, 8.92 ms on 96-wide tiles (144 splits), 9.13 on 64.
+// 132 / 127 / 129 / 123).  The FP64 96-wide rate is that of whole builds on either
+// width: 1.02 up to 640 AO, where 64-wide tiles have half the splits, 1.00 from there to
+// 880 and rising to 1.06 at 1,020, as 64-wide panels outgrow L2 (time on 64-wide over
+// time on 96-wide tiles: 480 AO 1.007, 576 0.95, 672 1.01, 750 0.97, 768 0.98, 864
+// 1.03, 930 0.99, 944 1.00, 960 1.016, 1,008 0.97, 1,056 1.07, 1,152 1.04, 1,200 0.99,
+// 1,260 0.99, 1,344 1.04, 1,410 1.12); above 1,440, beside 64-wide tiles at 0.92, 1.04.
+static double f64_rate_96(int64_t nao)
+{
+    if (nao > 1440) return 1.04;
+    return nao <= 640 ? 1.02 : 1.0 + 0.06 * std::min(1.0, std::max(0.0, ((double)nao - 880.0) / 140.0));
+}
+
 int syrk_tile_width(int64_t nao, bool f64)
 {
     int best = 64;
@@ -396,7 +406,7 @@ int syrk_tile_width(int64_t nao, bool f64)
     for (int T : {64, 96, 128}) {
         const double n = (double)((nao + T - 1) / T);
         const double rate = T == 64 ? (nao <= (f64 ? 1440 : 960) ? 1.0 : f64 ? 0.92 : 0.88)
-                          : T == 96 ? (f64 ? 1.04 : 1.03) : (f64 ? 1.027 : 1.05);
+                          : T == 96 ? (f64 ? f64_rate_96(nao) : 1.03) : (f64 ? 1.027 : 1.05);
         double c = n * (n + 1) * T * T / rate;
         const double f = (double)((nao + 15) / 16);
         if (T == 64 && skip_edges(nao)) c = std::min(c, 1.14 * f * (f + 1) * 256.0);   // as measured with EDGES

@@ -32,9 +32,9 @@ def query(tmp_path_factory):
     return ask
 
 
-def sizes(n):
-    """nao, naux_pad and nf_pad (every pair kept) of n waters in the test basis."""
-    nao = 30 * n
+def sizes(n, extra=0):
+    """nao, naux_pad and nf_pad (every pair kept) of n waters in the test basis, with more s functions."""
+    nao = 30 * n + extra
     return nao, -(-87 * n // 128) * 128, -(-nao * (nao + 1) // 2 // 64) * 64
 
 
@@ -49,7 +49,7 @@ def layouts(query, asked):
     for a in asked:
         o = dict(aux_slab=0, k_tile=0, tuned=(0, 0), with_D=0, delta=0, nsplit=0, overlap=1, force_slab=0, ktile=0)
         o.update(a)
-        nao, naux, nf = sizes(o["n"])
+        nao, naux, nf = sizes(o["n"], o.get("extra", 0))
         lines.append("layout %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d" % (
             nao, naux, nf, o["aux_slab"], o["k_tile"], *o["tuned"], o["nocc"], o["precision"], o["with_D"], o["delta"],
             o["nsplit"], o["overlap"], o["force_slab"], o["ktile"]))
@@ -131,3 +131,23 @@ def test_fp32_partials_stay_small(query):
         for slab in (0, 128, 256, 640, 1024):
             L, = layouts(query, [dict(n=n, nocc=5 * n, precision=FP32, aux_slab=slab)])
             assert L.kpart <= max(6e9, L.kpart // L.nsub), (n, slab)
+
+
+# whole FP64 builds, time on 64-wide over time on 96-wide tiles (AO count: n waters and more s functions)
+MEASURED = {(16, 32): 0.872, (18, 0): 0.938, (19, 6): 0.946, (20, 0): 0.886, (21, 0): 0.899, (23, 0): 0.889,
+            (24, 0): 0.932, (24, 16): 0.964, (25, 0): 0.971, (25, 18): 0.977, (26, 0): 0.898, (27, 0): 0.935,
+            (28, 24): 1.033, (29, 0): 0.908, (30, 0): 0.986, (31, 0): 0.992, (32, 0): 1.014, (32, 16): 0.958,
+            (33, 0): 0.977, (33, 18): 0.974, (35, 0): 1.070, (35, 6): 1.075, (36, 0): 0.957, (37, 0): 1.041,
+            (38, 12): 1.041, (39, 0): 1.011, (40, 0): 0.991, (42, 0): 0.992, (44, 24): 1.044, (47, 0): 1.119}
+
+
+def test_fp64_tile_width_follows_measurement(query):
+    """The FP64 tile rule takes the width that was faster wherever the two differ by 1% or more (1.5% on the
+    side of 96-wide tiles, whose ragged sizes it takes as 64-wide)."""
+    for (n, extra), ratio in MEASURED.items():
+        L, = layouts(query, [dict(n=n, extra=extra, nocc=5 * n, precision=FP64)])
+        if ratio <= 0.99:
+            assert L.ktile == 64, 30 * n + extra
+        elif ratio >= 1.015:
+            assert L.ktile == 96, 30 * n + extra
+    assert layouts(query, [dict(n=32, nocc=160, precision=FP64)])[0].ktile == 96
