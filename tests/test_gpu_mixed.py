@@ -301,3 +301,39 @@ def test_autotune_codes_at_large_split_counts():
     K = plan.build(C=C, precision="fp32")[1]
     d = torch.sqrt(torch.diagonal(K0).clamp(min=0))
     assert ((K - K0).abs() <= 1100 * 2.0 ** -53 * torch.outer(d, d)).all()
+
+
+@pytest.mark.parametrize("n,nocc,slab", [(3, 15, 0), (5, 25, 384), (7, 35, 256), (12, 60, 0)])
+def test_fp32_increment_elements(n, nocc, slab):
+    """The FP32 increment (128-wide tiles, every tile) for a real step, element by element against the FP64
+    one: (2^-15 + 2^-23) (S + S^T), S = sum_k |x_U||x_W| <= sqrt(G_U,mu mu G_W,nu nu) by Cauchy-Schwarz
+    with G_U = X_U X_U^T = K(U) / 2; the step itself is far larger than that."""
+    mol, S, C = case(n, nocc=nocc)
+    plan = G.Plan.from_molecule(mol, schwarz_thresh=TAU, aux_slab=slab).screen().setup()
+    C1 = W.perturbed_orbitals(C, S, 1, eps=1e-2, seed=1000)
+    K0 = plan.build(C=C)[1].clone()
+    K64 = plan.build_delta(C1, C, K0, precision="fp64")[1].clone()
+    K32 = plan.build_delta(C1, C, K0, precision="fp32")[1].clone()
+    u, _, vt = np.linalg.svd(C1.T @ C)
+    Cr = C1 @ (u @ vt)               # the build rotates C1 onto C first (orthogonal polar factor)
+    du, dw = (torch.sqrt(torch.diagonal(plan.build(C=X)[1]) / 2) for X in (Cr + C, Cr - C))
+    bound = torch.outer(du, dw)
+    tol = (2.0 ** -15 + 2.0 ** -23) * (bound + bound.T) + 1e-14 * K0.abs().max()
+    assert torch.equal(K32, K32.T)
+    assert ((K32 - K64).abs() / tol).max().item() <= 1.0
+    assert ((K64 - K0).abs() / tol).max().item() >= 100.0
+
+
+@pytest.mark.parametrize("nocc,slab", [(33, 0), (20, 512)])
+def test_fp32_128_wide_tiles(nocc, slab):
+    """FP32 K on the lower 128-wide tiles that the rule takes at 990 AO (a ragged last tile of 94 rows),
+    in one aux slab and in several, with the bound of the other widths."""
+    mol, S, C = case(33, nocc=nocc)
+    plan = G.Plan.from_molecule(mol, schwarz_thresh=TAU, aux_slab=slab).screen().setup()
+    assert plan.build_shape(nocc, "fp32")["k_tile"] == 128
+    K0 = plan.build(C=C)[1].clone()
+    K = plan.build(C=C, precision="fp32")[1]
+    assert torch.equal(K, K.T)
+    d = torch.sqrt(torch.diagonal(K0).clamp(min=0))
+    tol = (2.0 ** -15 + 2.0 ** -23) * torch.outer(d, d) + 1e-14 * K0.abs().max()
+    assert ((K - K0).abs() / tol).max().item() <= 1.0
