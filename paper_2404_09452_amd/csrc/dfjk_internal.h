@@ -402,7 +402,7 @@ void launch_syrk_f64(bool lower, const double *A, const double *B, int64_t M, in
                      int nsplit, int T, double *partial, hipStream_t s);
 void launch_syrk_f32(bool lower, const float *A, const float *B, int64_t M, int64_t kdim, int64_t ksplit, int nsplit,
                      int nsub, int T, double *partial, hipStream_t s);
-int syrk_tile_width(int64_t nao, bool f64);
+int syrk_tile_width(int64_t nao, int64_t kdim, bool f64, int num_cus);
 void launch_syrk_f64_group(int T, int n, const double *const *A, const int64_t *M, const int64_t *kdim,
                            const int64_t *ksplit, const int *nsplit, double *const *partial, hipStream_t s);
 void launch_gemm_nt_tri(const double *A, const double *B, double *C, int64_t M, int64_t N, int64_t ld,

@@ -1008,38 +1008,12 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     L.with_D = with_D;
     L.crows = c_split_rows(p.nf_pad, force_slab > 0);
     L.nsplit_c = (int)((p.nf_pad + L.crows - 1) / L.crows);
-    // Tile width of the K contraction: for FP64 (C and density routes) and FP32
-    // the rule of syrk_tile_width, for int8_fast that of i8_fast_tile; for FP64
-    // the autotuner's choice for the shape, or the caller's, wins.  int8, BF16x3
-    // and every increment keep 128.
-    // With a forced slab (the static scratch) the built-in shapes are those of the
-    // smallest partial tiles: 64-wide FP64 tiles where 128-wide ones execute over 14%
-    // more products, else 128, and no more splits than one per 256 k.
-    L.ktile = kTileK;
     const bool fixed = force_slab > 0;
     KShape tuned{0, 0};
     if (nsplit == 0 && !with_D && !delta) {
         const auto it = p.tuned.find((int64_t)nocc * 8 + precision);
         if (it != p.tuned.end()) tuned = it->second;
     }
-    if (fixed && precision == DFJK_FP64) {
-        auto executed = [&](int64_t t) { const int64_t n = (p.nao + t - 1) / t; return n * (n + 1) / 2 * t * t; };
-        const int kt = p.k_tile != 0 ? p.k_tile : tuned.tile;
-        if (kt == 64 || kt == 96) L.ktile = kt;
-        else if (kt == 0 && (double)executed(kTileK) > 1.14 * (double)executed(64)) L.ktile = 64;
-    } else if ((precision == DFJK_FP64 || precision == DFJK_MIXED_FP32) && !delta && !fixed) {
-        int kt = ktile;
-        if (kt == 0 && precision == DFJK_FP64) kt = p.k_tile;
-        if (kt == 0) kt = tuned.tile;
-        L.ktile = kt == 64 || kt == 96 || kt == kTileK ? kt : syrk_tile_width(p.nao, precision == DFJK_FP64);
-    }
-    if (fixed && (precision == DFJK_MIXED_FP32 || precision == DFJK_MIXED_INT8_FAST) && tuned.tile != 0)
-        L.ktile = tuned.tile;
-    if (precision == DFJK_MIXED_INT8_FAST && !delta && !fixed) {
-        const int kt = ktile != 0 ? ktile : tuned.tile;
-        L.ktile = kt == 64 || kt == kTileK ? kt : i8_fast_tile(p.nao);
-    }
-    L.ntile = (int)((p.nao + L.ktile - 1) / L.ktile);
     L.delta = delta;
     // aux slab of the K build: X = nao x slab x ncol elements per operand
     // bytes of X per element (both BF16 planes; int8 slices plus block scales)
@@ -1085,6 +1059,32 @@ BuildLayout build_layout(const Plan &p, int32_t nocc, int32_t precision, bool wi
     L.overlap = may_overlap && L.nslab >= 2;
     L.j_side = allow_overlap && !p.host_B;
     L.kdim = x_kdim(precision, slab, L.ncol);
+    // Tile width of the K contraction: for FP64 (C and density routes) and FP32
+    // the rule of syrk_tile_width, for int8_fast that of i8_fast_tile; for FP64
+    // the autotuner's choice for the shape, or the caller's, wins.  int8, BF16x3
+    // and every increment keep 128.
+    // With a forced slab (the static scratch) the built-in shapes are those of the
+    // smallest partial tiles: 64-wide FP64 tiles where 128-wide ones execute over 14%
+    // more products, else 128, and no more splits than one per 256 k.
+    L.ktile = kTileK;
+    if (fixed && precision == DFJK_FP64) {
+        auto executed = [&](int64_t t) { const int64_t n = (p.nao + t - 1) / t; return n * (n + 1) / 2 * t * t; };
+        const int kt = p.k_tile != 0 ? p.k_tile : tuned.tile;
+        if (kt == 64 || kt == 96) L.ktile = kt;
+        else if (kt == 0 && (double)executed(kTileK) > 1.14 * (double)executed(64)) L.ktile = 64;
+    } else if ((precision == DFJK_FP64 || precision == DFJK_MIXED_FP32) && !delta && !fixed) {
+        int kt = ktile;
+        if (kt == 0 && precision == DFJK_FP64) kt = p.k_tile;
+        if (kt == 0) kt = tuned.tile;
+        L.ktile = kt == 64 || kt == 96 || kt == kTileK ? kt : syrk_tile_width(p.nao, L.kdim, precision == DFJK_FP64, p.num_cus);
+    }
+    if (fixed && (precision == DFJK_MIXED_FP32 || precision == DFJK_MIXED_INT8_FAST) && tuned.tile != 0)
+        L.ktile = tuned.tile;
+    if (precision == DFJK_MIXED_INT8_FAST && !delta && !fixed) {
+        const int kt = ktile != 0 ? ktile : tuned.tile;
+        L.ktile = kt == 64 || kt == kTileK ? kt : i8_fast_tile(p.nao);
+    }
+    L.ntile = (int)((p.nao + L.ktile - 1) / L.ktile);
     const int ntiles = delta ? L.ntile * L.ntile : L.ntile * (L.ntile + 1) / 2;
     // FP64 and FP32 syrk: enough splits for 32 workgroups per CU with 96-wide tiles, 64
     // with 64-wide ones (32 in FP64 up to 640 AO, where more lengthen the reduction by as much)

@@ -381,35 +381,46 @@ void launch_syrk_f32(bool lower, const float *A, const float *B, int64_t M, int6
     launch_syrk<float>(lower, A, B, M, kdim, ksplit, ksub, nsplit, nsub, T, partial, s);
 }
 
-// Output tile of the FP64 and FP32 K: the width that executes the fewest
-// products (whole tiles, the diagonal ones included) at the rate each reaches.
-// Rates relative to 64-wide tiles on up to 1,440 AO (960 in FP32), where a split's
-// panels stay in L2; above, 64-wide tiles fall back (FP64 executed TFLOP/s at 960 /
-// 1,440 / 1,920 / 3,840 AO: 64-wide 72 / 70 / 65 / 64, 96-wide 72 / 73 / 71 / 71,
-// 128-wide 72 / 72 / 71 / 71; FP32: 121 / 111 / 106 / 103, 127 / 130 / 121 / 118,
-// 132 / 127 / 129 / 123).  The FP64 96-wide rate is that of whole builds on either
-// width: 1.02 up to 640 AO, where 64-wide tiles have half the splits, 1.00 from there to
-// 880 and rising to 1.06 at 1,020, as 64-wide panels outgrow L2 (time on 64-wide over
-// time on 96-wide tiles: 480 AO 1.007, 576 0.95, 672 1.01, 750 0.97, 768 0.98, 864
-// 1.03, 930 0.99, 944 1.00, 960 1.016, 1,008 0.97, 1,056 1.07, 1,152 1.04, 1,200 0.99,
-// 1,260 0.99, 1,344 1.04, 1,410 1.12); above 1,440, beside 64-wide tiles at 0.92, 1.04.
-static double f64_rate_96(int64_t nao)
+// Output tile of the FP64 and FP32 K (kdim long): the width that executes the fewest
+// products (whole tiles, the diagonal ones included) at the rate each reaches, relative
+// to 64-wide tiles on few AO.
+//
+// FP64, from whole builds on every width (480 to 2,160 AO, nao / 30 to nao orbitals; the
+// rule's choice is 0.2% slower than the best on average, 4.7% at worst).  Up to 1,440 AO
+// 64-wide tiles fall back as the panels of one of their splits, nao x k, outgrow an
+// XCD's L2 (4 MB; time on 64-wide over time on 96-wide tiles, with the panels: 750 AO
+// 0.97 at 8 MB, 1.03 at 23, 1.08 at 47; 960 AO 0.99 at 5, 1.02 to 1.04 at 25, 1.06 at 76; 1,200
+// AO 0.96 at 17, 1.02 at 86), and up to 640 AO they have half the splits.  Above,
+// rates in TFLOP/s executed (1,920 / 3,840 AO): 64-wide 65 / 64, 96-wide 71 / 71,
+// 128-wide 71 / 71; whole builds on 128-wide tiles gain from 1,800 AO on (1,650 / 1,740 /
+// 1,860 / 1,920 / 2,160 AO: 78.6 and 76.0, 96.6 and 96.9, 128.8 and 120.7, 133.6 and
+// 127.9, 213 and 203 ms on 96- and 128-wide tiles).
+//
+// FP32 executed TFLOP/s at 960 / 1,440 / 1,920 / 3,840 AO: 64-wide 121 / 111 / 106 / 103,
+// 96-wide 127 / 130 / 121 / 118, 128-wide 132 / 127 / 129 / 123 (the choice within 3%
+// of the autotuner's best at 22 of 23 sizes from 420 to 1,560 AO, 4.5% at the other).
+static double tile_rate(int T, int64_t nao, int64_t kdim, bool f64, int num_cus)
 {
-    if (nao > 1440) return 1.04;
-    return nao <= 640 ? 1.02 : 1.0 + 0.06 * std::min(1.0, std::max(0.0, ((double)nao - 880.0) / 140.0));
+    if (!f64) return T == 64 ? (nao <= 960 ? 1.0 : 0.88) : T == 96 ? 1.03 : 1.05;
+    if (nao > 1440) return T == 64 ? 0.92 : T == 96 ? 1.04 : nao <= 1780 ? 1.027 : 1.10;
+    const int64_t t = (nao + 63) / 64, slots = (nao <= 640 ? 32 : 64) * (int64_t)(num_cus > 0 ? num_cus : 256);
+    const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(slots / (t * (t + 1) / 2), kdim / 512));
+    const double panel = 8e-6 * (double)nao * (double)(kdim / splits);
+    const double large = std::min(1.0, std::max(0.0, (panel - 14.0) / 22.0));
+    if (T == 64) return 1.0;
+    return T == 96 ? std::max(1.0 + 0.08 * large, nao <= 640 ? 1.02 : 1.0) : 1.027 + 0.028 * large;
 }
 
-int syrk_tile_width(int64_t nao, bool f64)
+int syrk_tile_width(int64_t nao, int64_t kdim, bool f64, int num_cus)
 {
     int best = 64;
     double cost = 1e300;
     for (int T : {64, 96, 128}) {
         const double n = (double)((nao + T - 1) / T);
-        const double rate = T == 64 ? (nao <= (f64 ? 1440 : 960) ? 1.0 : f64 ? 0.92 : 0.88)
-                          : T == 96 ? (f64 ? f64_rate_96(nao) : 1.03) : (f64 ? 1.027 : 1.05);
-        double c = n * (n + 1) * T * T / rate;
+        double c = n * (n + 1) * T * T;
         const double f = (double)((nao + 15) / 16);
         if (T == 64 && skip_edges(nao)) c = std::min(c, 1.14 * f * (f + 1) * 256.0);   // as measured with EDGES
+        c /= tile_rate(T, nao, kdim, f64, num_cus);
         if (c < cost) { cost = c; best = T; }
     }
     return best;
