@@ -110,8 +110,9 @@ typedef struct {
                                     (syrk): 0 = dfjk_autotune's choice for the
                                     shape, else the width that executes the
                                     fewest products at the rate it reaches
-                                    (64 up to 1,440 AO mostly, else 96 or
-                                    128); 64, 96 or 128 = that
+                                    (64 mostly; 96 or 128 where they fit, the
+                                    more often the larger nao and the number
+                                    of orbitals); 64, 96 or 128 = that
                                     tile for every FP64 syrk of the plan.
                                     Other values are DFJK_E_INVALID.          */
 } dfjk_options;
@@ -274,10 +275,11 @@ int dfjk_build_delta(dfjk_plan *plan, const double *d_C, const double *d_C0, int
  * A batch of n closed-shell builds (molecules of any sizes, each with its own
  * set-up plan, all on the current device) on one stream: the same results as
  * n dfjk_build calls with d_C[i] (nao_i x nocc[i]), up to the order of the
- * split-K sums, but the K contractions of all FP64 molecules whose
- * half-transformed tensor fits one aux slab share one grouped launch (16
- * molecules per launch), with split counts chosen together to fill the chip,
- * and the split-K reductions and energies run as grouped launches too.  This
+ * split-K sums, but the FP64, int8 and int8_fast molecules whose
+ * half-transformed tensor fits one aux slab share the launches of every step
+ * (16 molecules per launch; K one per tile width, in FP64 with split counts
+ * chosen together), and the split-K reductions and energies of all molecules
+ * run as grouped launches.  This
  * is the serving form for many small molecules, where per-launch overhead
  * dominates.  plans, d_C, nocc, d_J, d_K, d_E are host arrays of n entries;
  * outputs as for dfjk_build.  d_scratch must hold dfjk_build_batch_bytes
@@ -437,8 +439,8 @@ int dfjk_build_uks(dfjk_plan *plan, const double *d_Ca, int32_t nocc_a, const do
  *   d_C: nao x nocc occupied orbitals (D = 2 C C^T), 1 <= nocc <= nao, or
  *   d_D: nao x nao symmetric density (nocc ignored),
  * and writes d_J, d_K (nao x nao, full symmetric, must not alias) and
- * d_E[2] = {E_J, E_K} = {1/2 Tr(D J), -1/4 Tr(D K)}.  FP64 throughout; K is
- * accumulated with atomics, so its last bits may differ between runs.
+ * d_E[2] = {E_J, E_K} = {1/2 Tr(D J), -1/4 Tr(D K)}.  FP64 throughout; J and K
+ * are accumulated with atomics, so their last bits may differ between runs.
  * d_scratch must hold dfjk_direct_build_bytes(plan, d_D != NULL).  No host
  * synchronisation; safe to capture in a HIP graph.
  *
@@ -515,12 +517,13 @@ int dfjk_boys(int32_t mmax, int64_t n, const double *d_T, double *d_F, void *str
  * DFJK_NSTAGES stages (host arrays), and clears the record.
  * dfjk_stage_name(i) names stage i ("build.K", ...).  "span.build" is a whole
  * dfjk_build (C or D route) from its first to its last launch on the caller's
- * stream: J runs on a side stream beside the half transform and K, so the
- * "build.*" stages of one build overlap and their sum exceeds the span.
- * "span.setup" is a whole dfjk_setup alike: the integrals, then the block
- * rows of L^-1, run on the side stream beside the metric and its factor, so
- * "setup.inverse" is the span of the inverse's steps, most of it beside
- * "setup.cholesky". */
+ * stream: where B is 64 MB or larger, J runs on a side stream beside the half
+ * transform and K, so the "build.*" stages of one build overlap and their sum
+ * exceeds the span.
+ * "span.setup" is a whole dfjk_setup alike: the integrals run on the side
+ * stream beside the metric and its factor, and above 512 auxiliary functions
+ * the block rows of L^-1 follow them there, so that "setup.inverse" is the
+ * span of the inverse's steps, most of it beside "setup.cholesky". */
 #define DFJK_NSTAGES 12
 int dfjk_profile(dfjk_plan *plan, int32_t on);
 int dfjk_profile_read(dfjk_plan *plan, double *ms, int32_t *count);

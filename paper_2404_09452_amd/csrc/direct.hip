@@ -34,11 +34,16 @@
 // million vector loads; from LDS 2.79 ms, 21 million).
 //
 // What bounds it: the latency of FP64 chains (Boys function, Hermite recursion) and of
-// the table loads at 1 to 3 waves per SIMD; the instructions issued would fill 1.2 ms of
-// the 3.6 ms that the three launches take on 32 waters at threshold 1e-10.  Before, every
+// the table loads at 1 to 3 waves per SIMD, and in the heaviest classes spills ((dd|dd)
+// holds 165 values of R, 330 of its 512 registers: 533 stores to and 1,522 loads from
+// scratch in its code, (dd|dp) 419 and 472, (dd|pp) 260 and 301; the others save and
+// restore registers only); the instructions issued would fill 1.2 ms of the 3.8 ms that
+// the three launches take on 32 waters at threshold 1e-10.  Before, every
 // ordered combination was visited, in 36 launches, and every quartet added its K blocks
-// to memory with scattered FP64 atomics (16 of 31 ms).  Now against then: 3.6 ms
-// against 30, and 0.49 ms against 3.0 for an incremental build of 8 waters.
+// to memory with scattered FP64 atomics (16 of 31 ms).  Whole builds now against then:
+// 3.9 ms against 34, 0.49 against 3.2 for an incremental build of 8 waters; past the sizes
+// whose rows fit LDS: 35 waters (D rows of the heavy launch in memory) 4.6 against 34,
+// 48 9.0 against 67, 64 17 against 125, 70 (K rows too) 25 against 148.
 #include "dfjk_internal.h"
 #include "hermite.h"
 
@@ -462,7 +467,7 @@ __device__ __noinline__ void direct_quartets(JobPtr job_, int u_, int piece_, in
 // 256 (2, 8 waves) and up to 168 (3, 6 waves).  Classes of one launch run side by
 // side: one launch per combination took 1.20 ms instead of 0.54 for the incremental build
 // of 8 waters.  Squeezing (dp|dp) and lighter ones of the first launch into 256 registers,
-// for a second wave, spills: 4.31 ms instead of 3.82 on 32 waters.  The row counts
+// for a second wave, makes them spill too: 4.31 ms instead of 3.82 on 32 waters.  The row counts
 // keep two sets of rows (K and D) in LDS up to 1,024, 1,280 and 2,560 AO; beyond, K alone
 // up to twice that, and then neither.
 #define COMBOS_0(X) X(0, 2, 2, 2, 2) X(1, 2, 2, 2, 1) X(2, 2, 1, 2, 1) X(3, 2, 2, 1, 1) X(4, 2, 2, 2, 0)       \

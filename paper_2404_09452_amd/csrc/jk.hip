@@ -1658,10 +1658,11 @@ void batch_nsplits(const Plan *const *plans, int n, const BuildLayout *Ls, int *
     }
 }
 
-// A batch of closed-shell builds on one stream.  Per molecule: density, J and
-// the half transform; then one grouped FP64 K launch over every molecule
-// whose X fits one slab, one grouped split-K reduction and one grouped energy
-// launch.  Mixed precision and multi-slab molecules contract on their own.
+// A batch of closed-shell builds on one stream.  The FP64, int8 and int8_fast
+// molecules whose X fits one slab share launches of every step: density and padded
+// coefficients, half transforms (by fragment count), c and J, K (by tile width).  The
+// others (FP32, BF16x3, several slabs) form and contract X on their own, J beside them.
+// Then one grouped split-K reduction and one grouped energy launch for all.
 void launch_build_batch(int n, Plan *const *plans, const BuildLayout *Ls, const double *const *C, double *const *J,
                         double *const *K, double *const *E, char *const *scratch, hipStream_t s)
 {
