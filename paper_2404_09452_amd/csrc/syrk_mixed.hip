@@ -532,7 +532,10 @@ int i8_fast_tile(int64_t nao) { return nao <= 1440 ? 64 : T; }
 // count up to 64 (128 above 960 AO: short k ranges keep a split's panels in L2) of
 // at least four scale blocks each, within 5% of the fewest rounds of the chip
 // (960 AO, 16 / 24 / 32 / 64 splits: 2.42 / 2.34 / 2.19 / 2.13 ms; 1,440 AO, 32 /
-// 64 / 128: 15.3 / 13.5 / 12.2 ms).  128-wide tiles (half a tile per workgroup,
+// 64 / 128: 15.3 / 13.5 / 12.2 ms), or of the best multiple where that is within 30%:
+// whole splits per XCD count for more than even rounds (whole builds of 390 / 420 / 510 /
+// 570 / 690 AO with 18 / 54 / 28 / 45 / 62 splits 0.380 / 0.488 / 0.823 / 1.01 / 2.08 ms, with
+// 16 / 32 / 56 / 64 / 64 0.341 / 0.434 / 0.719 / 0.884 / 1.90).  128-wide tiles (half a tile per workgroup,
 // one per CU), all with the same k length: the time is (rounds of workgroups) x
 // (k per split); counts that are multiples of the XCD count run whole splits per
 // XCD (rounds counted per XCD), smaller k lengths fall back to any count.
@@ -558,6 +561,11 @@ int i8_nsplit(int64_t nao, int64_t kdim, bool lower, int tile, int num_cus)
     if (tile != T) {
         for (int ns = maxs / kXcds * kXcds; ns > 0; ns -= kXcds)
             if (cost[ns] <= 1.05 * best) return ns;
+        double whole = 1e300;
+        for (int ns = kXcds; ns <= maxs; ns += kXcds) whole = std::min(whole, cost[ns]);
+        if (whole <= 1.3 * best)
+            for (int ns = maxs / kXcds * kXcds; ns > 0; ns -= kXcds)
+                if (cost[ns] <= 1.05 * whole) return ns;
         for (int ns = maxs; ns > 1; --ns)
             if (cost[ns] <= 1.05 * best) return ns;
         return 1;

@@ -133,6 +133,14 @@ def test_fp32_partials_stay_small(query):
             assert L.kpart <= max(6e9, L.kpart // L.nsub), (n, slab)
 
 
+def test_int8_fast_whole_splits_per_xcd(query):
+    """int8_fast on 64-wide tiles: a split count that is a multiple of the 8 XCDs from 6 waters on, where
+    there are enough scale blocks for two splits of each (10 to 18% of a build at 13 to 23 waters)."""
+    for n in range(6, 49):
+        L, = layouts(query, [dict(n=n, nocc=5 * n, precision=INT8_FAST)])
+        assert L.ktile == 64 and L.nsplit % 8 == 0, (n, L.nsplit)
+
+
 # whole FP64 builds on 64-, 96- and 128-wide tiles, times over the fastest (9: not timed), where one
 # width is 1% ahead: (waters, more s functions, orbitals)
 MEASURED = {(10, 0, 10): (1, 1.116, 1.152), (10, 0, 50): (1, 1.27, 1.298), (10, 0, 150): (1, 1.318, 1.453),
